@@ -13,6 +13,7 @@
 #include <new>
 
 #include "common.h"
+#include "dft8.h"
 #include "kernels.h"
 
 namespace tfhe {
@@ -415,11 +416,9 @@ static int tfhe_cloud_key_upload_impl(tfhe_cloud_key *ck) {
     TFHE_HIP(hipGetDevice(&ck->device));
     release_device_keys(ck);          // an earlier attempt may have failed half-way
 
-    // twiddle table psi^j = exp(i pi j / 1024), j < 2048, evaluated in extended precision
-    std::vector<double2> tables(2048);
-    const long double pi = 3.14159265358979323846264338327950288L;
-    for (int j = 0; j < 2048; ++j)
-        tables[j] = make_double2((double)cosl(pi * j / 1024), (double)sinl(pi * j / 1024));
+    // powers of psi = exp(i pi / 1024) and the constants of the eight-point passes
+    std::vector<double2> tables(fft512::kTableWords);
+    fft512::fill_tables(tables.data());
     TFHE_HIP(hipMalloc((void **)&ck->d_tables, tables.size() * sizeof(double2)));
     TFHE_HIP(hipMemcpy(ck->d_tables, tables.data(), tables.size() * sizeof(double2), hipMemcpyHostToDevice));
 

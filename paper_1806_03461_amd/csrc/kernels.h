@@ -12,8 +12,9 @@ struct BlindRotateArgs {
                                  // item 2g+1 is AND(NOT in0[g], in1_alt[g])
     uint32_t *ext;               // device [count][1025]: extracted samples
     size_t count;
+    size_t first;                // set by the launcher: a launch takes items first .. count - 1
     const double2 *bk_fft;       // device [n][4][4][512]
-    const double2 *tables;       // device [2048]: exp(i pi j / 1024)
+    const double2 *tables;       // device: exp(i pi j / 1024), j < 2048, and the constants of dft8.h
     int n, bgbit;
     double *margin;              // device, optional: largest rounding distance seen
 };

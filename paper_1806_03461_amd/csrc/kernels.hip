@@ -20,6 +20,7 @@
 #include <cstdlib>
 
 #include "common.h"
+#include "dft8.h"
 #include "fft512.h"
 #include "kernels.h"
 
@@ -187,7 +188,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         else __builtin_amdgcn_s_setprio(0);
     };
 
-    for (size_t gi = blockIdx.x; gi < a.count; gi += gridDim.x) {
+    for (size_t gi = a.first + blockIdx.x; gi < a.count; gi += gridDim.x) {
     // ---- prologue ----
     {
         int op = a.uniform_op;
@@ -405,6 +406,394 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 template <bool MARGIN>
 __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu(1, 1))) void blind_rotate_latency_kernel(BlindRotateArgs a) {
     blind_rotate_body<MARGIN, 4>(a);
+}
+
+// ------------------------------------------------------------------------------------------
+// Blind rotation of large batches: one gate per wavefront, four gates per workgroup of 256 threads, two
+// workgroups per CU (256 VGPRs a wave).
+//
+// A lane holds all four digit spectra of its eight frequencies (x[4][8], 128 registers), so the products
+// need no exchange between lanes and no barrier stands between a wave and its data: against the four-wave
+// kernel the 256 lane swaps of a gate's step and three barriers are gone, both digits of a component come
+// from one rotated read and one subtraction, and both limbs of an output are added before one LDS
+// accumulation.  With the twiddles of dft8.h a step is 2,500 vector instructions per gate (3,430 issue
+// slots in the four-wave kernel).  A polynomial passes through one 9 KB buffer that belongs to the wave; LDS
+// operations of a wave execute in order, so the stores of one polynomial may follow the loads of the one
+// before it at once.
+//
+// What bounds it: at 2,048 gates or more, about 1,830 ns per gate-step and CU -- vector instructions 68 % of
+// the time, LDS and the key stream through L1 (128 KB per gate-step at 64 B a clock) about half each -- while
+// the clock has dropped to 2.0 GHz, i.e. the chip is at its power limit.  12,288 gates 52.3 -> 44.0 ms.
+// What it took, one by one on 12,288 gates: without the twiddles of dft8.h + 2.6 ms; without the barrier
+// before the products + 6 ms (below); without the priorities + 3 ms (below); without interleaving LDS
+// instructions with arithmetic + 2 ms.  Key rows brought to LDS by loads to LDS and read by all four waves
+// instead of four L1 reads: equal (the LDS pipe then carries what L1 carried).
+//
+// Barrier before the products: the four waves of a workgroup then read the key row together and three
+// quarters of their reads hit L1 (265 instead of 1,024 lines per gate-step from L2); without it the waves of
+// an XCD spread over more rows than its L2 holds.
+// Priorities: the inverse transforms and the first half of the forward ones issue ahead of the second half and
+// the products.  Each half holds half of a step's arithmetic, so the two waves of a SIMD fall into opposite
+// halves: one computes while the other waits for LDS and keys.  One level less or more, or the change
+// at another place, is 1 to 7 % slower.
+// ------------------------------------------------------------------------------------------
+constexpr int kWaveGates = 4;      // waves (= gates) of a workgroup
+constexpr int kKeyRing = 4;        // key batches (one output at one frequency: four 16-byte loads) in registers
+
+struct WaveLds {
+    double2 buf[kWaveGates][8 * kRowStride];
+    uint32_t acc[kWaveGates][2][kN + kMirror];     // as in GateLds
+    double2 fwd2[64], inv2[64], inv1[512];         // constants of dft8.h, in the order of the table in memory
+};
+static_assert(2 * sizeof(WaveLds) <= 160 * 1024, "two workgroups share a CU's LDS");
+
+// Scheduling patterns of the instructions between two region ends: eight stores to LDS, then eight
+// loads, each followed by V vector instructions of other work, instead of sixteen LDS instructions in a row.
+#define REGION_END() __builtin_amdgcn_sched_barrier(0)
+#define ONE_STORE(V) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0); __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+#define ONE_LOAD(V) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+#define EIGHT(X, V) X(V) X(V) X(V) X(V) X(V) X(V) X(V) X(V)
+#define TRANSPOSE_BESIDE(V) EIGHT(ONE_STORE, V) EIGHT(ONE_LOAD, V)
+
+template <bool MARGIN>
+__global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu(2, 2))) void blind_rotate_wave_kernel(BlindRotateArgs a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    WaveLds &my = *reinterpret_cast<WaveLds *>(lds_raw);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int L = threadIdx.x & 63;
+    const size_t slot = a.first + (size_t)blockIdx.x * kWaveGates + wv;
+    const size_t gi = slot < a.count ? slot : a.count - 1;      // a wave without a gate repeats the last one and writes nothing
+    uint32_t (&acc)[2][kN + kMirror] = my.acc[wv];
+    double2 *const buf = my.buf[wv];
+    double2 *const mine = buf + (L >> 3) * kRowStride;          // passes 2, 3: lane = 8 k0 + (j0 or k1)
+    for (int e = threadIdx.x; e < 64 + 64 + 512; e += 64 * kWaveGates) my.fwd2[e] = a.tables[kFwd2 + e];
+    Shift8 f3;
+    f3.h4 = a.tables[kFwd3 + L];
+    f3.h2 = a.tables[kFwd3 + 64 + L];
+    f3.h1 = a.tables[kFwd3 + 128 + L];
+    f3.h1w = a.tables[kFwd3 + 192 + L];
+    const __amdgpu_buffer_rsrc_t key_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<double2 *>(a.bk_fft), 0, (int)((size_t)a.n * 16 * kHalf * sizeof(double2)), 0x00020000);
+    // slot 256 q + 64 w + lane' of the key rows is frequency k0 = 2 w + (lane' >> 3 & 1), k1 = lane' & 7,
+    // k2 = 2 (lane' >> 4) + q; here lane = 8 k0 + k1 reads it at its own part (L >> 4) * 64 + L % 16 plus
+    // 256 (k2 & 1) + 16 (k2 >> 1): four runs of 256 consecutive bytes per load
+    const uint32_t voff = (uint32_t)((L >> 4) * 64 + (L & 15)) * (uint32_t)sizeof(double2);
+    double worst = 0.0;
+
+    int op = a.uniform_op;
+    size_t i0 = gi, i1 = gi;
+    uint32_t s0 = 1u, s1 = 1u;
+    const uint32_t *src1 = a.in1;
+    if (a.recs) {
+        const tfhe_gate_rec r = a.recs[gi];
+        op = r.op; i0 = (size_t)r.in0; i1 = (size_t)r.in1;
+        s0 = r.neg0 ? 0xFFFFFFFFu : 1u; s1 = r.neg1 ? 0xFFFFFFFFu : 1u;
+    } else if (op == TFHE_MUX) {
+        i0 = i1 = gi >> 1;
+        if (gi & 1) { op = TFHE_MUX_ELSE; src1 = a.in1_alt; }
+    }
+    if (op == TFHE_MUX_ELSE) s0 = 0u - s0;
+    if (op >= TFHE_MUX) op = TFHE_AND;
+    uint32_t kappa, mult;
+    gate_constants(op, kappa, mult);
+    const uint32_t *c0 = a.in0 + i0 * ((size_t)a.n + 1), *c1 = src1 + i1 * ((size_t)a.n + 1);
+    auto rotation = [&](int j) -> int {
+        uint32_t c = mult * (s0 * c0[j] + s1 * c1[j]);
+        if (j == a.n) c += kappa;
+        return (int)(((c + (1u << 20)) >> 21) & 2047u);
+    };
+    {
+        const int bbar = __builtin_amdgcn_readfirstlane(rotation(a.n));
+        const int bb = bbar & (kN - 1);
+        const uint32_t first = bbar < kN ? kEighth : 0u - kEighth;
+        for (int j = L; j < kN; j += 64) {
+            const uint32_t c = ~(j < kN - bb ? first : 0u - first);
+            acc[0][j] = ~0u;
+            acc[1][j] = c;
+            if (j < kMirror) { acc[0][kN + j] = 0u - ~0u - 2u; acc[1][kN + j] = 0u - c - 2u; }
+        }
+    }
+    __syncthreads();
+
+    const uint32_t dround = 1u << (31 - 2 * a.bgbit), dhalf = 1u << (31 - a.bgbit);
+    const uint32_t field0 = (uint32_t)(32 - a.bgbit), field1 = (uint32_t)(32 - 2 * a.bgbit);
+    int bars = 0;                               // the rotation amounts of 64 steps, one per lane
+    for (int i = 0; i < a.n; ++i) {
+        if ((i & 63) == 0) bars = rotation(i + L < a.n ? i + L : a.n);
+        const int abar = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(bars, i & 63));
+        const uint32_t back4 = (uint32_t)(0 - abar) << 2;
+        double2 x[4][8];
+
+        // ---- the pieces of a step ----
+        // rotated and plain reads of a component (see blind_rotate_body for the mirror and the sign)
+        typedef __attribute__((address_space(3))) const uint32_t lds_word;
+        uint32_t rot[8][2], own[8][2];
+        auto read_component = [&](int comp) {
+            const uint32_t acc_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_word *)acc[comp]);
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t s = back4 + (uint32_t)(64 * m + h * kHalf) * 4u + 4096u;
+                    const uint32_t from = __builtin_amdgcn_readfirstlane(acc_at + (s & 4095u));
+                    rot[m][h] = *(lds_word *)(uintptr_t)(((uint32_t)L << 2) + from);
+                    own[m][h] = acc[comp][L + 64 * m + h * kHalf];
+                }
+            wave_sync();
+        };
+        // both digits of the difference, folded: x[2 comp] and x[2 comp + 1]
+        auto digits = [&](int comp) {
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+                int32_t hi[2], lo[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t s = back4 + (uint32_t)(64 * m + h * kHalf) * 4u + 4096u;
+                    const uint32_t flip = __builtin_amdgcn_readfirstlane((uint32_t)((int32_t)(s << 19) >> 31));
+                    const uint32_t bias = __builtin_amdgcn_readfirstlane(dround + 2u + flip);
+                    const uint32_t d = (rot[m][h] ^ flip) + own[m][h] + bias;
+                    lo[h] = __builtin_amdgcn_sbfe((int32_t)d, field1, (uint32_t)a.bgbit);
+                    hi[h] = (int32_t)(d + dhalf) >> field0;
+                }
+                x[2 * comp][m] = make_double2((double)hi[0], (double)hi[1]);
+                x[2 * comp + 1][m] = make_double2((double)lo[0], (double)lo[1]);
+            }
+        };
+        // lane-dependent constants are read again where they are needed: kept in registers they would
+        // leave none for the key loads in flight
+        auto load_twiddles = [&](const double2 *table, int width, int lane, double2 (&p)[8]) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) p[q] = table[q * width + lane];
+        };
+        // the uniform ones come through the scalar cache once a step (the pointer is made opaque, or the
+        // compiler keeps all of them in scalar registers and spills)
+        typedef __attribute__((address_space(4))) const double const_double;
+        auto uniform_constants = [&]() {
+            const_double *p = (const_double *)(uintptr_t)(a.tables + kUniform);
+            asm volatile("" : "+s"(p));
+            return p;
+        };
+        auto store_columns = [&](const double2 (&v)[8]) {            // element k of lane L at row k, column L
+#pragma unroll
+            for (int k = 0; k < 8; ++k) buf[k * kRowStride + L] = v[k];
+            wave_sync();
+        };
+        auto load_columns = [&](double2 (&v)[8]) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = buf[k * kRowStride + L];
+            wave_sync();
+        };
+        auto store_row = [&](const double2 (&v)[8]) {                // row L / 8: element k at L % 8 + 8 k
+#pragma unroll
+            for (int k = 0; k < 8; ++k) mine[(L & 7) + 8 * k] = v[k];
+            wave_sync();
+        };
+        auto load_row = [&](double2 (&v)[8]) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = mine[(L & 7) + 8 * k];
+            wave_sync();
+        };
+        auto store_across = [&](const double2 (&v)[8]) {             // the inner transpose, groups of 8 lanes
+#pragma unroll
+            for (int k = 0; k < 8; ++k) mine[k * kGrpStride + (L & 7)] = v[k];
+            wave_sync();
+        };
+        auto load_across = [&](double2 (&v)[8]) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = mine[k * kGrpStride + (L & 7)];
+            wave_sync();
+        };
+        auto store_along = [&](const double2 (&v)[8]) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) mine[(L & 7) * kGrpStride + k] = v[k];
+            wave_sync();
+        };
+        auto load_along = [&](double2 (&v)[8]) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = mine[(L & 7) * kGrpStride + k];
+            wave_sync();
+        };
+        const uint32_t row = (uint32_t)i * 16u * kHalf * (uint32_t)sizeof(double2);
+        double2 ring[kKeyRing][4];
+        auto load_batch = [&](int b) {                               // output b % 4 at frequency k2 = b / 4
+            const int k2 = b >> 2, o = b & 3;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                ring[b % kKeyRing][r] = load_key(key_rsrc, voff, row + (uint32_t)(((r * 4 + o) * kHalf + 256 * (k2 & 1) + 16 * (k2 >> 1)) * sizeof(double2)));
+        };
+
+        // ---- forward: four polynomials, the LDS exchanges of one beside the arithmetic of another ----
+        {
+            double2 p[8];
+            read_component(0);
+            load_twiddles(my.fwd2, 8, L >> 3, p);
+            const Twiddle8 w2 = unpack_twiddles(p);
+            Twiddle8 w1;
+            const_double *u = uniform_constants();
+            w1.t[0] = 0.0;
+#pragma unroll
+            for (int e = 1; e < 8; ++e) w1.t[e] = u[e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w1.rho[e] = u[8 + e];
+            w1.sig0 = u[12]; w1.sig1 = u[13]; w1.tau = u[14]; w1.tauh = u[15];
+
+            digits(0);
+            dft8_twiddled<false>(x[0], w1);
+            REGION_END();
+            store_columns(x[0]); load_row(x[0]);
+            dft8_twiddled<false>(x[1], w1);
+            TRANSPOSE_BESIDE(6)
+            REGION_END();
+            read_component(1);
+            dft8_twiddled<false>(x[0], w2);
+            REGION_END();
+            store_across(x[0]); load_along(x[0]); store_columns(x[1]); load_row(x[1]);
+            digits(1);
+            dft8_twiddled<false>(x[2], w1);
+            TRANSPOSE_BESIDE(7) TRANSPOSE_BESIDE(7)
+            REGION_END();
+            dft8_twiddled<false>(x[1], w2);
+            REGION_END();
+            store_across(x[1]); load_along(x[1]); store_columns(x[2]); load_row(x[2]);
+            dft8_shifted(x[0], f3);
+            dft8_twiddled<false>(x[3], w1);
+            TRANSPOSE_BESIDE(5) TRANSPOSE_BESIDE(5)
+            REGION_END();
+            __builtin_amdgcn_s_setprio(0);
+            dft8_twiddled<false>(x[2], w2);
+            REGION_END();
+            store_across(x[2]); load_along(x[2]); store_columns(x[3]); load_row(x[3]);
+            dft8_shifted(x[1], f3);
+            TRANSPOSE_BESIDE(2) TRANSPOSE_BESIDE(1)
+            REGION_END();
+            load_batch(0); load_batch(1);
+            dft8_twiddled<false>(x[3], w2);
+            REGION_END();
+            store_across(x[3]); load_along(x[3]);
+            dft8_shifted(x[2], f3);
+            TRANSPOSE_BESIDE(3)
+            REGION_END();
+            load_batch(2);
+            dft8_shifted(x[3], f3);
+            REGION_END();
+        }
+
+        // ---- products with the key row: at every frequency the four digit spectra give way to the four outputs ----
+        __builtin_amdgcn_s_barrier();                // no data passes: the four waves share their key reads
+#pragma unroll
+        for (int k2 = 0; k2 < 8; ++k2) {
+            double2 y[4];
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+                const int b = 4 * k2 + o;
+                if (b + kKeyRing - 1 < 32) load_batch(b + kKeyRing - 1);
+                REGION_END();
+                const double2 (&k)[4] = ring[b % kKeyRing];
+                const double2 d0 = x[0][k2];
+                double yr = d0.x * k[0].x, yi = d0.x * k[0].y;
+                yr = fma(-d0.y, k[0].y, yr);
+                yi = fma(d0.y, k[0].x, yi);
+#pragma unroll
+                for (int r = 1; r < 4; ++r) {
+                    const double2 d = x[r][k2];
+                    yr = fma(d.x, k[r].x, yr);
+                    yi = fma(d.x, k[r].y, yi);
+                    yr = fma(-d.y, k[r].y, yr);
+                    yi = fma(d.y, k[r].x, yi);
+                }
+                y[o] = make_double2(yr, yi);
+                REGION_END();
+            }
+#pragma unroll
+            for (int o = 0; o < 4; ++o) x[o][k2] = y[o];
+        }
+
+        // ---- back: inverse transforms, exact rounding, accumulate ----
+        __builtin_amdgcn_s_setprio(2);
+        {
+            double2 p[8];
+            load_twiddles(my.inv2, 8, L & 7, p);
+            const Twiddle8 w2 = unpack_twiddles(p);
+            load_twiddles(my.inv1, 64, L, p);
+            const Twiddle8 w1 = unpack_twiddles(p);
+            const double2 w10 = p[7];
+            double tan_m[8], cos_m[8];
+            const_double *u = uniform_constants();
+#pragma unroll
+            for (int m = 1; m < 8; ++m) { tan_m[m] = u[m]; cos_m[m] = u[16 + m]; }
+            uint32_t low[8][2];
+            // pass 1, rounding, and with the second limb the accumulation of a component
+            auto finish = [&](int o) {
+                double2 (&v)[8] = x[o];
+                v[0] = cmul(v[0], w10);
+                dft8_twiddled<true>(v, w1);
+#pragma unroll
+                for (int m = 0; m < 8; ++m) {
+                    if (m) v[m] = cturn(v[m], -tan_m[m]);
+                    const double part[2] = {v[m].x, v[m].y};
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        // 1.5 * 2^52 - value leaves round-to-nearest(-value) mod 2^32 in the low word; the value's
+                        // pending cosine rides in the multiply-add, so it is rounded once
+                        const double shifted = m ? fma(-cos_m[m], part[h], 6755399441055744.0) : 6755399441055744.0 - part[h];
+                        const uint32_t r = (uint32_t)__double2loint(shifted);
+                        if (MARGIN) worst = fmax(worst, fabs((m ? cos_m[m] * part[h] : part[h]) + (shifted - 6755399441055744.0)));
+                        if (!(o & 1)) {
+                            low[m][h] = r;
+                        } else {
+                            const uint32_t t = low[m][h] + (r << 16);
+                            atomicAdd(&acc[o >> 1][L + 64 * m + h * kHalf], t);
+                            if (m == 0 && h == 0) atomicSub(&acc[o >> 1][kN + L], t);      // the mirror holds -c - 2
+                        }
+                    }
+                }
+            };
+            radix8<true>(x[0]);
+            REGION_END();
+            store_along(x[0]); load_across(x[0]);
+            radix8<true>(x[1]);
+            TRANSPOSE_BESIDE(4)
+            REGION_END();
+            dft8_twiddled<true>(x[0], w2);
+            REGION_END();
+            store_row(x[0]); load_columns(x[0]); store_along(x[1]); load_across(x[1]);
+            radix8<true>(x[2]);
+            TRANSPOSE_BESIDE(2) TRANSPOSE_BESIDE(2)
+            REGION_END();
+            dft8_twiddled<true>(x[1], w2);
+            REGION_END();
+            store_row(x[1]); load_columns(x[1]);
+            finish(0);
+            TRANSPOSE_BESIDE(6)
+            REGION_END();
+            store_along(x[2]); load_across(x[2]);
+            radix8<true>(x[3]);
+            TRANSPOSE_BESIDE(4)
+            REGION_END();
+            dft8_twiddled<true>(x[2], w2);
+            REGION_END();
+            store_row(x[2]); load_columns(x[2]); store_along(x[3]); load_across(x[3]);
+            finish(1);
+            TRANSPOSE_BESIDE(3) TRANSPOSE_BESIDE(3)
+            REGION_END();
+            dft8_twiddled<true>(x[3], w2);
+            REGION_END();
+            store_row(x[3]); load_columns(x[3]);
+            finish(2);
+            TRANSPOSE_BESIDE(6)
+            REGION_END();
+            finish(3);
+            wave_sync();
+        }
+    }
+
+    if (slot < a.count) {
+        uint32_t *ext = a.ext + gi * (size_t)(kN + 1);
+        for (int j = L; j < kN; j += 64) ext[j] = j == 0 ? ~acc[0][0] : acc[0][kN - j] + 1u;
+        if (L == 0) ext[kN] = ~acc[1][0];
+    }
+    if (MARGIN)
+        atomicMax(reinterpret_cast<unsigned long long *>(a.margin), (unsigned long long)__double_as_longlong(worst));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -727,6 +1116,16 @@ static int resident_groups() {
     return groups;
 }
 
+// TFHE_WAVE_GATES_FROM overrides the rule of launch_blind_rotate: batches from this size on run whole on the
+// one-gate-per-wave kernel, smaller ones on the four-wave kernels.
+static long wave_gates_from() {
+    static const long from = [] {
+        const char *e = getenv("TFHE_WAVE_GATES_FROM");
+        return e ? atol(e) : -1L;
+    }();
+    return from;
+}
+
 // Kernels that use more than 64 KB of dynamic LDS have to be told so once per device;
 // `done` is that kernel's own bit mask of devices.
 static int allow_dynamic_lds(const void *kernel, size_t bytes, std::atomic<uint64_t> &done) {
@@ -779,17 +1178,19 @@ int launch_bk_to_spectrum(const uint32_t *bk_raw, double2 *bk_fft, const double2
     return TFHE_OK;
 }
 
-// the four blind-rotation kernels and the two matrix-core key-switch kernels, with their
+// the six blind-rotation kernels and the two matrix-core key-switch kernels, with their
 // dynamic LDS sizes and per-device "attribute set" masks
 namespace {
 struct BigLdsKernel { const void *fn; size_t lds; std::atomic<uint64_t> done; };
-BigLdsKernel big_lds_kernels[6] = {
+BigLdsKernel big_lds_kernels[8] = {
     {reinterpret_cast<const void *>(&blind_rotate_kernel<false>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_kernel<true>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<false>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<true>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&key_switch_mfma_kernel<false>), sizeof(KsMatrixLds), {0}},
     {reinterpret_cast<const void *>(&key_switch_mfma_kernel<true>), sizeof(KsMatrixLds), {0}},
+    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false>), sizeof(WaveLds), {0}},
+    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<true>), sizeof(WaveLds), {0}},
 };
 int allow(int which) { return allow_dynamic_lds(big_lds_kernels[which].fn, big_lds_kernels[which].lds, big_lds_kernels[which].done); }
 }  // namespace
@@ -800,29 +1201,59 @@ int allow(int which) { return allow_dynamic_lds(big_lds_kernels[which].fn, big_l
 int prepare_kernels() {
     (void)latency_batch_limit();
     (void)resident_groups();
-    for (int k = 0; k < 6; ++k)
+    (void)wave_gates_from();
+    for (int k = 0; k < 8; ++k)
         if (int rc = allow(k)) return rc;
     return static_scratch_init();
 }
 
-int launch_blind_rotate(const BlindRotateArgs &a, hipStream_t stream) {
-    if (a.count == 0) return TFHE_OK;
-    const size_t lds = sizeof(GateLds);
-    const bool latency = a.count <= (size_t)latency_batch_limit();
+// Items first .. count - 1 of a batch with the four-wave kernels.
+static int launch_four_waves(const BlindRotateArgs &a, hipStream_t stream) {
+    const size_t lds = sizeof(GateLds), items = a.count - a.first;
+    const bool latency = items <= (size_t)latency_batch_limit();
     if (int rc = allow((latency ? 2 : 0) + (a.margin ? 1 : 0))) return rc;
     if (latency) {
         // at most one gate per CU: the variant that requests each key row a step ahead
-        const dim3 grid((unsigned)a.count);
+        const dim3 grid((unsigned)items);
         if (a.margin) hipLaunchKernelGGL(blind_rotate_latency_kernel<true>, grid, dim3(kThreadsPerGate), lds, stream, a);
         else hipLaunchKernelGGL(blind_rotate_latency_kernel<false>, grid, dim3(kThreadsPerGate), lds, stream, a);
     } else {
         const size_t bound = (size_t)resident_groups();
-        const dim3 grid((unsigned)(bound ? std::min(a.count, bound) : a.count));
+        const dim3 grid((unsigned)(bound ? std::min(items, bound) : items));
         if (a.margin) hipLaunchKernelGGL(blind_rotate_kernel<true>, grid, dim3(kThreadsPerGate), lds, stream, a);
         else hipLaunchKernelGGL(blind_rotate_kernel<false>, grid, dim3(kThreadsPerGate), lds, stream, a);
     }
     TFHE_HIP(hipGetLastError());
     return TFHE_OK;
+}
+
+// The wave kernel holds eight gates per CU at a time and one round takes 5.2 ms with up to four of them
+// and 7.5 ms with all eight; the four-wave kernels take 1.6, 2.4 and 3.2 ms for one, two and three gates
+// per CU, 5.5 ms for four (a second round begins) and 6.0 to 6.3 ms for five.  So whole rounds go to the wave
+// kernel, and what remains follows on the four-wave kernels where those are the faster ones.
+constexpr size_t kRoundPerCu = 2 * kWaveGates;
+static bool four_waves_faster(size_t per_cu) { return per_cu <= 3 || per_cu == 5; }
+
+int launch_blind_rotate(const BlindRotateArgs &args, hipStream_t stream) {
+    if (args.count == 0) return TFHE_OK;
+    BlindRotateArgs a = args;
+    a.first = 0;
+    const size_t cus = device_cus() > 0 ? (size_t)device_cus() : 256;
+    size_t whole = a.count - a.count % (kRoundPerCu * cus);
+    if (!four_waves_faster((a.count - whole + cus - 1) / cus)) whole = a.count;
+    if (wave_gates_from() >= 0) whole = a.count >= (size_t)wave_gates_from() ? a.count : 0;
+    if (whole) {
+        a.count = whole;
+        if (int rc = allow(6 + (a.margin ? 1 : 0))) return rc;
+        const dim3 grid((unsigned)((whole + kWaveGates - 1) / kWaveGates));
+        if (a.margin) hipLaunchKernelGGL(blind_rotate_wave_kernel<true>, grid, dim3(64 * kWaveGates), sizeof(WaveLds), stream, a);
+        else hipLaunchKernelGGL(blind_rotate_wave_kernel<false>, grid, dim3(64 * kWaveGates), sizeof(WaveLds), stream, a);
+        TFHE_HIP(hipGetLastError());
+    }
+    if (whole == args.count) return TFHE_OK;
+    a.first = whole;
+    a.count = args.count;
+    return launch_four_waves(a, stream);
 }
 
 int launch_ksk_to_tiles(const uint32_t *ksk, int stride, int words, void *tiles, hipStream_t stream) {

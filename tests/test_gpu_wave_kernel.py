@@ -1,0 +1,113 @@
+"""GPU parity of the blind rotation that keeps one gate per wavefront (large batches), against the four-wave
+kernels -- which the parity tests compare with the oracle -- and against the oracle itself.
+
+All arithmetic is exact modulo 2^32, so the bar is equal bytes.  The sizes are where the kernel and the
+rule that selects it can go wrong: fewer gates than waves of a workgroup, a ragged last workgroup, a round
+of eight gates per CU, one item to either side of it (the remainder goes to another kernel), and
+multiplexer pairs split between the two launches.
+"""
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+_SCRIPT = r"""
+import hashlib, sys
+import numpy as np, torch
+sys.path.insert(0, sys.argv[1])
+import paper_1806_03461_amd as T, workloads
+sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
+rng = np.random.default_rng(61)
+h = hashlib.sha256()
+# arbitrary words reach every rotation amount, encryptions do not hit rounding ties
+for count in (1, 3, 4, 5, 66):
+    a, b = (torch.from_numpy(rng.integers(0, 1 << 32, (count, 501), dtype=np.uint64).astype(np.uint32).view(np.int32)).cuda() for _ in range(2))
+    a[0] = torch.from_numpy(((np.arange(501) * 64 + 1) % 2048 << 21).astype(np.uint32).view(np.int32))
+    for op in ("NAND", "XOR"):
+        out = torch.empty_like(a)
+        T.tfhe_gate_batch(ck, op, a, b, out, count)
+        torch.cuda.synchronize()
+        h.update(T.to_host(out).tobytes())
+s, a, b = (T.to_device(T.tfhe_encrypt(sk, 300 + k, rng.integers(0, 2, 7).astype(np.uint8))) for k in range(3))
+out = torch.empty_like(a)
+T.tfhe_mux_batch(ck, s, a, b, out, 7)
+W = rng.choice(np.array([-1, 0, 1], np.int8), (9, 13), p=[0.45, 0.1, 0.45])
+res = torch.empty((9, 501), dtype=torch.int32, device="cuda")
+x = T.to_device(T.tfhe_encrypt(sk, 310, rng.integers(0, 2, 13).astype(np.uint8)))
+T.bnn_dense_encrypted_opts(ck, x, 13, W, np.arange(2, 11).astype(np.int32), 9, res, 0, T.LOWER_MUX_COMPARATOR)
+torch.cuda.synchronize()
+h.update(T.to_host(out).tobytes() + T.to_host(res).tobytes())
+P = T.Params(300, 1024, 1, 2, 8, 5, 3, -15, -25)          # another gadget base and step count
+sk2, ck2 = T.tfhe_keygen(P, 777)
+a, b = (T.to_device(T.tfhe_encrypt(sk2, 320 + k, rng.integers(0, 2, 6).astype(np.uint8))) for k in range(2))
+out = torch.empty_like(a)
+T.tfhe_gate_batch(ck2, "AND", a, b, out, 6)
+torch.cuda.synchronize()
+h.update(T.to_host(out).tobytes())
+print("digest", h.hexdigest())
+"""
+
+
+def test_small_batches_equal_the_four_wave_kernels():
+    """Every batch on the wave kernel, and none: the same bytes."""
+    digests = []
+    for gates_from in ("1", "1000000000"):
+        env = dict(os.environ, TFHE_WAVE_GATES_FROM=gates_from)
+        r = subprocess.run([sys.executable, "-c", _SCRIPT, ROOT], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                           text=True, timeout=200)
+        assert r.returncode == 0, r.stdout
+        digests.append([l for l in r.stdout.splitlines() if l.startswith("digest")][-1])
+    assert digests[0] == digests[1]
+
+
+@pytest.mark.parametrize("count", [769, 1281, 2047, 2048, 2049])
+def test_batches_around_a_round(real_keys, count):
+    """Default dispatch on a CU's worth of rounds: the first and last gates and a few between equal the oracle's,
+    and all of them equal the same gates evaluated in small batches."""
+    import torch
+    import paper_1806_03461_amd as T
+    sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
+    rng = np.random.default_rng(count)
+    a, b = rng.integers(0, 2, count).astype(np.uint8), rng.integers(0, 2, count).astype(np.uint8)
+    cta, ctb = T.tfhe_encrypt(sk, 401, a), T.tfhe_encrypt(sk, 402, b)
+    da, db = T.to_device(cta), T.to_device(ctb)
+    out, small = torch.empty_like(da), torch.empty_like(da)
+    T.tfhe_gate_batch(ck, "NOR", da, db, out, count)
+    for at in range(0, count, 250):
+        n = min(250, count - at)
+        T.tfhe_gate_batch(ck, "NOR", da[at:], db[at:], small[at:], n)
+    torch.cuda.synchronize()
+    assert torch.equal(out, small)
+    host = T.to_host(out)
+    for i in (0, 3, count // 2, count - 2, count - 1):
+        assert np.array_equal(host[i], real_keys.gate("NOR", cta[i], ctb[i])), i
+
+
+def test_rounding_margin_and_multiplexers_of_a_large_batch(real_keys):
+    """1,041 multiplexers = 2,082 items: a round on the wave kernel and a remainder elsewhere.  They decrypt to
+    s ? a : b, sampled ones equal the oracle's, and the transform outputs stay far from a rounding tie."""
+    import torch
+    import paper_1806_03461_amd as T
+    sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
+    rng = np.random.default_rng(8)
+    m = 1041
+    s, a, b = (rng.integers(0, 2, m).astype(np.uint8) for _ in range(3))
+    cts, cta, ctb = T.tfhe_encrypt(sk, 411, s), T.tfhe_encrypt(sk, 412, a), T.tfhe_encrypt(sk, 413, b)
+    out = torch.empty((m, 501), dtype=torch.int32, device="cuda")
+    T.tfhe_rounding_margin_enable(ck, True)
+    T.tfhe_mux_batch(ck, T.to_device(cts), T.to_device(cta), T.to_device(ctb), out, m)
+    worst = T.tfhe_rounding_margin_read(ck)
+    T.tfhe_rounding_margin_enable(ck, False)
+    assert 0 < worst < 1e-3, worst          # the bound the parity tests hold the four-wave kernels to
+    host = T.to_host(out)
+    assert np.array_equal(T.tfhe_decrypt(sk, host), np.where(s == 1, a, b))
+    for i in (0, 1, 1022, 1023, 1024, 1025, m - 1):
+        assert np.array_equal(host[i], real_keys.mux(cts[i], cta[i], ctb[i])), i
