@@ -93,6 +93,7 @@ struct tfhe_cloud_key {
     // device side
     bool uploaded = false;
     int device = -1;
+    size_t cus = 256;               // compute units of that device
     uint32_t *d_ksk = nullptr;
     void *d_ksk_tiles = nullptr;    // the same key as int8 operand tiles (t = 8, basebit = 2, n < 512 only)
     double2 *d_bk_fft = nullptr;    // [n][2l][4][N/2]: output o = 2*component + limb

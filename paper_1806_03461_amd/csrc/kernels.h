@@ -33,6 +33,24 @@ struct KeySwitchArgs {
     int matrix;                  // use the matrix-core kernel (needs ksk_tiles, t = 8, basebit = 2, n + 1 <= 512)
 };
 
+// How long a blind rotation of `items` gates takes on a device with `cus` compute units, in milliseconds, as
+// measured on 256 of them (n = 500; other step counts scale all of it alike): what the launcher's choice of
+// kernels and the scheduler of narrow circuits go by.
+//   wave kernel       eight gates per CU at a time: 7.5 ms a round, 5.2 ms with at most four per CU in it,
+//                     6.3 ms with five
+//   four-wave kernel  1.6, 2.4 and 3.2 ms for one, two and three gates per CU; more begin a second round
+inline double rest_ms(size_t per_cu) {      // a launch of less than a round
+    const double ms[9] = {0.0, 1.6, 2.4, 3.2, 5.2, 6.1, 6.6, 7.1, 7.5};
+    return ms[per_cu];
+}
+// of a batch's last, partial round: whether the four-wave kernels serve it faster than the wave kernel
+inline bool four_waves_faster(size_t per_cu) { return per_cu <= 3 || per_cu == 5; }
+constexpr size_t kRoundPerCu = 8;
+inline double rotation_ms(size_t items, size_t cus) {
+    const size_t round = kRoundPerCu * cus, rest = items % round;
+    return 7.5 * (double)(items / round) + rest_ms((rest + cus - 1) / cus);
+}
+
 size_t blind_rotate_lds_bytes();
 int launch_bk_to_spectrum(const uint32_t *bk_raw, double2 *bk_fft, const double2 *tables, int n,
                           hipStream_t stream);

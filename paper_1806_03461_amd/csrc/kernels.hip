@@ -1227,12 +1227,9 @@ static int launch_four_waves(const BlindRotateArgs &a, hipStream_t stream) {
     return TFHE_OK;
 }
 
-// The wave kernel holds eight gates per CU at a time and one round takes 5.2 ms with up to four of them
-// and 7.5 ms with all eight; the four-wave kernels take 1.6, 2.4 and 3.2 ms for one, two and three gates
-// per CU, 5.5 ms for four (a second round begins) and 6.0 to 6.3 ms for five.  So whole rounds go to the wave
-// kernel, and what remains follows on the four-wave kernels where those are the faster ones.
-constexpr size_t kRoundPerCu = 2 * kWaveGates;
-static bool four_waves_faster(size_t per_cu) { return per_cu <= 3 || per_cu == 5; }
+// Whole rounds go to the wave kernel, and what remains follows on the four-wave kernels where those are the
+// faster ones (times in kernels.h).
+static_assert(kRoundPerCu == 2 * kWaveGates, "two workgroups of the wave kernel per CU");
 
 int launch_blind_rotate(const BlindRotateArgs &args, hipStream_t stream) {
     if (args.count == 0) return TFHE_OK;
