@@ -1,5 +1,4 @@
-// Eight-point transforms with their input twiddles written as cos (1 + i tan), for the blind rotation that
-// keeps one gate in one wavefront.
+// Eight-point transforms with their input twiddles written as cos (1 + i tan), for the blind rotations.
 //
 // A 512-point transform at the odd roots, X_k = sum_n z_n psi^(n (1 + 4k)) with psi = exp(i pi / 1024),
 // n = j0 + 8 j1 + 64 m and k = k0 + 8 k1 + 64 k2, splits into three eight-point passes whose twiddles
@@ -12,13 +11,13 @@
 //   pass 2 over k1   psi^(-32 j0 k1)                                          -> j1
 //   pass 1 over k0   psi^(-L (1 + 4 k0)), L = j0 + 8 j1                       -> m
 //   and psi^(-64 m) on the outputs, whose cosine the caller folds into its rounding.
-// The spectra are the ones the four-wave kernels produce (same frequencies, same scale), so both share
-// one transformed key.
+// The spectra are those of fft512.h (same frequencies, same scale), whose steps transform the key.
 //
 // A twiddle c (1 + i t) costs two fused multiply-adds for the turn by (1 + i t); its cosine is not applied
 // to the number but left pending and absorbed, as a ratio of cosines, by the multiply-adds that take
 // the place of the transform's additions.  Fourteen instructions twiddle seven inputs instead of
-// twenty-eight, and the eight-point transform itself keeps its 52.  Pending factors do not
+// twenty-eight, and the eight-point transform itself keeps its 52: 202 to 210 instructions a lane for a whole
+// transform instead of 244.  Pending factors do not
 // cost accuracy however small a cosine is: x (1 + i t) with |t| up to 2^65 and a factor c with c t = 1 is
 // as accurate relative to its size as x times the rounded twiddle.
 #pragma once
@@ -40,9 +39,14 @@ FFT_HD double2 cturn(double2 a, double t) { return make_double2(fma(-t, a.y, a.x
 FFT_HD double2 cmadd(double2 a, double s, double2 b) { return make_double2(fma(s, b.x, a.x), fma(s, b.y, a.y)); }      // a + s b
 FFT_HD double2 cmaddi(double2 a, double s, double2 b) { return make_double2(fma(-s, b.y, a.x), fma(s, b.x, a.y)); }    // a + i s b
 
-// y[k] = sum_j exp(i phi_j) x[j] w^(j k), w = exp(2 pi i / 8) (INV: exp(-2 pi i / 8)), in place
-template <bool INV>
-FFT_HD void dft8_twiddled(double2 (&x)[8], const Twiddle8 &w) {
+// The transforms hand out their results one by one, emit(k, y[k]): the four even ones, then -- after
+// between() -- the four odd ones, whose half of the additions is still to come.  A caller that stores them to
+// LDS so has half of its stores under way while it computes.  The array versions leave them in x.
+// w = exp(2 pi i / 8) (INV: exp(-2 pi i / 8)).
+
+// y[k] = sum_j exp(i phi_j) x[j] w^(j k)
+template <bool INV, class Emit, class Between>
+FFT_HD void dft8_twiddled(double2 (&x)[8], const Twiddle8 &w, Emit &&emit, Between &&between) {
     for (int j = 1; j < 8; ++j) x[j] = cturn(x[j], w.t[j]);
     double2 a[8];
     for (int j = 0; j < 4; ++j) {
@@ -52,24 +56,24 @@ FFT_HD void dft8_twiddled(double2 (&x)[8], const Twiddle8 &w) {
     {
         const double2 c0 = cmadd(a[0], w.sig0, a[2]), c1 = cmadd(a[0], -w.sig0, a[2]);
         const double2 c2 = cmadd(a[1], w.sig1, a[3]), d = cmadd(a[1], -w.sig1, a[3]);
-        x[0] = cmadd(c0, w.tau, c2);
-        x[4] = cmadd(c0, -w.tau, c2);
         const double ti = INV ? -w.tau : w.tau;
-        x[2] = cmaddi(c1, ti, d);
-        x[6] = cmaddi(c1, -ti, d);
+        emit(0, cmadd(c0, w.tau, c2));
+        emit(4, cmadd(c0, -w.tau, c2));
+        emit(2, cmaddi(c1, ti, d));
+        emit(6, cmaddi(c1, -ti, d));
     }
+    between();
     {
         // sqrt 2 times a5 w and a7 w^3; the 1 / sqrt 2 is in tauh
         const double2 s5 = INV ? make_double2(a[5].x + a[5].y, a[5].y - a[5].x) : make_double2(a[5].x - a[5].y, a[5].x + a[5].y);
         const double2 s7 = INV ? make_double2(a[7].y - a[7].x, -a[7].x - a[7].y) : make_double2(-a[7].x - a[7].y, a[7].x - a[7].y);
-        const double s6 = INV ? -w.sig0 : w.sig0;
+        const double s6 = INV ? -w.sig0 : w.sig0, hi = INV ? -w.tauh : w.tauh;
         const double2 c0 = cmaddi(a[4], s6, a[6]), c1 = cmaddi(a[4], -s6, a[6]);
         const double2 t = cmadd(s5, w.sig1, s7), u = cmadd(s5, -w.sig1, s7);
-        x[1] = cmadd(c0, w.tauh, t);
-        x[5] = cmadd(c0, -w.tauh, t);
-        const double hi = INV ? -w.tauh : w.tauh;
-        x[3] = cmaddi(c1, hi, u);
-        x[7] = cmaddi(c1, -hi, u);
+        emit(1, cmadd(c0, w.tauh, t));
+        emit(5, cmadd(c0, -w.tauh, t));
+        emit(3, cmaddi(c1, hi, u));
+        emit(7, cmaddi(c1, -hi, u));
     }
 }
 
@@ -79,24 +83,90 @@ FFT_HD void dft8_twiddled(double2 (&x)[8], const Twiddle8 &w) {
 struct Shift8 {
     double2 h4, h2, h1, h1w;
 };
-template <bool I>
-FFT_HD void bfly(double2 &a, double2 &b, double2 w) {      // a, b <- a +- w b (I: a +- i w b)
-    const double2 r = cturn(b, w.y), p = a;
-    a = I ? cmaddi(p, w.x, r) : cmadd(p, w.x, r);
-    b = I ? cmaddi(p, -w.x, r) : cmadd(p, -w.x, r);
+// a +- w b and a +- i w b; b already turned by (1 + i tan)
+FFT_HD void bfly(double2 &a, double2 &b, double c) { const double2 p = a, r = b; a = cmadd(p, c, r); b = cmadd(p, -c, r); }
+FFT_HD void bfly_i(double2 &a, double2 &b, double c) { const double2 p = a, r = b; a = cmaddi(p, c, r); b = cmaddi(p, -c, r); }
+
+template <bool INV, class Emit, class Between>
+FFT_HD void dft8_shifted(double2 (&x)[8], const Shift8 &w, Emit &&emit, Between &&between) {
+    const double i2 = INV ? -w.h2.x : w.h2.x, i1 = INV ? -w.h1.x : w.h1.x, i1w = INV ? -w.h1w.x : w.h1w.x;
+    for (int j = 0; j < 4; ++j) {
+        x[j + 4] = cturn(x[j + 4], w.h4.y);
+        bfly(x[j], x[j + 4], w.h4.x);
+    }
+    x[2] = cturn(x[2], w.h2.y);
+    x[3] = cturn(x[3], w.h2.y);
+    bfly(x[0], x[2], w.h2.x);
+    bfly(x[1], x[3], w.h2.x);
+    x[1] = cturn(x[1], w.h1.y);
+    x[3] = cturn(x[3], w.h1.y);
+    bfly(x[0], x[1], w.h1.x);
+    bfly_i(x[2], x[3], i1);
+    emit(0, x[0]);
+    emit(4, x[1]);
+    emit(2, x[2]);
+    emit(6, x[3]);
+    between();
+    x[6] = cturn(x[6], w.h2.y);
+    x[7] = cturn(x[7], w.h2.y);
+    bfly_i(x[4], x[6], i2);
+    bfly_i(x[5], x[7], i2);
+    x[5] = cturn(x[5], w.h1w.y);
+    x[7] = cturn(x[7], w.h1w.y);
+    bfly(x[4], x[5], w.h1w.x);
+    bfly_i(x[6], x[7], i1w);
+    emit(1, x[4]);
+    emit(5, x[5]);
+    emit(3, x[6]);
+    emit(7, x[7]);
 }
+
+// no twiddle: radix8 of fft512.h
+template <bool INV, class Emit, class Between>
+FFT_HD void dft8_plain(double2 (&x)[8], Emit &&emit, Between &&between) {
+    const double c = 0.70710678118654752440;
+    for (int j = 0; j < 4; ++j) {
+        const double2 p = x[j], q = x[j + 4];
+        x[j] = cadd(p, q);
+        x[j + 4] = csub(p, q);
+    }
+    {
+        const double2 c0 = cadd(x[0], x[2]), c1 = csub(x[0], x[2]), c2 = cadd(x[1], x[3]), d = csub(x[1], x[3]);
+        const double2 c3 = INV ? make_double2(d.y, -d.x) : make_double2(-d.y, d.x);
+        emit(0, cadd(c0, c2));
+        emit(4, csub(c0, c2));
+        emit(2, cadd(c1, c3));
+        emit(6, csub(c1, c3));
+    }
+    between();
+    {
+        const double2 a4 = x[4], a5 = x[5], a6 = x[6], a7 = x[7];
+        const double2 s5 = INV ? make_double2(a5.x + a5.y, a5.y - a5.x) : make_double2(a5.x - a5.y, a5.x + a5.y);
+        const double2 s7 = INV ? make_double2(a7.y - a7.x, -a7.x - a7.y) : make_double2(-a7.x - a7.y, a7.x - a7.y);
+        const double2 b6 = INV ? make_double2(a6.y, -a6.x) : make_double2(-a6.y, a6.x);
+        const double2 c0 = cadd(a4, b6), c1 = csub(a4, b6), t = cadd(s5, s7), u = csub(s5, s7);
+        const double ci = INV ? -c : c;
+        emit(1, cmadd(c0, c, t));
+        emit(5, cmadd(c0, -c, t));
+        emit(3, cmaddi(c1, ci, u));
+        emit(7, cmaddi(c1, -ci, u));
+    }
+}
+
+struct Nothing {
+    FFT_HD void operator()() const {}
+};
+template <bool INV>
+FFT_HD void dft8_twiddled(double2 (&x)[8], const Twiddle8 &w) {
+    double2 y[8];
+    dft8_twiddled<INV>(x, w, [&](int k, double2 v) { y[k] = v; }, Nothing());
+    for (int k = 0; k < 8; ++k) x[k] = y[k];
+}
+template <bool INV>
 FFT_HD void dft8_shifted(double2 (&x)[8], const Shift8 &w) {
-    for (int j = 0; j < 4; ++j) bfly<false>(x[j], x[j + 4], w.h4);
-    bfly<false>(x[0], x[2], w.h2);
-    bfly<false>(x[1], x[3], w.h2);
-    bfly<true>(x[4], x[6], w.h2);
-    bfly<true>(x[5], x[7], w.h2);
-    bfly<false>(x[0], x[1], w.h1);
-    bfly<true>(x[2], x[3], w.h1);
-    bfly<false>(x[4], x[5], w.h1w);
-    bfly<true>(x[6], x[7], w.h1w);
-    const double2 y4 = x[1], y2 = x[2], y6 = x[3], y1 = x[4], y3 = x[6], y7 = x[7];
-    x[1] = y1; x[2] = y2; x[3] = y3; x[4] = y4; x[6] = y6; x[7] = y7;
+    double2 y[8];
+    dft8_shifted<INV>(x, w, [&](int k, double2 v) { y[k] = v; }, Nothing());
+    for (int k = 0; k < 8; ++k) x[k] = y[k];
 }
 
 // ---- the constants in memory, behind the 2,048 powers of psi (offsets in complex words) ----
@@ -106,7 +176,9 @@ constexpr int kFwd2 = kPsiWords;          // [word 8][k0 8]      forward pass 2
 constexpr int kInv2 = kFwd2 + 64;         // [word 8][j0 8]      inverse pass 2
 constexpr int kInv1 = kInv2 + 64;         // [word 8][L 64]      inverse pass 1
 constexpr int kFwd3 = kInv1 + 512;        // [word 4][lane 64]   forward pass 3, lane = 8 k0 + k1: h4, h2, h1, h1w
-constexpr int kUniform = kFwd3 + 256;     // 24 doubles of passes 1: tan, rho, sig0, sig1, tau, tauh; then cos
+constexpr int kFwd2Shift = kFwd3 + 256;   // [word 4][k0 8]      the same form of forward pass 2
+constexpr int kInv2Shift = kFwd2Shift + 32;   // [word 4][j0 8]  and of inverse pass 2
+constexpr int kUniform = kInv2Shift + 32; // 24 doubles of passes 1: tan, rho, sig0, sig1, tau, tauh; then cos
 constexpr int kTableWords = kUniform + 12;
 
 FFT_HD Twiddle8 unpack_twiddles(const double2 (&p)[8]) {
@@ -133,7 +205,17 @@ inline void fill_tables(double2 *tables) {
                                    c[7] / c[3], c[2] / c[0], c[3] / c[1], c[1] / c[0], c0, s0};
         for (int q = 0; q < 8; ++q) tables[base + q * width + lane] = make_double2((double)v[2 * q], (double)v[2 * q + 1]);
     };
+    // theta = psi^e, w = psi^w8
+    auto shift = [&](int base, int width, int lane, int e, int w8) {
+        const int h[4] = {4 * e, 2 * e, e, e + w8};
+        for (int q = 0; q < 4; ++q) {
+            const long double c = cosl(angle(h[q]));
+            tables[base + q * width + lane] = make_double2((double)c, (double)(sinl(angle(h[q])) / c));
+        }
+    };
     for (int a = 0; a < 8; ++a) {
+        shift(kFwd2Shift, 8, a, 8 * (1 + 4 * a), 256);
+        shift(kInv2Shift, 8, a, -32 * a, -256);
         int f[8], g[8];
         for (int j = 0; j < 8; ++j) { f[j] = 8 * j * (1 + 4 * a); g[j] = -32 * a * j; }
         pack(kFwd2, 8, a, f, false);
@@ -143,9 +225,7 @@ inline void fill_tables(double2 *tables) {
         int f[8];
         for (int k = 0; k < 8; ++k) f[k] = -L * (1 + 4 * k);
         pack(kInv1, 64, L, f, true);
-        const int e = 1 + 4 * (L >> 3) + 32 * (L & 7), h[4] = {4 * e, 2 * e, e, e + 256};
-        for (int q = 0; q < 4; ++q)
-            tables[kFwd3 + q * 64 + L] = make_double2((double)cosl(angle(h[q])), (double)(sinl(angle(h[q])) / cosl(angle(h[q]))));
+        shift(kFwd3, 64, L, 1 + 4 * (L >> 3) + 32 * (L & 7), 256);
     }
     long double c[8], v[24] = {};
     for (int m = 0; m < 8; ++m) { c[m] = cosl(pi * m / 16); v[m] = sinl(pi * m / 16) / c[m]; v[16 + m] = c[m]; }

@@ -109,9 +109,13 @@ struct GateLds {
     // coefficients that runs past X^N continues into the mirror, and the value found there already
     // carries the sign change of X^N = -1 (see the rotation in blind_rotate_body)
     uint32_t acc[2][kN + kMirror];
-    double2 buf[kBufWords];       // the four polynomials' transform buffers
+    // the four polynomials' transform buffers, without the gap behind the last: the LDS of a workgroup is
+    // given out in units of 1,280 bytes, and with it three of them would not fit a CU
+    double2 buf[kBufWords - 16];
+    double2 inv1[5 * 64];         // words 0..4 of the constants of inverse pass 1 (dft8.h)
     uint16_t bar[1032];           // abar_0 .. abar_{n-1}, bbar
 };
+static_assert(3 * ((sizeof(GateLds) + 1279) / 1280 * 1280) <= 160 * 1024, "three workgroups share a CU's LDS");
 
 __device__ __forceinline__ void gate_constants(int op, uint32_t &kappa, uint32_t &mult) {
     switch (op) {
@@ -132,6 +136,25 @@ __device__ __forceinline__ double2 load_key(__amdgpu_buffer_rsrc_t rsrc, uint32_
     out.x = __hiloint2double((int)v.y, (int)v.x);
     out.y = __hiloint2double((int)v.w, (int)v.z);
     return out;
+}
+
+// The constants that are the same in every lane come through the scalar cache once a step (the pointer is
+// made opaque, or the compiler keeps all of them in scalar registers over the loop and spills).
+typedef __attribute__((address_space(4))) const double const_double;
+__device__ __forceinline__ const_double *uniform_constants(const double2 *tables) {
+    const_double *p = (const_double *)(uintptr_t)(tables + kUniform);
+    asm volatile("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ Twiddle8 pass1_twiddles(const_double *u) {
+    Twiddle8 w;
+    w.t[0] = 0.0;
+#pragma unroll
+    for (int j = 1; j < 8; ++j) w.t[j] = u[j];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w.rho[j] = u[8 + j];
+    w.sig0 = u[12]; w.sig1 = u[13]; w.tau = u[14]; w.tauh = u[15];
+    return w;
 }
 
 // A step's key values of one thread come in four parts of 8 (32 registers): part p = 2 q + h holds
@@ -156,8 +179,20 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave, in a scalar register
     const int L = tid & 63;
 
-    Lane ln;
-    lane_init(ln, a.tables, L);
+    // Constants of the passes (dft8.h).  Those of inverse pass 1 are the largest set: five of its eight words
+    // wait in LDS, read while the barrier before the pass is waited for.
+    const int k0 = 2 * wv + (L >> 3 & 1);
+    Shift8 f2, f3, i2;
+    f2.h4 = a.tables[kFwd2Shift + k0]; f2.h2 = a.tables[kFwd2Shift + 8 + k0];
+    f2.h1 = a.tables[kFwd2Shift + 16 + k0]; f2.h1w = a.tables[kFwd2Shift + 24 + k0];
+    f3.h4 = a.tables[kFwd3 + 8 * k0 + (L & 7)]; f3.h2 = a.tables[kFwd3 + 64 + 8 * k0 + (L & 7)];
+    f3.h1 = a.tables[kFwd3 + 128 + 8 * k0 + (L & 7)]; f3.h1w = a.tables[kFwd3 + 192 + 8 * k0 + (L & 7)];
+    i2.h4 = a.tables[kInv2Shift + (L & 7)]; i2.h2 = a.tables[kInv2Shift + 8 + (L & 7)];
+    i2.h1 = a.tables[kInv2Shift + 16 + (L & 7)]; i2.h1w = a.tables[kInv2Shift + 24 + (L & 7)];
+    double2 i1[3];
+    for (int q = 0; q < 3; ++q) i1[q] = a.tables[kInv1 + (5 + q) * 64 + L];
+    for (int e = tid; e < 5 * 64; e += kThreadsPerGate) my.inv1[e] = a.tables[kInv1 + e];
+    auto pause = [] { __builtin_amdgcn_sched_barrier(0); };
     const __amdgpu_buffer_rsrc_t key_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<double2 *>(a.bk_fft), 0, (int)((size_t)a.n * 16 * kHalf * sizeof(double2)), 0x00020000);
     const uint32_t voff = (uint32_t)tid * (uint32_t)sizeof(double2);
@@ -177,14 +212,15 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     double2 *const poly = my.buf + wv * kPolyStride;      // pass 1: this wave's polynomial
     double2 *const mine = my.buf + row_of(wv, L);         // passes 2, 3: this lane's row
     double worst = 0.0;
-    // Wave priority, throughput kernel only (three workgroups share a CU): the phases that lead up to
-    // a barrier or follow one directly -- rotation and forward pass 1, forward passes 2 and 3, inverse
-    // pass 1 and the accumulation -- issue ahead of the other workgroups' gather, products and
-    // scatter, which wait on swaps and key loads anyway.  Measured: 3-4 % (12,288 gates 55.0 -> 53.3 ms,
-    // 65,536 gates 286 -> 276 ms); raising the priority at the gather instead costs up to 30 %.
+    // Wave priority, throughput kernel only (two or three workgroups share a CU): the phases that lead up to a
+    // barrier or follow one directly -- rotation and forward pass 1, inverse pass 1 and the accumulation -- issue
+    // first, forward passes 2 and 3 next, and the other workgroups' gather, products and scatter, which wait
+    // on swaps and key loads anyway, last.  Measured against one high level for all of the former: 301 gates
+    // 2.36 -> 2.26 ms, 768 gates 3.41 -> 3.30 ms; raising the gather instead costs up to 30 %.
     auto priority = [](int level) {
         if (AHEAD) return;               // a lone workgroup per CU has nobody to overtake
-        if (level) __builtin_amdgcn_s_setprio(2);
+        if (level == 2) __builtin_amdgcn_s_setprio(2);
+        else if (level == 1) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
     };
 
@@ -246,7 +282,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     int abar_next = my.bar[0];
     for (int i = 0; i < a.n; ++i) {
         double2 x[8];
-        priority(1);
+        priority(2);
         {
         // ---- rotate, subtract, decompose, fold and twist ----
         // read one step ahead (off the critical path); the same in every lane, so it goes to a scalar
@@ -298,16 +334,23 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         }
         }
         if (i > 0) load_ahead(i, 6);
-        fwd_pass1_store(x, ln, poly, L);
+        {
+            const_double *u = uniform_constants(a.tables);
+            dft8_twiddled<false>(x, pass1_twiddles(u), [&](int k, double2 v) { poly[k * kRowStride + L] = v; }, pause);
+        }
         __syncthreads();
         if (i > 0) load_ahead(i, 7);
 
         // ---- this wave's frequencies of all four polynomials ----
-        fwd_pass2_load(x, mine, L);
+        priority(1);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = mine[(L & 7) + 8 * j];
         wave_sync();
-        fwd_pass2_store(x, ln, mine, L);
+        dft8_shifted<false>(x, f2, [&](int k, double2 v) { mine[k * kGrpStride + (L & 7)] = v; }, pause);
         wave_sync();
-        fwd_pass3(x, mine, L);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = mine[(L & 7) * kGrpStride + j];
+        dft8_shifted<false>(x, f3);
         priority(0);
         gather_rows(x);                      // x[2 r + q]: digit polynomial r at slot 256 q + tid
 
@@ -346,30 +389,40 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
 
         // ---- back: scatter the four output spectra to their lanes, inverse passes 3 and 2 ----
         scatter_rows(y);
-        inv_pass3_store(y, ln, mine, L);
+        dft8_plain<true>(y, [&](int k, double2 v) { mine[(L & 7) * kGrpStride + k] = v; }, pause);
         wave_sync();
         load_ahead(next, 1);
-        inv_pass2(y, mine, L);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) y[k] = mine[k * kGrpStride + (L & 7)];
         wave_sync();
         load_ahead(next, 2);
-        inv_pass2_store(y, mine, L);
+        dft8_shifted<true>(y, i2, [&](int k, double2 v) { mine[(L & 7) + 8 * k] = v; }, pause);
+        double2 p[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) p[q] = q < 5 ? my.inv1[q * 64 + L] : i1[q < 5 ? 0 : q - 5];
         __syncthreads();
         abar_next = my.bar[i + 1];           // bar[n] exists (it holds bbar)
         load_ahead(next, 3);
 
         // ---- inverse pass 1 of output polynomial o = wave, exact rounding, accumulate ----
-        priority(1);
-        inv_pass1(x, ln, poly, L);
+        priority(2);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = poly[k * kRowStride + L];
+        x[0] = cmul(x[0], p[7]);
+        dft8_twiddled<true>(x, unpack_twiddles(p));
+        const_double *u = uniform_constants(a.tables);
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
+            if (m) x[m] = cturn(x[m], -u[m]);
             const double part[2] = {x[m].x, x[m].y};
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                // 1.5 * 2^52 - part leaves round-to-nearest(-part) = -round(part) mod 2^32 in the low word
-                // (ties go to even either way); the complemented accumulator takes it: ~(ACC + r) = ~ACC - r
-                const double shifted = 6755399441055744.0 - part[h];
+                // 1.5 * 2^52 - value leaves round-to-nearest(-value) = -round(value) mod 2^32 in the low word (ties
+                // go to even either way); the complemented accumulator takes it: ~(ACC + r) = ~ACC - r.
+                // The value's pending cosine rides in the multiply-add, so it is rounded once.
+                const double shifted = m ? fma(-u[16 + m], part[h], 6755399441055744.0) : 6755399441055744.0 - part[h];
                 uint32_t r = (uint32_t)__double2loint(shifted);
-                if (MARGIN) worst = fmax(worst, fabs(part[h] + (shifted - 6755399441055744.0)));
+                if (MARGIN) worst = fmax(worst, fabs((m ? u[16 + m] * part[h] : part[h]) + (shifted - 6755399441055744.0)));
                 if (sel) r <<= 16;
                 if (m == 3 && h == 1) load_ahead(next, 4);
                 atomicAdd(&my.acc[comp][L + 64 * m + h * kHalf], r);
@@ -565,14 +618,6 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
             for (int q = 0; q < 8; ++q) p[q] = table[q * width + lane];
         };
-        // the uniform ones come through the scalar cache once a step (the pointer is made opaque, or the
-        // compiler keeps all of them in scalar registers and spills)
-        typedef __attribute__((address_space(4))) const double const_double;
-        auto uniform_constants = [&]() {
-            const_double *p = (const_double *)(uintptr_t)(a.tables + kUniform);
-            asm volatile("" : "+s"(p));
-            return p;
-        };
         auto store_columns = [&](const double2 (&v)[8]) {            // element k of lane L at row k, column L
 #pragma unroll
             for (int k = 0; k < 8; ++k) buf[k * kRowStride + L] = v[k];
@@ -628,14 +673,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             read_component(0);
             load_twiddles(my.fwd2, 8, L >> 3, p);
             const Twiddle8 w2 = unpack_twiddles(p);
-            Twiddle8 w1;
-            const_double *u = uniform_constants();
-            w1.t[0] = 0.0;
-#pragma unroll
-            for (int e = 1; e < 8; ++e) w1.t[e] = u[e];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w1.rho[e] = u[8 + e];
-            w1.sig0 = u[12]; w1.sig1 = u[13]; w1.tau = u[14]; w1.tauh = u[15];
+            const Twiddle8 w1 = pass1_twiddles(uniform_constants(a.tables));
 
             digits(0);
             dft8_twiddled<false>(x[0], w1);
@@ -655,7 +693,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             dft8_twiddled<false>(x[1], w2);
             REGION_END();
             store_across(x[1]); load_along(x[1]); store_columns(x[2]); load_row(x[2]);
-            dft8_shifted(x[0], f3);
+            dft8_shifted<false>(x[0], f3);
             dft8_twiddled<false>(x[3], w1);
             TRANSPOSE_BESIDE(5) TRANSPOSE_BESIDE(5)
             REGION_END();
@@ -663,18 +701,18 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             dft8_twiddled<false>(x[2], w2);
             REGION_END();
             store_across(x[2]); load_along(x[2]); store_columns(x[3]); load_row(x[3]);
-            dft8_shifted(x[1], f3);
+            dft8_shifted<false>(x[1], f3);
             TRANSPOSE_BESIDE(2) TRANSPOSE_BESIDE(1)
             REGION_END();
             load_batch(0); load_batch(1);
             dft8_twiddled<false>(x[3], w2);
             REGION_END();
             store_across(x[3]); load_along(x[3]);
-            dft8_shifted(x[2], f3);
+            dft8_shifted<false>(x[2], f3);
             TRANSPOSE_BESIDE(3)
             REGION_END();
             load_batch(2);
-            dft8_shifted(x[3], f3);
+            dft8_shifted<false>(x[3], f3);
             REGION_END();
         }
 
@@ -718,7 +756,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             const Twiddle8 w1 = unpack_twiddles(p);
             const double2 w10 = p[7];
             double tan_m[8], cos_m[8];
-            const_double *u = uniform_constants();
+            const_double *u = uniform_constants(a.tables);
 #pragma unroll
             for (int m = 1; m < 8; ++m) { tan_m[m] = u[m]; cos_m[m] = u[16 + m]; }
             uint32_t low[8][2];
