@@ -171,9 +171,13 @@ __device__ __forceinline__ Twiddle8 pass1_twiddles(const_double *u) {
 // XCD has touched yet is what keeps the workgroups of an XCD within the few rows its L2 holds.
 template <bool MARGIN, int AHEAD>
 __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
+    extern __shared__ __align__(4096) unsigned char lds_raw[];
     GateLds &my = *reinterpret_cast<GateLds *>(lds_raw);
     static_assert(AHEAD == 0 || AHEAD == 4, "no key values or a whole step's ahead");
+
+    // The accumulator's components: with their mirrors in the throughput kernel, 4 KB each from a multiple of
+    // 4 KB on, without mirrors, in the latency kernel (see the rotation).
+    auto acc = [&](int c) -> uint32_t * { return AHEAD ? reinterpret_cast<uint32_t *>(lds_raw) + c * kN : my.acc[c]; };
 
     const int tid = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave, in a scalar register
@@ -196,9 +200,12 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     const __amdgpu_buffer_rsrc_t key_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<double2 *>(a.bk_fft), 0, (int)((size_t)a.n * 16 * kHalf * sizeof(double2)), 0x00020000);
     const uint32_t voff = (uint32_t)tid * (uint32_t)sizeof(double2);
-    auto key_offset = [](int row, int part, int r, int o2) {
-        return (uint32_t)row * 16u * kHalf * (uint32_t)sizeof(double2) +
-               (uint32_t)(((r * 4 + 2 * (part & 1) + o2) * kHalf + 256 * (part >> 1)) * sizeof(double2));
+    // value of row r, output 2 (part & 1) + o2 at slot 256 (part >> 1) + tid; the two slots of a thread share the scalar
+    // offset, so that the compiler forms it once for both
+    auto key = [&](int row, int part, int r, int o2) {
+        return load_key(key_rsrc, voff + (part >> 1 ? 4096u : 0u),
+                        (uint32_t)row * 16u * kHalf * (uint32_t)sizeof(double2) +
+                            (uint32_t)((r * 4 + 2 * (part & 1) + o2) * kHalf * sizeof(double2)));
     };
 
     const int comp = wv >> 1;                   // pass 1 forward: component of D; inverse: component of ACC
@@ -259,9 +266,9 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         const uint32_t first = bbar < kN ? kEighth : 0u - kEighth;   // X^-bbar v, closed form
         for (int j = tid; j < kN; j += kThreadsPerGate) {
             const uint32_t c = ~(j < kN - bb ? first : 0u - first);
-            my.acc[0][j] = ~0u;
-            my.acc[1][j] = c;
-            if (j < kMirror) { my.acc[0][kN + j] = 0u - ~0u - 2u; my.acc[1][kN + j] = 0u - c - 2u; }
+            acc(0)[j] = ~0u;
+            acc(1)[j] = c;
+            if (!AHEAD && j < kMirror) { my.acc[0][kN + j] = 0u - ~0u - 2u; my.acc[1][kN + j] = 0u - c - 2u; }
         }
     }
     __syncthreads();
@@ -274,7 +281,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         for (int r = 2 * (e & 1); r < 2 * (e & 1) + 2; ++r)
 #pragma unroll
             for (int o2 = 0; o2 < 2; ++o2)
-                ahead[e >> 1][r][o2] = load_key(key_rsrc, voff, key_offset(row, e >> 1, r, o2));
+                ahead[e >> 1][r][o2] = key(row, e >> 1, r, o2);
     };
 #pragma unroll
     for (int e = 0; e < 8; ++e) load_ahead(0, e);
@@ -289,7 +296,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         // register and everything below that does not depend on the lane is scalar arithmetic
         const int abar = __builtin_amdgcn_readfirstlane(abar_next);
         typedef __attribute__((address_space(3))) const uint32_t lds_word;
-        const uint32_t acc_at = (uint32_t)(uintptr_t)(lds_word *)my.acc[comp];
+        const uint32_t acc_at = (uint32_t)(uintptr_t)(lds_word *)acc(comp);
         const uint32_t lane4 = (uint32_t)L << 2;
         const uint32_t back4 = (uint32_t)(0 - abar) << 2;       // X^abar reads abar coefficients back, mod 8192 bytes
         // Coefficient j = L + 64 m + 512 h of X^abar ACC is +-ACC[(j - abar) mod N].  The 64 lanes read 64
@@ -302,7 +309,24 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         // i.e. (c[src] ^ flip) + c[j] + (doffset + 2 + flip); a lane in the mirror needs the other flip,
         // and (mu ^ flip) + flip = (c ^ ~flip) + ~flip for either flip: two vector instructions per
         // coefficient, whatever the lane.
+        // A wave alone on its SIMD pays for scalar instructions like for vector ones; the latency kernel
+        // therefore keeps address and sign per lane (five vector instructions per coefficient instead of three
+        // and five scalar ones) and needs no mirror: bit 12 of a lane's own sum is its sign, the bits below are its
+        // offset, and (c ^ flip) + flip is +-ACC - 1 for either flip.
         uint32_t from[8][2], flip[8][2], bias[8][2];
+        if (AHEAD) {
+            uint32_t low12 = 4095u;
+            asm("" : "+v"(low12));                   // in a vector register: one v_and_or_b32 takes no second constant
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t s = (lane4 + back4 + 4096u) + (uint32_t)(64 * m + h * kHalf) * 4u;
+                    from[m][h] = (s & low12) | acc_at;
+                    flip[m][h] = (uint32_t)__builtin_amdgcn_sbfe((int32_t)s, 12, 1);
+                    bias[m][h] = doffset + 2u;
+                }
+        } else
 #pragma unroll
         for (int m = 0; m < 8; ++m)
 #pragma unroll
@@ -320,14 +344,15 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         for (int m = 0; m < 8; ++m)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                rot[m][h] = *(lds_word *)(uintptr_t)(lane4 + from[m][h]);
+                rot[m][h] = *(lds_word *)(uintptr_t)(AHEAD ? from[m][h] : lane4 + from[m][h]);
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
             int32_t dig[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int j = L + 64 * m + h * kHalf;
-                const uint32_t d = (rot[m][h] ^ flip[m][h]) + my.acc[comp][j] + bias[m][h];
+                const uint32_t turned = (rot[m][h] ^ flip[m][h]) + (AHEAD ? flip[m][h] : 0u);
+                const uint32_t d = turned + acc(comp)[j] + bias[m][h];
                 dig[h] = __builtin_amdgcn_sbfe((int32_t)d, dfield, (uint32_t)a.bgbit);    // signed field
             }
             x[m] = make_double2((double)dig[0], (double)dig[1]);
@@ -365,7 +390,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
 #pragma unroll
                 for (int o2 = 0; o2 < 2; ++o2)
                     k[r][o2] = part < AHEAD ? ahead[part < AHEAD ? part : 0][r][o2]
-                                            : load_key(key_rsrc, voff, key_offset(i, part, r, o2));
+                                            : key(i, part, r, o2);
 #pragma unroll
             for (int o2 = 0; o2 < 2; ++o2) {
                 // one chain of fused multiply-adds per real output (four independent chains per part)
@@ -425,8 +450,8 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
                 if (MARGIN) worst = fmax(worst, fabs((m ? u[16 + m] * part[h] : part[h]) + (shifted - 6755399441055744.0)));
                 if (sel) r <<= 16;
                 if (m == 3 && h == 1) load_ahead(next, 4);
-                atomicAdd(&my.acc[comp][L + 64 * m + h * kHalf], r);
-                if (m == 0 && h == 0) atomicSub(&my.acc[comp][kN + L], r);      // the mirror holds -c - 2
+                atomicAdd(&acc(comp)[L + 64 * m + h * kHalf], r);
+                if (!AHEAD && m == 0 && h == 0) atomicSub(&my.acc[comp][kN + L], r);      // the mirror holds -c - 2
             }
         }
         __syncthreads();
@@ -437,8 +462,8 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     {
         uint32_t *ext = a.ext + gi * (size_t)(kN + 1);
         // ACC = ~c, -ACC = c + 1
-        for (int j = tid; j < kN; j += kThreadsPerGate) ext[j] = j == 0 ? ~my.acc[0][0] : my.acc[0][kN - j] + 1u;
-        if (tid == 0) ext[kN] = ~my.acc[1][0];
+        for (int j = tid; j < kN; j += kThreadsPerGate) ext[j] = j == 0 ? ~acc(0)[0] : acc(0)[kN - j] + 1u;
+        if (tid == 0) ext[kN] = ~acc(1)[0];
     }
     __syncthreads();          // the next gate's prologue overwrites the accumulator
     }
