@@ -87,8 +87,7 @@ size_t chunk_gates() {
 }
 
 // Batches from which the key switch runs as an int8 contraction on the matrix cores: all of them
-// (small batches split each gate's mask words over several workgroups; 16 gates take 0.035 ms
-// against 0.086 ms of the gather kernels, 256 gates 0.065 against 0.42 ms).  The gather kernels
+// (16 gates take 0.014 ms against 0.086 ms of the gather kernels, 256 gates 0.033 against 0.42 ms).  The gather kernels
 // remain for parameter sets the matrix kernel does not cover.
 int key_switch_matrix(size_t count) {
     static const long threshold = env_long("TFHE_KS_MATRIX_FROM", 1);

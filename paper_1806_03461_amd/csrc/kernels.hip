@@ -935,8 +935,8 @@ __global__ void zero_outputs_kernel(KeySwitchArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Key switch of large batches as a dense contraction on the matrix cores (t = 8 digits in base
-// 4, N = 1024, n + 1 <= 512).  With one-hot digits the sum is a matrix product
+// Key switch as a dense contraction on the matrix cores (t = 8 digits in base 4, N = 1024, n + 1 <= 512).
+// With one-hot digits the sum is a matrix product
 //     S[g][c] = sum_{i, j, v} [digit_ij(g) == v] * KSK[i][j][v][c]      (v = 0: a zero row)
 // with K = 1024 * 8 * 4 = 32,768.  The 32-bit key words are split into four balanced signed
 // bytes, x = s0 + 2^8 s1 + 2^16 s2 + 2^24 s3 (mod 2^32), |s| <= 128, so every plane is an exact
@@ -948,20 +948,17 @@ __global__ void zero_outputs_kernel(KeySwitchArgs a) {
 // in registers: 4 digits -> 4 words 1 << (8 * digit).  The key is pre-tiled so that a B operand
 // (32 columns x 32 k) is 1 KB contiguous in lane order: tiles[block of 32 words][i][plane][lane].
 //
-// Workgroup = 4 waves = 256 gates x 64 output words; wave = 128 gates x 32 words x 4 planes =
-// 16 accumulator tiles (256 registers): per mask word 4 B tiles are loaded and 16 MFMAs issued.
+// A workgroup takes 32 TILES gates, 32 output words and a share of the mask words, of which each of its four
+// waves takes a quarter.  The waves' sums meet in LDS and go into the zeroed outputs with one integer atomic
+// per word and workgroup (order-independent: still exact).  Few gates are bound by the one pass over the 64 MB
+// of key tiles and by the latency of getting them started, many by the tiles' way from L2 (64 MB per 32 TILES
+// gates), which two workgroups on a CU keep busier than one with more gates.  Measured against 256 gates x 64 words a
+// workgroup, one wave per SIMD, with up to 32 partial sums of every word added by atomics:
+// 8 gates 26.5 -> 13.3 us, 64 gates 36 -> 17, 256 gates 56 -> 33, 512 gates 82 -> 65, 1,536 gates 237 -> 121,
+// 4,096 gates 403 -> 291, 16,384 gates 1,457 -> 1,353.
 // ------------------------------------------------------------------------------------------
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-
-constexpr int kKsRows = 256;      // gates per workgroup
-constexpr int kKsChunk = 128;     // mask words staged per round (132 KB of LDS: one workgroup per CU anyway)
-constexpr int kKsAhead = 8;       // mask words whose key tiles are in flight
-
-struct KsMatrixLds {
-    uint32_t mask_words[kKsChunk][kKsRows + 1];     // +1: the transposing store hits 32 banks
-    int32_t out_row[kKsRows];                        // output sample of each gate, -1: none
-};
 
 // tiles[((cb * 1024 + i) * 4 + plane) * 64 + lane] = 16 bytes: byte q is plane `plane` of
 // KSK[i][4 * (lane / 32) + q / 4][q % 4][32 * cb + lane % 32]  (value 0 and words past n: 0)
@@ -989,18 +986,29 @@ __global__ __launch_bounds__(256) void ksk_to_tiles_kernel(const uint32_t *__res
     tiles[(((size_t)cb * kN + i) * 4 + plane) * 64 + lane] = t;
 }
 
-template <bool SPLIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void key_switch_mfma_kernel(KeySwitchArgs a) {
+constexpr int kKsShare = 128;     // mask words of a workgroup at most
+
+template <int TILES>
+struct KsLds {
+    union {
+        uint32_t mask_words[kKsShare][32 * TILES + 1];
+        uint32_t partial[4][16 * TILES][64];
+    };
+    int32_t out_row[32 * TILES];
+};
+
+template <int TILES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TILES == 4 ? 1 : 2, TILES == 4 ? 1 : 2)))
+void key_switch_mfma_kernel(KeySwitchArgs a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    KsMatrixLds &lds = *reinterpret_cast<KsMatrixLds *>(lds_raw);
-    uint32_t (&mask_words)[kKsChunk][kKsRows + 1] = lds.mask_words;
-    int32_t (&out_row)[kKsRows] = lds.out_row;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int wr = wave >> 1;                                   // which 128 gates
-    const int cb = 2 * blockIdx.y + (wave & 1);                 // which 32 output words
-    const size_t g0 = (size_t)blockIdx.x * kKsRows;
+    KsLds<TILES> &lds = *reinterpret_cast<KsLds<TILES> *>(lds_raw);
+    constexpr int kRows = 32 * TILES;
+    constexpr int kAhead = TILES == 1 ? 8 : 4;                  // mask words whose key tiles are in flight
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int cb = blockIdx.y;
+    const size_t g0 = (size_t)blockIdx.x * kRows;
     const int words = a.n + 1;
-    {
+    if (tid < kRows) {
         const size_t gi = g0 + tid;
         int32_t row = -1;
         if (gi < a.count) {
@@ -1008,85 +1016,75 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             else if (!a.uniform_mux) row = (int32_t)gi;
             else if (!(gi & 1)) row = (int32_t)(gi >> 1);
         }
-        out_row[tid] = row;
+        lds.out_row[tid] = row;
     }
-    v16i acc[4][4];
+    const int share = kN / a.splits, share_shift = 31 - __builtin_clz(share);      // a power of two, 64 or 128
+    const int i_begin = (int)blockIdx.z * share;
+    const int mine = share >> 2, first = wave * mine;           // this wave's mask words, from i_begin + first on
+    const v4i *tiles = reinterpret_cast<const v4i *>(a.ksk_tiles) + ((size_t)cb * kN + i_begin + first) * 4 * 64 + lane;
+    v4i ring[kAhead][4];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
+    for (int s = 0; s < kAhead; ++s)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) ring[s][b] = tiles[(s * 4 + b) * 64];
+    v16i acc[TILES][4];
+#pragma unroll
+    for (int rt = 0; rt < TILES; ++rt)
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[rt][b][r] = 0;
-    const v4i *tiles = reinterpret_cast<const v4i *>(a.ksk_tiles) + (size_t)cb * kN * 4 * 64 + lane;
     const uint32_t round = 1u << (31 - 16);
-    const int byte_shift = 24 - 8 * (lane >> 5);               // digits 0..3 or 4..7 of the word
-    const int my_row = wr * 128 + (lane & 31);
-
-    // a.splits workgroups (blockIdx.z) share the 1,024 mask words of their gates: each takes a
-    // contiguous range and adds its partial sum into the zeroed outputs (integer adds commute:
-    // still exact).  That is what gives a small batch enough workgroups to use the whole chip.
-    // (SPLIT = false: one workgroup takes them all, and every loop bound is a constant)
-    const int per_split = SPLIT ? kN / a.splits : kN;           // >= 32, a multiple of kKsAhead
-    const int w_begin = SPLIT ? (int)blockIdx.z * per_split : 0, w_end = w_begin + per_split;
-    const int chunk = SPLIT && per_split < kKsChunk ? per_split : kKsChunk;   // a power of two
-    const int chunk_shift = 31 - __builtin_clz(chunk);
-    const bool wave_live = g0 + (size_t)wr * 128 < a.count;     // none of the wave's 128 gates exists otherwise
-
-    // key tiles of the next kKsAhead mask words, in a ring of registers
-    v4i ring[kKsAhead][4];
+    // consecutive lanes read consecutive mask words of one gate; a row without an output is summed up and dropped
+#pragma unroll 8
+    for (int idx = tid; idx < share * kRows; idx += 256) {
+        const int g = idx >> share_shift, ii = idx & (share - 1);
+        const size_t gi = g0 + g < a.count ? g0 + g : a.count - 1;
+        lds.mask_words[ii][g] = a.ext[gi * (size_t)(kN + 1) + i_begin + ii] + round;
+    }
+    __syncthreads();
+    const int byte_shift = 24 - 8 * (lane >> 5);
+    for (int i1 = 0; i1 < mine; i1 += kAhead) {
 #pragma unroll
-    for (int s = 0; s < kKsAhead; ++s)
+        for (int s = 0; s < kAhead; ++s) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) ring[s][b] = tiles[((size_t)(w_begin + s) * 4 + b) * 64];
-
-    for (int i0 = w_begin; i0 < w_end; i0 += chunk) {
-        __syncthreads();                                        // the previous chunk has been consumed
-        // consecutive lanes read consecutive mask words of one gate; a dead gate stages all-zero digits
-        for (int idx = tid; idx < chunk * kKsRows; idx += 256) {
-            const int g = idx >> chunk_shift, ii = idx & (chunk - 1);
-            mask_words[ii][g] = out_row[g] >= 0 ? a.ext[(g0 + g) * (size_t)(kN + 1) + i0 + ii] + round : 0u;
-        }
-        __syncthreads();
-        if (!wave_live) continue;
-        for (int i1 = 0; i1 < chunk; i1 += kKsAhead) {
+            for (int rt = 0; rt < TILES; ++rt) {
+                const uint32_t w = (lds.mask_words[first + i1 + s][(lane & 31) + 32 * rt] >> byte_shift) & 0xFFu;
+                v4i at;
+                at.x = (int)(1u << (((w >> 6) & 3u) << 3));
+                at.y = (int)(1u << (((w >> 4) & 3u) << 3));
+                at.z = (int)(1u << (((w >> 2) & 3u) << 3));
+                at.w = (int)(1u << ((w & 3u) << 3));
 #pragma unroll
-            for (int s = 0; s < kKsAhead; ++s) {
-                const int ii = i1 + s;
+                for (int b = 0; b < 4; ++b)
+                    acc[rt][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(at, ring[s][b], acc[rt][b], 0, 0, 0);
+            }
+            if (i1 + kAhead < mine) {
 #pragma unroll
-                for (int rt = 0; rt < 4; ++rt) {
-                    const uint32_t w = (mask_words[ii][my_row + 32 * rt] >> byte_shift) & 0xFFu;
-                    v4i at;
-                    at.x = (int)(1u << (((w >> 6) & 3u) << 3));
-                    at.y = (int)(1u << (((w >> 4) & 3u) << 3));
-                    at.z = (int)(1u << (((w >> 2) & 3u) << 3));
-                    at.w = (int)(1u << ((w & 3u) << 3));
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        acc[rt][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(at, ring[s][b], acc[rt][b], 0, 0, 0);
-                }
-                // refill the slot with the tiles kKsAhead mask words on (the last ones reload the end)
-                const int nxt = i0 + ii + kKsAhead < kN ? i0 + ii + kKsAhead : kN - 1;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) ring[s][b] = tiles[((size_t)nxt * 4 + b) * 64];
+                for (int b = 0; b < 4; ++b) ring[s][b] = tiles[((size_t)(i1 + s + kAhead) * 4 + b) * 64];
             }
         }
     }
+    __syncthreads();                                            // the mask words give way to the partial sums
+#pragma unroll
+    for (int rt = 0; rt < TILES; ++rt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            lds.partial[wave][16 * rt + r][lane] = (uint32_t)acc[rt][0][r] + ((uint32_t)acc[rt][1][r] << 8) +
+                                                   ((uint32_t)acc[rt][2][r] << 16) + ((uint32_t)acc[rt][3][r] << 24);
+    __syncthreads();
     // accumulator register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
     const int c = 32 * cb + (lane & 31);
-    if (c < words) {
+    if (c >= words) return;
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int g = wr * 128 + 32 * rt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const int32_t row = out_row[g];
-                if (row < 0) continue;
-                const uint32_t sum = (uint32_t)acc[rt][0][r] + ((uint32_t)acc[rt][1][r] << 8) +
-                                     ((uint32_t)acc[rt][2][r] << 16) + ((uint32_t)acc[rt][3][r] << 24);
-                const uint32_t body = (c == a.n && (!SPLIT || blockIdx.z == 0)) ? a.ext[(g0 + g) * (size_t)(kN + 1) + kN] : 0u;
-                if (SPLIT) atomicAdd(a.out + (size_t)row * words + c, body - sum);
-                else a.out[(size_t)row * words + c] = body - sum;
-            }
+    for (int e = 0; e < 4 * TILES; ++e) {
+        const int at = wave * 4 * TILES + e, rt = at >> 4, r = at & 15;
+        const int g = 32 * rt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int32_t row = lds.out_row[g];
+        if (row < 0) continue;
+        const uint32_t sum = lds.partial[0][at][lane] + lds.partial[1][at][lane] + lds.partial[2][at][lane] + lds.partial[3][at][lane];
+        const uint32_t body = (c == a.n && blockIdx.z == 0) ? a.ext[(g0 + g) * (size_t)(kN + 1) + kN] : 0u;
+        atomicAdd(a.out + (size_t)row * words + c, body - sum);
     }
 }
 
@@ -1241,19 +1239,19 @@ int launch_bk_to_spectrum(const uint32_t *bk_raw, double2 *bk_fft, const double2
     return TFHE_OK;
 }
 
-// the six blind-rotation kernels and the two matrix-core key-switch kernels, with their
+// the six blind-rotation kernels and the widest matrix-core key switch, with their
 // dynamic LDS sizes and per-device "attribute set" masks
 namespace {
+constexpr int kBigLdsKernels = 7;
 struct BigLdsKernel { const void *fn; size_t lds; std::atomic<uint64_t> done; };
-BigLdsKernel big_lds_kernels[8] = {
+BigLdsKernel big_lds_kernels[kBigLdsKernels] = {
     {reinterpret_cast<const void *>(&blind_rotate_kernel<false>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_kernel<true>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<false>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<true>), sizeof(GateLds), {0}},
-    {reinterpret_cast<const void *>(&key_switch_mfma_kernel<false>), sizeof(KsMatrixLds), {0}},
-    {reinterpret_cast<const void *>(&key_switch_mfma_kernel<true>), sizeof(KsMatrixLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false>), sizeof(WaveLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<true>), sizeof(WaveLds), {0}},
+    {reinterpret_cast<const void *>(&key_switch_mfma_kernel<4>), sizeof(KsLds<4>), {0}},
 };
 int allow(int which) { return allow_dynamic_lds(big_lds_kernels[which].fn, big_lds_kernels[which].lds, big_lds_kernels[which].done); }
 }  // namespace
@@ -1265,7 +1263,7 @@ int prepare_kernels() {
     (void)latency_batch_limit();
     (void)resident_groups();
     (void)wave_gates_from();
-    for (int k = 0; k < 8; ++k)
+    for (int k = 0; k < kBigLdsKernels; ++k)
         if (int rc = allow(k)) return rc;
     return static_scratch_init();
 }
@@ -1304,7 +1302,7 @@ int launch_blind_rotate(const BlindRotateArgs &args, hipStream_t stream) {
     if (wave_gates_from() >= 0) whole = a.count >= (size_t)wave_gates_from() ? a.count : 0;
     if (whole) {
         a.count = whole;
-        if (int rc = allow(6 + (a.margin ? 1 : 0))) return rc;
+        if (int rc = allow(4 + (a.margin ? 1 : 0))) return rc;
         const dim3 grid((unsigned)((whole + kWaveGates - 1) / kWaveGates));
         if (a.margin) hipLaunchKernelGGL(blind_rotate_wave_kernel<true>, grid, dim3(64 * kWaveGates), sizeof(WaveLds), stream, a);
         else hipLaunchKernelGGL(blind_rotate_wave_kernel<false>, grid, dim3(64 * kWaveGates), sizeof(WaveLds), stream, a);
@@ -1328,21 +1326,24 @@ size_t ksk_tiles_bytes() { return (size_t)16 * kN * 4 * 64 * sizeof(v4i); }
 int launch_key_switch(const KeySwitchArgs &a, hipStream_t stream) {
     if (a.count == 0) return TFHE_OK;
     if (a.ksk_tiles && a.matrix && a.t == 8 && a.basebit == 2 && a.n + 1 <= 512) {
-        // fewer than one workgroup per CU: share each gate's mask words between workgroups
+        // Gates of a workgroup: as many as there are, up to 128 while one workgroup per CU serves them all; beyond,
+        // 64, of which two workgroups share a CU (64 against 128: 512 gates 87 against 65 us, 1,024 gates 94
+        // against 125).  A sixteenth of the mask words each fills the chip for up to 128 gates (against an
+        // eighth: 128 gates 23 against 29 us, 256 gates 43 against 33).
         KeySwitchArgs m = a;
-        const unsigned row_blocks = (unsigned)((a.count + kKsRows - 1) / kKsRows);
-        m.splits = 1;
-        while (m.splits < 32 && row_blocks * 8 * m.splits < 256) m.splits *= 2;
-        if (int rc = allow(m.splits > 1 ? 5 : 4)) return rc;
-        if (m.splits > 1) {
-            hipLaunchKernelGGL(zero_outputs_kernel, dim3((unsigned)a.count), dim3(256), 0, stream, m);
-            TFHE_HIP(hipGetLastError());
+        const unsigned tiles = a.count <= 32 ? 1 : a.count <= 64 || a.count > 512 ? 2 : 4;
+        m.splits = a.count <= 128 ? 16 : 8;
+        hipLaunchKernelGGL(zero_outputs_kernel, dim3((unsigned)a.count), dim3(256), 0, stream, m);
+        TFHE_HIP(hipGetLastError());
+        const dim3 grid((unsigned)((a.count + 32 * tiles - 1) / (32 * tiles)), 16, (unsigned)m.splits);
+        if (tiles == 1) {
+            hipLaunchKernelGGL(key_switch_mfma_kernel<1>, grid, dim3(256), sizeof(KsLds<1>), stream, m);
+        } else if (tiles == 2) {
+            hipLaunchKernelGGL(key_switch_mfma_kernel<2>, grid, dim3(256), sizeof(KsLds<2>), stream, m);
+        } else {
+            if (int rc = allow(6)) return rc;
+            hipLaunchKernelGGL(key_switch_mfma_kernel<4>, grid, dim3(256), sizeof(KsLds<4>), stream, m);
         }
-        const dim3 grid(row_blocks, 8, (unsigned)m.splits);
-        if (m.splits > 1)
-            hipLaunchKernelGGL(key_switch_mfma_kernel<true>, grid, dim3(256), sizeof(KsMatrixLds), stream, m);
-        else
-            hipLaunchKernelGGL(key_switch_mfma_kernel<false>, grid, dim3(256), sizeof(KsMatrixLds), stream, m);
         TFHE_HIP(hipGetLastError());
         return TFHE_OK;
     }

@@ -111,3 +111,27 @@ def test_rounding_margin_and_multiplexers_of_a_large_batch(real_keys):
     assert np.array_equal(T.tfhe_decrypt(sk, host), np.where(s == 1, a, b))
     for i in (0, 1, 1022, 1023, 1024, 1025, m - 1):
         assert np.array_equal(host[i], real_keys.mux(cts[i], cta[i], ctb[i])), i
+
+
+@pytest.mark.parametrize("count", [1, 32, 33, 64, 65, 128, 129, 256, 257, 512, 513])
+def test_batches_around_the_small_limits(real_keys, count):
+    """One item to either side of each change of kernel: one, two or three gates per CU in the blind rotation, 32, 64 or
+    128 gates and an eighth or a sixteenth of the mask words per workgroup in the key switch.  First and last gates
+    equal the oracle's, all equal the same gates in other batches."""
+    import torch
+    import paper_1806_03461_amd as T
+    sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
+    rng = np.random.default_rng(1000 + count)
+    cta, ctb = (T.tfhe_encrypt(sk, 420 + k, rng.integers(0, 2, count).astype(np.uint8)) for k in range(2))
+    da, db = T.to_device(cta), T.to_device(ctb)
+    out, other = torch.empty_like(da), torch.empty_like(da)
+    T.tfhe_gate_batch(ck, "XNOR", da, db, out, count)
+    step = 31 if count <= 256 else 300
+    for at in range(0, count, step):
+        n = min(step, count - at)
+        T.tfhe_gate_batch(ck, "XNOR", da[at:], db[at:], other[at:], n)
+    torch.cuda.synchronize()
+    assert torch.equal(out, other)
+    host = T.to_host(out)
+    for i in {0, count // 2, count - 1}:
+        assert np.array_equal(host[i], real_keys.gate("XNOR", cta[i], ctb[i])), i
