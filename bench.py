@@ -291,7 +291,7 @@ def main():
                    "source": entry.get("source")}
     roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP64_VECTOR_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / FP64_VECTOR_PEAK_TFLOPS, 4),
-                "traffic": traffic, "kernel": "blind_rotate_kernel",
+                "traffic": traffic, "kernel": "blind_rotate_wave_kernel",
                 "avg_launch_ms": round(br_avg_ms, 4), "gates_per_launch": round(gates_per_launch, 1),
                 "flops_per_gate": flops_per_gate,
                 "peak_measured": round(measured_peak, 2),
