@@ -38,13 +38,15 @@ struct KeySwitchArgs {
 // kernels and the scheduler of narrow circuits go by.
 //   wave kernel       eight gates per CU at a time: 7.5 ms a round, 5.2 ms with at most four per CU in it,
 //                     6.3 ms with five
-//   four-wave kernel  1.6, 2.4 and 3.2 ms for one, two and three gates per CU; more begin a second round
+//   four-wave kernel  1.6, 2.4 and 3.2 ms for one, two and three gates per CU; more begin a second round: four per CU
+//                     take 4.7 ms as two launches of two (1,024 gates 4.8 ms a call, 5.3 on the wave kernel,
+//                     5.2 as three and one), five 6.1 ms (5.9 as three and two: the same), six 7.1 as twice three
 inline double rest_ms(size_t per_cu) {      // a launch of less than a round
-    const double ms[9] = {0.0, 1.6, 2.4, 3.2, 5.2, 6.1, 6.6, 7.1, 7.5};
+    const double ms[9] = {0.0, 1.6, 2.4, 3.2, 4.7, 6.1, 6.6, 7.1, 7.5};
     return ms[per_cu];
 }
 // of a batch's last, partial round: whether the four-wave kernels serve it faster than the wave kernel
-inline bool four_waves_faster(size_t per_cu) { return per_cu <= 3 || per_cu == 5; }
+inline bool four_waves_faster(size_t per_cu) { return per_cu <= 5; }
 constexpr size_t kRoundPerCu = 8;
 inline double rotation_ms(size_t items, size_t cus) {
     const size_t round = kRoundPerCu * cus, rest = items % round;

@@ -68,7 +68,7 @@ def test_small_batches_equal_the_four_wave_kernels():
     assert digests[0] == digests[1]
 
 
-@pytest.mark.parametrize("count", [769, 1281, 2047, 2048, 2049])
+@pytest.mark.parametrize("count", [769, 1024, 1025, 1281, 2047, 2048, 2049, 2900])
 def test_batches_around_a_round(real_keys, count):
     """Default dispatch on a CU's worth of rounds: the first and last gates and a few between equal the oracle's,
     and all of them equal the same gates evaluated in small batches."""
