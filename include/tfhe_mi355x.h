@@ -117,11 +117,15 @@ void tfhe_default_params(tfhe_params *p);
 int tfhe_keygen(const tfhe_params *p, uint64_t seed, tfhe_secret_key **sk, tfhe_cloud_key **ck);
 
 /* Encrypt nbits bits (HOST uint8, 0/1) into ct_host (HOST, [nbits][n+1]); bit 1 is the
- * torus value 1/8, bit 0 is -1/8; mask and noise come from `seed`. */
+ * torus value 1/8, bit 0 is -1/8; mask and noise come from `seed`.  Larger counts (from 400 at
+ * n = 500) are shared out over up to 16 threads that end with the call.  bits may lie in the
+ * last nbits bytes of ct_host; such a call runs in order, on the calling thread. */
 int tfhe_encrypt(const tfhe_secret_key *sk, uint64_t seed, const uint8_t *bits, size_t nbits,
                  uint32_t *ct_host);
 
-/* Decrypt: bits[i] = 1 iff the phase b - <a, s> of sample i, read as int32, is positive. */
+/* Decrypt: bits[i] = 1 iff the phase b - <a, s> of sample i, read as int32, is positive.
+ * Threads as in tfhe_encrypt (from 1,600 samples at n = 500).  bits may be the first nbits bytes
+ * of ct_host, which the call then overwrites, in order and on the calling thread. */
 int tfhe_decrypt(const tfhe_secret_key *sk, const uint32_t *ct_host, size_t nbits, uint8_t *bits);
 
 /* Noiseless ciphertext of a known bit (a = 0, b = +-1/8) into ct_host (HOST, n+1 words). */

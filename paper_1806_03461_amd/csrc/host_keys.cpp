@@ -115,6 +115,13 @@ std::vector<uint32_t> select_masks(const tfhe_secret_key *sk) {
     return m;
 }
 
+// Whether two buffers share bytes.  A call may be given its bits inside the ciphertext buffer (decryption in place,
+// say): in order, sample by sample, every word is read before it is overwritten, so such a call keeps to one thread.
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + b_bytes && y < x + a_bytes;
+}
+
 // body(begin, end) over [0, count) on up to 16 threads, each with at least `grain` items (below it a thread costs
 // more than it takes off: starting one is about 20 us).
 template <class F>
@@ -262,7 +269,8 @@ static int tfhe_encrypt_impl(const tfhe_secret_key *sk, uint64_t seed, const uin
     const Stream mask(seed, Stream::kEncMask), err(seed, Stream::kEncNoise);
     const std::vector<uint32_t> select = select_masks(sk);
     static const FillFn fill = pick_fill();
-    parallel_ranges(nbits, std::max<size_t>(1, 100000 / (size_t)n), [&](size_t begin, size_t end) {
+    const bool in_order = overlap(bits, nbits, ct, nbits * (size_t)(n + 1) * sizeof *ct);
+    parallel_ranges(nbits, in_order ? nbits : std::max<size_t>(1, 100000 / (size_t)n), [&](size_t begin, size_t end) {
         for (size_t s = begin; s < end; ++s) {
             uint32_t *c = ct + s * (size_t)(n + 1);
             const uint32_t body = (bits[s] ? kEighth : 0u - kEighth) + err.noise(s, sk->params.lwe_noise_log2);
@@ -283,7 +291,8 @@ static int tfhe_decrypt_impl(const tfhe_secret_key *sk, const uint32_t *ct, size
     const int n = sk->params.n;
     const std::vector<uint32_t> select = select_masks(sk);
     static const DotFn dot = pick_dot();
-    parallel_ranges(nbits, std::max<size_t>(1, 400000 / (size_t)n), [&](size_t begin, size_t end) {
+    const bool in_order = overlap(bits, nbits, ct, nbits * (size_t)(n + 1) * sizeof *ct);
+    parallel_ranges(nbits, in_order ? nbits : std::max<size_t>(1, 400000 / (size_t)n), [&](size_t begin, size_t end) {
         for (size_t s = begin; s < end; ++s) {
             const uint32_t *c = ct + s * (size_t)(n + 1);
             bits[s] = (int32_t)(c[n] - dot(select.data(), c, n)) > 0;

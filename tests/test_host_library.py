@@ -94,6 +94,23 @@ def test_encrypt_decrypt_match_oracle(real_keys):
     assert T.tfhe_encrypt(sk, 1, np.zeros(0, np.uint8)).shape == (0, 501)
 
 
+@pytest.mark.parametrize("count", [1, 801, 12544])
+def test_encryption_and_decryption_in_place(count):
+    """Bits inside the ciphertext buffer -- decryption into its first bytes, encryption of its last ones --
+    give what separate buffers give, whatever the count: samples are taken in order there."""
+    sk, _ = T.tfhe_keygen(T.Params(500, 2, 1, 2, 10, 1, 1, -15, -25), 5)
+    bits = np.random.default_rng(count).integers(0, 2, count).astype(np.uint8)
+    ct = T.tfhe_encrypt(sk, 3, bits)
+    buf = ct.copy()
+    assert T.lib().tfhe_decrypt(sk.handle, buf.ctypes.data, count, buf.ctypes.data) == 0
+    assert np.array_equal(buf.view(np.uint8).ravel()[:count], bits)
+    buf = np.zeros_like(ct)
+    tail = buf.view(np.uint8).reshape(-1)[-count:]
+    tail[:] = bits
+    assert T.lib().tfhe_encrypt(sk.handle, C.c_uint64(3), tail.ctypes.data, count, buf.ctypes.data) == 0
+    assert np.array_equal(buf, ct)
+
+
 _INTERN = {}
 
 
