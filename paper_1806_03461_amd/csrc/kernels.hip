@@ -1067,11 +1067,19 @@ void key_switch_mfma_kernel(KeySwitchArgs a) {
     }
     __syncthreads();                                            // the mask words give way to the partial sums
 #pragma unroll
-    for (int rt = 0; rt < TILES; ++rt)
+    for (int rt = 0; rt < TILES; ++rt) {
+        // With four tiles the accumulators are all 256 accumulation registers; left alone the compiler copies every one of
+        // them to vector registers first and spills three.  The last tile stays where it is until the others are stored (212
+        // vector registers; by events around the zeroing and this kernel, with the spills and now: 128 gates 30.5 and 30.4 us,
+        // 256 gates 40.5 and 40.4, 512 gates 72.0 and 71.6).
+        if constexpr (TILES == 4)
+            if (rt == TILES - 1) asm volatile("" : "+a"(acc[rt][0]), "+a"(acc[rt][1]), "+a"(acc[rt][2]), "+a"(acc[rt][3]));
 #pragma unroll
         for (int r = 0; r < 16; ++r)
             lds.partial[wave][16 * rt + r][lane] = (uint32_t)acc[rt][0][r] + ((uint32_t)acc[rt][1][r] << 8) +
                                                    ((uint32_t)acc[rt][2][r] << 16) + ((uint32_t)acc[rt][3][r] << 24);
+        if constexpr (TILES == 4) __builtin_amdgcn_sched_barrier(0);
+    }
     __syncthreads();
     // accumulator register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
     const int c = 32 * cb + (lane & 31);

@@ -1,0 +1,23 @@
+"""What the compiler reports for the device kernels, with the build's own flags: no kernel needs scratch memory.
+Scratch is memory that the runtime sets up for a queue when the first kernel that needs it is dispatched, and
+tfhe_gate_batch_noalloc promises that no allocation of any kind happens inside."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_1806_03461_amd import build
+
+
+def test_no_kernel_uses_scratch_memory():
+    if not shutil.which("hipcc"):
+        pytest.skip("no hipcc")
+    r = subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", "-Rpass-analysis=kernel-resource-usage", "-o", os.devnull,
+                        os.path.join(build.CSRC, "kernels.hip")], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout
+    names = re.findall(r"Function Name: (\S+)", r.stdout)
+    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stdout)]
+    assert len(names) == len(scratch) and any("blind_rotate_wave_kernel" in n for n in names), r.stdout
+    assert [(n, s) for n, s in zip(names, scratch) if s] == []
