@@ -191,7 +191,9 @@ int tfhe_mux_batch(tfhe_cloud_key *ck, const uint32_t *s, const uint32_t *a, con
  * tree representation of the circuit can be evaluated in parallel").  gates: HOST,
  * topologically ordered (an input is either never written or written by an earlier
  * record), every wire written at most once.  wires: DEVICE [nwires][n+1], read and
- * written in place.  Gates are grouped by depth and each depth is run as batches. */
+ * written in place.  Gates are grouped into as many
+ * levels as the circuit is deep, and each level is run as batches; a gate that can wait without
+ * making the circuit deeper may run in a later level than its depth. */
 int tfhe_gate_stream(tfhe_cloud_key *ck, const tfhe_gate_rec *gates, size_t ngates,
                      uint32_t *wires, size_t nwires, void *stream);
 
@@ -277,13 +279,16 @@ typedef struct {
 int tfhe_profile_enable(tfhe_cloud_key *ck, int on);
 int tfhe_profile_read(tfhe_cloud_key *ck, tfhe_profile *out, int reset);
 
-/* The schedule a layer call runs, as a host-side function: sort a lowered circuit by depth and
- * rename its wires to slots of a pool in which a slot is reused once the last depth that reads
+/* A schedule of a lowered circuit with a wire pool, as a host-side function: sort the records by
+ * depth (their earliest level) and rename its wires to slots of a pool in which a slot is reused once the last depth that reads
  * its wire has run.  Wires 0 .. n_fixed-1 (inputs and the two constants) and the wires referenced
  * by outs keep their slots; outs (HOST, nouts entries) is rewritten in place to slot numbers.
  * *planned (release with tfhe_free_buffer) receives the ngates records in depth order with slot
  * numbers: evaluating them in that order, depth by depth, on a pool of *pool_wires slots gives
- * the circuit's outputs.  Same validation and errors as tfhe_gate_stream. */
+ * the circuit's outputs.  Same validation and errors as tfhe_gate_stream.  Layer calls plan
+ * their pool the same way, but first move gates that can wait into later levels where that fills
+ * launches: their pool (tfhe_last_layer_stats) can come out larger or smaller, by up to a
+ * quarter for a layer of a few thousand gates, by a few per cent for large ones. */
 int tfhe_plan_wire_pool(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, size_t n_fixed,
                         tfhe_out_ref *outs, size_t nouts, tfhe_gate_rec **planned, size_t *pool_wires,
                         size_t *depths);

@@ -15,6 +15,7 @@
 #include "common.h"
 #include "dft8.h"
 #include "kernels.h"
+#include "schedule.h"
 
 namespace tfhe {
 
@@ -188,16 +189,6 @@ int run_batch(tfhe_cloud_key *ck, const tfhe_gate_rec *d_recs, int uniform_op, c
 
 }  // namespace
 
-namespace {
-
-// Validation and ASAP levels of a topologically ordered gate list.
-struct Levels {
-    std::vector<int32_t> level;     // per record
-    std::vector<size_t> start;      // records of level l occupy sorted positions [start[l], start[l+1])
-    int32_t max_level = 0;
-    bool any_mux = false;
-};
-
 int levelize(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, Levels &lv) {
     if (ngates > (size_t)INT32_MAX || nwires > (size_t)INT32_MAX)
         return set_error(TFHE_E_SIZE, "too many gates or wires");
@@ -262,7 +253,6 @@ int levelize(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, Levels &l
 // gates (estimated 4 to 15 % less time than earliest levels; 1.0 and 1.2 within 1 %).  The number of levels
 // stays.  Circuits whose levels average more than kRounds rounds have little to gain and keep theirs.
 constexpr double kWorth = 1.1;
-constexpr size_t kRounds = 16;
 
 void fill_levels(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, size_t cus, Levels &lv) {
     const size_t round = kRoundPerCu * cus, depth = (size_t)lv.max_level;
@@ -344,6 +334,8 @@ void fill_levels(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, size_
     for (size_t g = 0; g < ngates; ++g) ++lv.start[(size_t)lv.level[g] + 1];
     for (int32_t l = 1; l <= end; ++l) lv.start[l] += lv.start[l - 1];
 }
+
+namespace {
 
 // The depth-sorted records already sit in the pinned staging buffer: upload them and run one
 // kernel pair per depth (in chunks) on the stream.  The upload is ordered on the stream and the

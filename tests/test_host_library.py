@@ -376,7 +376,7 @@ def _asap_levels(gates, nwires):
 @pytest.mark.parametrize("flags", [T.LOWER_DEFAULT, T.LOWER_MUX_COMPARATOR, T.LOWER_PLUS_ONE | T.LOWER_SHARE_GATES,
                                    T.LOWER_SORTING_NETWORK])
 def test_wire_pool_plan_keeps_the_circuit_and_never_reuses_a_live_slot(flags):
-    """tfhe_plan_wire_pool (the schedule of the layer calls): run depth by depth -- all reads of a
+    """tfhe_plan_wire_pool (earliest levels on a wire pool): run depth by depth -- all reads of a
     depth before its writes, as the two kernels of a launch do -- the renamed records give the
     outputs of the circuit as lowered; no slot written at a depth is read at that depth; fixed
     wires and outputs keep their slots; the pool is smaller than one slot per wire."""
