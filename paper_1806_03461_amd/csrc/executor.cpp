@@ -11,6 +11,7 @@
 #include <cstring>
 #include <functional>
 #include <new>
+#include <set>
 
 #include "common.h"
 #include "dft8.h"
@@ -289,10 +290,16 @@ void fill_levels(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, size_
     }
 
     std::vector<std::vector<int32_t>> ready((size_t)end);      // by latest level
+    std::set<int32_t> waiting;                         // latest levels with ready gates: a deep circuit has many without
     size_t nready = 0;
     auto weight = [&](int32_t g) { return gates[g].op == TFHE_MUX ? (size_t)2 : (size_t)1; };
+    auto add = [&](int32_t g) {
+        if (ready[late[g]].empty()) waiting.insert(late[g]);
+        ready[late[g]].push_back(g);
+        nready += weight(g);
+    };
     for (size_t g = 0; g < ngates; ++g)
-        if (gates[g].op != TFHE_MUX_ELSE && !missing[g]) { ready[late[g]].push_back((int32_t)g); nready += weight((int32_t)g); }
+        if (gates[g].op != TFHE_MUX_ELSE && !missing[g]) add((int32_t)g);
     const double full = kWorth * rotation_ms(round, cus) / (double)round;
     std::vector<int32_t> now;
     for (int32_t l = 1; l < end; ++l) {
@@ -309,7 +316,8 @@ void fill_levels(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, size_
         for (size_t w = (must / cus + 1) * cus; w < nready; w += cus) offer(w);
         now.clear();
         size_t taken = 0;
-        for (int32_t v = l; v < end && taken < width; ++v) {
+        while (taken < width && !waiting.empty()) {
+            const int32_t v = *waiting.begin();        // none before l: those gates have run
             size_t k = 0;
             while (k < ready[v].size() && (v == l || taken + weight(ready[v][k]) <= width)) {
                 taken += weight(ready[v][k]);
@@ -318,6 +326,7 @@ void fill_levels(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, size_
             const bool part = k < ready[v].size();
             ready[v].erase(ready[v].begin(), ready[v].begin() + (std::ptrdiff_t)k);
             if (part) break;
+            waiting.erase(waiting.begin());
         }
         nready -= taken;
         for (int32_t g : now) {
@@ -326,7 +335,7 @@ void fill_levels(const tfhe_gate_rec *gates, size_t ngates, size_t nwires, size_
             const int32_t w = gates[g].out;
             for (uint32_t k = at[w]; k < at[w + 1]; ++k) {
                 const int32_t user = readers[k];
-                if (--missing[user] == 0) { ready[late[user]].push_back(user); nready += weight(user); }
+                if (--missing[user] == 0) add(user);
             }
         }
     }
