@@ -521,8 +521,10 @@ constexpr int kKeyRing = 4;        // key batches (one output at one frequency: 
 struct WaveLds {
     double2 buf[kWaveGates][8 * kRowStride];
     uint32_t acc[kWaveGates][2][kN + kMirror];     // as in GateLds
-    double2 fwd2[64], inv2[64], inv1[512];         // constants of dft8.h, in the order of the table in memory
+    // lane-dependent constants of dft8.h, a piece of the table in memory: forward pass 2, inverse passes 2 and 1
+    double2 constants[kFwd3 - kFwd2];
 };
+static_assert(kFwd2 < kInv2 && kInv2 < kInv1 && kInv1 < kFwd3, "the table's order");
 static_assert(2 * sizeof(WaveLds) <= 160 * 1024, "two workgroups share a CU's LDS");
 
 // Scheduling patterns of the instructions between two region ends: eight stores to LDS, then eight
@@ -544,7 +546,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
     uint32_t (&acc)[2][kN + kMirror] = my.acc[wv];
     double2 *const buf = my.buf[wv];
     double2 *const mine = buf + (L >> 3) * kRowStride;          // passes 2, 3: lane = 8 k0 + (j0 or k1)
-    for (int e = threadIdx.x; e < 64 + 64 + 512; e += 64 * kWaveGates) my.fwd2[e] = a.tables[kFwd2 + e];
+    for (int e = threadIdx.x; e < kFwd3 - kFwd2; e += 64 * kWaveGates) my.constants[e] = a.tables[kFwd2 + e];
     Shift8 f3;
     f3.h4 = a.tables[kFwd3 + L];
     f3.h2 = a.tables[kFwd3 + 64 + L];
@@ -696,7 +698,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         {
             double2 p[8];
             read_component(0);
-            load_twiddles(my.fwd2, 8, L >> 3, p);
+            load_twiddles(my.constants, 8, L >> 3, p);
             const Twiddle8 w2 = unpack_twiddles(p);
             const Twiddle8 w1 = pass1_twiddles(uniform_constants(a.tables));
 
@@ -775,9 +777,9 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         __builtin_amdgcn_s_setprio(2);
         {
             double2 p[8];
-            load_twiddles(my.inv2, 8, L & 7, p);
+            load_twiddles(my.constants + (kInv2 - kFwd2), 8, L & 7, p);
             const Twiddle8 w2 = unpack_twiddles(p);
-            load_twiddles(my.inv1, 64, L, p);
+            load_twiddles(my.constants + (kInv1 - kFwd2), 64, L, p);
             const Twiddle8 w1 = unpack_twiddles(p);
             const double2 w10 = p[7];
             double tan_m[8], cos_m[8];
