@@ -1,5 +1,7 @@
 // Four 512-point complex FFTs held by the four 64-lane wavefronts of a workgroup, 8 points per
-// lane, used to multiply polynomials of Z[X]/(X^1024+1) exactly.
+// lane, used to multiply polynomials of Z[X]/(X^1024+1) exactly: the forward transform that the bootstrapping
+// key goes through, and the layout, buffers and lane exchanges that the four-wave blind rotations share with it
+// (their transforms, in either direction, are those of dft8.h).
 //
 // A real polynomial a of degree < N = 1024 is folded to z_j = (a_j + i a_{j+512}) psi^j,
 // psi = exp(i pi / N) (the twist is applied inside pass 1); its 512-point DFT (kernel
@@ -24,16 +26,16 @@
 //   gather  two register <-> lane-bit exchanges (lane bits 5 and 4, which hold r, against bits 2
 //           and 1 of k2): register 2 r + q of lane (k2 >> 1, k0 & 1, k1) is polynomial r at
 //           frequency k0 + 8 k1 + 64 k2, q = k2 & 1
-// The inverse runs the same steps backwards with conjugate twiddles (scatter, pass 3, T2, pass 2
-// into the rows, barrier, pass 1 by wave o for polynomial o), so it consumes exactly the order
-// the forward produces and no reordering is ever needed.  Spectra are stored and multiplied in
+// An inverse runs the same steps backwards (scatter, pass 3, T2, pass 2 into the rows, barrier,
+// pass 1 by wave o for polynomial o), so it consumes exactly the order the forward produces and no
+// reordering is ever needed.  Spectra are stored and multiplied in
 // "slot" order: slot = 256 q + 64 w + lane.
 //
 // Rows 2w, 2w+1 of the four buffers are wave w's own between the two barriers (it is their only
 // reader after the first and their only writer before the second), so T2 needs only wave-level
 // fences.  Every function is a per-lane step; between a *_store and the matching load all lanes
 // involved must have executed the store (the caller places the fence or barrier).  The same code
-// compiles for the host, where a test drives the 256 lanes one after the other.
+// compiles for the host, where tests drive the 256 lanes one after the other.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -54,9 +56,6 @@ FFT_HD double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y +
 FFT_HD double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 FFT_HD double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-FFT_HD double2 cmulc(double2 a, double2 b) {   // a * conj(b)
-    return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
 
 // y[k] = sum_m x[m] w^(m k), w = exp(+2 pi i / 8) (INV: exp(-2 pi i / 8)), in place.
@@ -157,29 +156,6 @@ FFT_HD void fwd_pass3(double2 (&x)[8], const double2 *row, int L) {
     radix8<false>(x);
 }
 
-// ---- inverse (unnormalised: 512 times the folded, untwisted points come out) -----------
-FFT_HD void inv_pass3_store(double2 (&x)[8], const Lane &ln, double2 *row, int L) {
-    radix8<true>(x);
-    const int base = (L & 7) * kGrpStride;
-    row[base] = x[0];
-    for (int j0 = 1; j0 < 8; ++j0) row[base + j0] = cmulc(x[j0], ln.tw2[j0]);
-}
-FFT_HD void inv_pass2(double2 (&x)[8], const double2 *row, int L) {
-    const int j0 = L & 7;
-    for (int k = 0; k < 8; ++k) x[k] = row[k * kGrpStride + j0];
-    radix8<true>(x);
-}
-FFT_HD void inv_pass2_store(const double2 (&x)[8], double2 *row, int L) {
-    const int j0 = L & 7;
-    for (int j1 = 0; j1 < 8; ++j1) row[j0 + 8 * j1] = x[j1];
-}
-// wave o, from its polynomial's buffer
-FFT_HD void inv_pass1(double2 (&x)[8], const Lane &ln, const double2 *poly, int L) {
-    for (int k = 0; k < 8; ++k) x[k] = cmulc(poly[k * kRowStride + L], ln.tw1[k]);
-    radix8<true>(x);
-    for (int m = 1; m < 8; ++m) x[m] = cmulc(x[m], twist_const(m));
-}
-
 // ---- gather / scatter: registers <-> lane bits 5 and 4 -----------------------------------
 // One exchange step on a pair of 32-bit registers (a, b) of all lanes, lane bit `bit` (5 or 4):
 // afterwards a holds, in lanes with the bit clear, what it held, and in lanes with the bit set,
@@ -221,36 +197,5 @@ __device__ __forceinline__ void scatter_rows(double2 (&x)[8]) {
     for (int k = 0; k < 4; ++k) lane_bit_swap<5>(x[k], x[k + 4]);
 }
 #endif
-
-// The same exchanges written out over the registers of a whole wave (x[lane][register]), for
-// host code that drives the lanes one after the other.
-inline void gather_rows_wave(double2 (*x)[8]) {
-    for (int bit = 5; bit >= 4; --bit) {
-        const int d = 1 << bit, rs = bit == 5 ? 4 : 2;      // lane distance, register distance
-        for (int L = 0; L < 64; ++L) {
-            if (L & d) continue;
-            for (int k = 0; k < 8; ++k) {
-                if (k & rs) continue;
-                const double2 t = x[L][k + rs];
-                x[L][k + rs] = x[L + d][k];
-                x[L + d][k] = t;
-            }
-        }
-    }
-}
-inline void scatter_rows_wave(double2 (*x)[8]) {
-    for (int bit = 4; bit <= 5; ++bit) {
-        const int d = 1 << bit, rs = bit == 5 ? 4 : 2;
-        for (int L = 0; L < 64; ++L) {
-            if (L & d) continue;
-            for (int k = 0; k < 8; ++k) {
-                if (k & rs) continue;
-                const double2 t = x[L][k + rs];
-                x[L][k + rs] = x[L + d][k];
-                x[L + d][k] = t;
-            }
-        }
-    }
-}
 
 }  // namespace fft512

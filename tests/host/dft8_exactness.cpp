@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../paper_1806_03461_amd/csrc/dft8.h"
+#include "fft512_inverse.h"
 
 using namespace fft512;
 

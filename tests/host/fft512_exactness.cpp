@@ -1,6 +1,6 @@
 // Host run of the four-wave transform of csrc/fft512.h: the 256 lanes of a workgroup are driven
-// one after the other through exactly the per-lane steps the kernels execute (forward, gather,
-// products with a transformed key, scatter, inverse), and the rounded results are compared with
+// one after the other through the per-lane steps of the key's transform (forward, gather), products with a
+// transformed key, and the inverse steps of fft512_inverse.h, and the rounded results are compared with
 // the exact integer negacyclic products  sum_r digit_r * limb_{r,o}  mod X^1024 + 1  computed
 // with 64-bit integers.  Operands: random ones and the extremes of the ranges the blind rotation
 // feeds (digits in [-512, 511], 16-bit key limbs in [-32768, 32767]), with sign patterns that
@@ -12,7 +12,7 @@
 #include <cstdlib>
 #include <vector>
 
-#include "../../paper_1806_03461_amd/csrc/fft512.h"
+#include "fft512_inverse.h"
 
 using namespace fft512;
 

@@ -1,6 +1,6 @@
-"""CPU run of the transform header the blind-rotation kernel is built from (csrc/fft512.h): the
-host program tests/host/fft512_exactness.cpp drives the 256 lanes of a workgroup one after the other
-through the kernel's own per-lane steps and compares the rounded products with exact 64-bit integer
+"""CPU run of the transform that the key goes through (csrc/fft512.h): the host program
+tests/host/fft512_exactness.cpp drives the 256 lanes of a workgroup one after the other through the
+kernel's own per-lane steps, forward, and through the matching inverse, and compares the rounded products with exact 64-bit integer
 negacyclic convolutions, on random operands and on operands at the ends of their ranges arranged so
 that the 4,096 terms of one coefficient add coherently (|sum| = 2^36)."""
 import os
