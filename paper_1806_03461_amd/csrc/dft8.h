@@ -38,8 +38,6 @@ struct Twiddle8 {
 };
 
 FFT_HD double2 cturn(double2 a, double t) { return make_double2(fma(-t, a.y, a.x), fma(t, a.x, a.y)); }
-FFT_HD double2 cmadd(double2 a, double s, double2 b) { return make_double2(fma(s, b.x, a.x), fma(s, b.y, a.y)); }      // a + s b
-FFT_HD double2 cmaddi(double2 a, double s, double2 b) { return make_double2(fma(-s, b.y, a.x), fma(s, b.x, a.y)); }    // a + i s b
 
 // The transforms hand out their results one by one, emit(k, y[k]): the four even ones, then -- after
 // between() -- the four odd ones, whose half of the additions is still to come.  A caller that stores them to
@@ -123,41 +121,6 @@ FFT_HD void dft8_shifted(double2 (&x)[8], const Shift8 &w, Emit &&emit, Between 
     emit(7, x[7]);
 }
 
-// no twiddle: radix8 of fft512.h
-template <bool INV, class Emit, class Between>
-FFT_HD void dft8_plain(double2 (&x)[8], Emit &&emit, Between &&between) {
-    const double c = 0.70710678118654752440;
-    for (int j = 0; j < 4; ++j) {
-        const double2 p = x[j], q = x[j + 4];
-        x[j] = cadd(p, q);
-        x[j + 4] = csub(p, q);
-    }
-    {
-        const double2 c0 = cadd(x[0], x[2]), c1 = csub(x[0], x[2]), c2 = cadd(x[1], x[3]), d = csub(x[1], x[3]);
-        const double2 c3 = INV ? make_double2(d.y, -d.x) : make_double2(-d.y, d.x);
-        emit(0, cadd(c0, c2));
-        emit(4, csub(c0, c2));
-        emit(2, cadd(c1, c3));
-        emit(6, csub(c1, c3));
-    }
-    between();
-    {
-        const double2 a4 = x[4], a5 = x[5], a6 = x[6], a7 = x[7];
-        const double2 s5 = INV ? make_double2(a5.x + a5.y, a5.y - a5.x) : make_double2(a5.x - a5.y, a5.x + a5.y);
-        const double2 s7 = INV ? make_double2(a7.y - a7.x, -a7.x - a7.y) : make_double2(-a7.x - a7.y, a7.x - a7.y);
-        const double2 b6 = INV ? make_double2(a6.y, -a6.x) : make_double2(-a6.y, a6.x);
-        const double2 c0 = cadd(a4, b6), c1 = csub(a4, b6), t = cadd(s5, s7), u = csub(s5, s7);
-        const double ci = INV ? -c : c;
-        emit(1, cmadd(c0, c, t));
-        emit(5, cmadd(c0, -c, t));
-        emit(3, cmaddi(c1, ci, u));
-        emit(7, cmaddi(c1, -ci, u));
-    }
-}
-
-struct Nothing {
-    FFT_HD void operator()() const {}
-};
 template <bool INV>
 FFT_HD void dft8_twiddled(double2 (&x)[8], const Twiddle8 &w) {
     double2 y[8];

@@ -58,47 +58,52 @@ FFT_HD double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-// y[k] = sum_m x[m] w^(m k), w = exp(+2 pi i / 8) (INV: exp(-2 pi i / 8)), in place.
-// The odd branch needs a5 w and a7 w^3 with w = (1 + i) / sqrt 2: the factor 1 / sqrt 2 is not
-// applied to them but folded into the fused multiply-adds of the last stage (16 operations for
-// the four odd outputs instead of 20).
+FFT_HD double2 cmadd(double2 a, double s, double2 b) { return make_double2(fma(s, b.x, a.x), fma(s, b.y, a.y)); }      // a + s b
+FFT_HD double2 cmaddi(double2 a, double s, double2 b) { return make_double2(fma(-s, b.y, a.x), fma(s, b.x, a.y)); }    // a + i s b
+
+struct Nothing {
+    FFT_HD void operator()() const {}
+};
+
+// y[k] = sum_m x[m] w^(m k), w = exp(+2 pi i / 8) (INV: exp(-2 pi i / 8)), handed out one by one as emit(k, y[k]): the four
+// even ones, then, after between(), the four odd ones.  The odd branch needs a5 w and a7 w^3 with w = (1 + i) / sqrt 2:
+// the factor 1 / sqrt 2 is not applied to them but folded into the fused multiply-adds of the last stage (16
+// operations for the four odd outputs instead of 20).  The version without emit leaves the results in x.
+template <bool INV, class Emit, class Between>
+FFT_HD void radix8(double2 (&x)[8], Emit &&emit, Between &&between) {
+    const double c = 0.70710678118654752440;
+    for (int j = 0; j < 4; ++j) {
+        const double2 p = x[j], q = x[j + 4];
+        x[j] = cadd(p, q);
+        x[j + 4] = csub(p, q);
+    }
+    {
+        const double2 c0 = cadd(x[0], x[2]), c1 = csub(x[0], x[2]), c2 = cadd(x[1], x[3]), d = csub(x[1], x[3]);
+        const double2 c3 = INV ? make_double2(d.y, -d.x) : make_double2(-d.y, d.x);
+        emit(0, cadd(c0, c2));
+        emit(4, csub(c0, c2));
+        emit(2, cadd(c1, c3));
+        emit(6, csub(c1, c3));
+    }
+    between();
+    {
+        const double2 a4 = x[4], a5 = x[5], a6 = x[6], a7 = x[7];
+        const double2 s5 = INV ? make_double2(a5.x + a5.y, a5.y - a5.x) : make_double2(a5.x - a5.y, a5.x + a5.y);
+        const double2 s7 = INV ? make_double2(a7.y - a7.x, -a7.x - a7.y) : make_double2(-a7.x - a7.y, a7.x - a7.y);
+        const double2 b6 = INV ? make_double2(a6.y, -a6.x) : make_double2(-a6.y, a6.x);
+        const double2 c0 = cadd(a4, b6), c1 = csub(a4, b6), t = cadd(s5, s7), u = csub(s5, s7);
+        const double ci = INV ? -c : c;
+        emit(1, cmadd(c0, c, t));
+        emit(5, cmadd(c0, -c, t));
+        emit(3, cmaddi(c1, ci, u));
+        emit(7, cmaddi(c1, -ci, u));
+    }
+}
 template <bool INV>
 FFT_HD void radix8(double2 (&x)[8]) {
-    const double c = 0.70710678118654752440;
-    double2 a0 = cadd(x[0], x[4]), a4 = csub(x[0], x[4]);
-    double2 a1 = cadd(x[1], x[5]), a5 = csub(x[1], x[5]);
-    double2 a2 = cadd(x[2], x[6]), a6 = csub(x[2], x[6]);
-    double2 a3 = cadd(x[3], x[7]), a7 = csub(x[3], x[7]);
-    // even outputs: a 4-point DFT with w4 = +-i
-    {
-        double2 c0 = cadd(a0, a2), c1 = csub(a0, a2), c2 = cadd(a1, a3), d = csub(a1, a3);
-        double2 c3 = INV ? make_double2(d.y, -d.x) : make_double2(-d.y, d.x);
-        x[0] = cadd(c0, c2); x[4] = csub(c0, c2); x[2] = cadd(c1, c3); x[6] = csub(c1, c3);
-    }
-    // odd outputs: s5 = sqrt 2 * a5 w, b6 = a6 w^2, s7 = sqrt 2 * a7 w^3 (conjugate w for INV)
-    double2 s5, b6, s7;
-    if (!INV) {
-        s5 = make_double2(a5.x - a5.y, a5.x + a5.y);
-        b6 = make_double2(-a6.y, a6.x);
-        s7 = make_double2(-a7.x - a7.y, a7.x - a7.y);
-    } else {
-        s5 = make_double2(a5.x + a5.y, a5.y - a5.x);
-        b6 = make_double2(a6.y, -a6.x);
-        s7 = make_double2(a7.y - a7.x, -a7.x - a7.y);
-    }
-    {
-        const double2 c0 = cadd(a4, b6), c1 = csub(a4, b6), t = cadd(s5, s7), u = csub(s5, s7);
-        // x1, x5 = c0 +- c t;  x3, x7 = c1 +- c (+-i u)
-        x[1] = make_double2(fma(c, t.x, c0.x), fma(c, t.y, c0.y));
-        x[5] = make_double2(fma(-c, t.x, c0.x), fma(-c, t.y, c0.y));
-        if (!INV) {
-            x[3] = make_double2(fma(-c, u.y, c1.x), fma(c, u.x, c1.y));
-            x[7] = make_double2(fma(c, u.y, c1.x), fma(-c, u.x, c1.y));
-        } else {
-            x[3] = make_double2(fma(c, u.y, c1.x), fma(-c, u.x, c1.y));
-            x[7] = make_double2(fma(-c, u.y, c1.x), fma(c, u.x, c1.y));
-        }
-    }
+    double2 y[8];
+    radix8<INV>(x, [&](int k, double2 v) { y[k] = v; }, Nothing());
+    for (int k = 0; k < 8; ++k) x[k] = y[k];
 }
 
 // psi^(64 m) = exp(i pi m / 16), m = 0..7: the part of the negacyclic twist psi^(L + 64 m) that

@@ -414,7 +414,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
 
         // ---- back: scatter the four output spectra to their lanes, inverse passes 3 and 2 ----
         scatter_rows(y);
-        dft8_plain<true>(y, [&](int k, double2 v) { mine[(L & 7) * kGrpStride + k] = v; }, pause);
+        radix8<true>(y, [&](int k, double2 v) { mine[(L & 7) * kGrpStride + k] = v; }, pause);
         wave_sync();
         load_ahead(next, 1);
 #pragma unroll

@@ -85,7 +85,7 @@ void inverse(Form form, const double2 *X, std::vector<double> &out) {
             if (form == kFft512) inv_pass3_store(y[k1], g_lane[k1], row, k1);
             else if (form == kTable) radix8<true>(y[k1]);
             else { for (int k2 = 0; k2 < 8; ++k2) x[k2] = y[k1][k2];
-                   dft8_plain<true>(x, [&](int k, double2 v) { y[k1][k] = v; }, Nothing()); }
+                   radix8<true>(x, [&](int k, double2 v) { y[k1][k] = v; }, Nothing()); }
         }
         for (int j0 = 0; j0 < 8; ++j0) {
             if (form == kFft512) {

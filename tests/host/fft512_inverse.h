@@ -33,7 +33,7 @@ FFT_HD void inv_pass1(double2 (&x)[8], const Lane &ln, const double2 *poly, int 
     for (int m = 1; m < 8; ++m) x[m] = cmulc(x[m], twist_const(m));
 }
 
-// The same exchanges written out over the registers of a whole wave (x[lane][register]), for
+// gather_rows and scatter_rows written out over the registers of a whole wave (x[lane][register]), for
 // host code that drives the lanes one after the other.
 inline void gather_rows_wave(double2 (*x)[8]) {
     for (int bit = 5; bit >= 4; --bit) {
