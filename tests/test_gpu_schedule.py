@@ -42,6 +42,8 @@ def test_filled_levels_leave_every_wire_unchanged(d, p, flag):
     res = torch.empty((p, 501), dtype=torch.int32, device="cuda")
     T.bnn_dense_encrypted_opts(ck, T.to_device(wires[:d]), d, W, Tt, p, res, 0, getattr(T, flag))
     torch.cuda.synchronize()
+    # filling did move gates: the pool is not the one that earliest levels give
+    assert T.tfhe_last_layer_stats(ck)["pool_wires"] != T.tfhe_plan_wire_pool(gates, nw, d + 2, outs)[2]
     host = T.to_host(by_depth)
     want = np.stack([(host[o["wire"]] if not o["value"] else 0 - host[o["wire"]]) if o["wire"] >= 0 else
                      T.tfhe_trivial(T.default_params(), int(o["value"])) for o in outs])

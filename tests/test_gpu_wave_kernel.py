@@ -60,12 +60,48 @@ def test_small_batches_equal_the_four_wave_kernels():
     """Every batch on the wave kernel, and none: the same bytes."""
     digests = []
     for gates_from in ("1", "1000000000"):
-        env = dict(os.environ, TFHE_WAVE_GATES_FROM=gates_from)
+        env = {k: v for k, v in os.environ.items() if not k.startswith("TFHE_")}
+        env["TFHE_WAVE_GATES_FROM"] = gates_from
         r = subprocess.run([sys.executable, "-c", _SCRIPT, ROOT], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
                            text=True, timeout=200)
         assert r.returncode == 0, r.stdout
         digests.append([l for l in r.stdout.splitlines() if l.startswith("digest")][-1])
     assert digests[0] == digests[1]
+
+
+_EXTREMES = r"""
+import sys
+import torch
+sys.path[:0] = [sys.argv[1], sys.argv[1] + "/tests"]
+import paper_1806_03461_amd as T, workloads
+from oracle import oracle as orc
+import test_gpu_parity as parity
+read = T.tfhe_rounding_margin_read
+def margin(ck):
+    worst = read(ck)
+    print("largest distance from an integer", worst, flush=True)
+    return worst
+T.tfhe_rounding_margin_read = margin
+sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
+parity.test_rotation_amounts_at_every_boundary((T, sk, ck), orc.Keys(orc.default_params(), workloads.KEY_SEED))
+print("boundaries ok", flush=True)
+for pattern in ("all_min", "alternating", "random"):
+    parity.test_extreme_key_limbs_stay_exact((T, sk, ck), orc, pattern)
+    print(pattern, "ok", flush=True)
+"""
+
+
+@pytest.mark.parametrize("kernel,knobs", [("wave", {"TFHE_WAVE_GATES_FROM": "1"}), ("four waves", {"TFHE_LATENCY_BATCH": "0"})],
+                         ids=["wave", "four_waves"])
+def test_extreme_keys_and_rotations_on_the_kernels_of_larger_batches(kernel, knobs, say):
+    """The parity tests with key limbs at the ends of their range and with rotation amounts on every boundary are too
+    small to leave the latency kernel by themselves: the same checks with every launch on the others."""
+    env = {k: v for k, v in os.environ.items() if not k.startswith("TFHE_")}
+    r = subprocess.run([sys.executable, "-c", _EXTREMES, ROOT], env={**env, **knobs}, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                       text=True, timeout=200)
+    assert r.returncode == 0, r.stdout
+    assert r.stdout.count(" ok") == 4 and r.stdout.count("largest distance") == 3, r.stdout
+    say(kernel + ": " + "; ".join(l for l in r.stdout.splitlines() if "distance" in l or l.endswith("ok")))
 
 
 @pytest.mark.parametrize("count", [769, 1024, 1025, 1281, 2047, 2048, 2049, 2900])
