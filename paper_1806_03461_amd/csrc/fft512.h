@@ -161,6 +161,12 @@ FFT_HD void fwd_pass3(double2 (&x)[8], const double2 *row, int L) {
     radix8<false>(x);
 }
 
+// Slots of a spectrum for a wave that holds one whole polynomial, lane 8 k0 + k1, register k2: slot 256 q + 64 w + lane'
+// is frequency k0 = 2 w + (lane' >> 3 & 1), k1 = lane' & 7, k2 = 2 (lane' >> 4) + q, so the lane reads at its own
+// part plus the register's: four runs of 16 consecutive slots per load.
+FFT_HD constexpr int wave_slot_lane(int L) { return (L >> 4) * 64 + (L & 15); }
+FFT_HD constexpr int wave_slot_register(int k2) { return 256 * (k2 & 1) + 16 * (k2 >> 1); }
+
 // ---- gather / scatter: registers <-> lane bits 5 and 4 -----------------------------------
 // One exchange step on a pair of 32-bit registers (a, b) of all lanes, lane bit `bit` (5 or 4):
 // afterwards a holds, in lanes with the bit clear, what it held, and in lanes with the bit set,

@@ -554,10 +554,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
     f3.h1w = a.tables[kFwd3 + 192 + L];
     const __amdgpu_buffer_rsrc_t key_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<double2 *>(a.bk_fft), 0, (int)((size_t)a.n * 16 * kHalf * sizeof(double2)), 0x00020000);
-    // slot 256 q + 64 w + lane' of the key rows is frequency k0 = 2 w + (lane' >> 3 & 1), k1 = lane' & 7,
-    // k2 = 2 (lane' >> 4) + q; here lane = 8 k0 + k1 reads it at its own part (L >> 4) * 64 + L % 16 plus
-    // 256 (k2 & 1) + 16 (k2 >> 1): four runs of 256 consecutive bytes per load
-    const uint32_t voff = (uint32_t)((L >> 4) * 64 + (L & 15)) * (uint32_t)sizeof(double2);
+    const uint32_t voff = (uint32_t)wave_slot_lane(L) * (uint32_t)sizeof(double2);
     double worst = 0.0;
 
     int op = a.uniform_op;
@@ -691,7 +688,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             const int k2 = b >> 2, o = b & 3;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                ring[b % kKeyRing][r] = load_key(key_rsrc, voff, row + (uint32_t)(((r * 4 + o) * kHalf + 256 * (k2 & 1) + 16 * (k2 >> 1)) * sizeof(double2)));
+                ring[b % kKeyRing][r] = load_key(key_rsrc, voff, row + (uint32_t)(((r * 4 + o) * kHalf + wave_slot_register(k2)) * sizeof(double2)));
         };
 
         // ---- forward: four polynomials, the LDS exchanges of one beside the arithmetic of another ----

@@ -3,7 +3,8 @@
 // The key comes, as on the device, from the steps of csrc/fft512.h.  The products
 // sum_r digit_r * limb_{r,o} mod X^1024 + 1 are compared with exact 64-bit integers, and their largest distance
 // from an integer with that of the same products through the transforms of fft512.h, on random operands and on
-// operands at the ends of their ranges.
+// operands at the ends of their ranges.  A second part runs whole steps lane by lane as the two kernels do: the key in slot
+// order, its slots addressed by each kernel's own rule, and the exchanges through LDS and between lanes.
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -156,6 +157,162 @@ void product(const char *name, const Poly (&digit)[4], const Poly (&limb)[4]) {
     printf("\n");
 }
 
+// ---- whole steps, lane by lane ----
+typedef double2 Lanes[4][64][8];        // [wave or polynomial][lane][register]
+Lanes g_x;
+double2 g_key[4][4][kHalf];             // [row][output][slot]
+
+Twiddle8 pass1() {
+    Twiddle8 w;
+    const double *u = uniform();
+    w.t[0] = 0.0;
+    for (int j = 1; j < 8; ++j) w.t[j] = u[j];
+    for (int j = 0; j < 4; ++j) w.rho[j] = u[8 + j];
+    w.sig0 = u[12]; w.sig1 = u[13]; w.tau = u[14]; w.tauh = u[15];
+    return w;
+}
+void fold(const Poly (&p)[4], double scale) {
+    for (int r = 0; r < 4; ++r)
+        for (int L = 0; L < 64; ++L)
+            for (int m = 0; m < 8; ++m)
+                g_x[r][L][m] = make_double2((double)p[r][L + 64 * m] * scale, (double)p[r][L + 64 * m + kHalf] * scale);
+}
+#define LANES for (int L = 0; L < 64; ++L)
+#define REGISTERS for (int k = 0; k < 8; ++k)
+
+// the key as the upload stores it: the steps of fft512.h, four outputs of a row at a time
+void store_key(const Poly (&limb)[4][4]) {
+    for (int r = 0; r < 4; ++r) {
+        fold(limb[r], 1.0 / 512.0);
+        for (int w = 0; w < 4; ++w) LANES fwd_pass1_store(g_x[w][L], g_lane[L], g_buf + w * kPolyStride, L);
+        for (int w = 0; w < 4; ++w) {
+            LANES fwd_pass2_load(g_x[w][L], g_buf + row_of(w, L), L);
+            LANES fwd_pass2_store(g_x[w][L], g_lane[L], g_buf + row_of(w, L), L);
+            LANES fwd_pass3(g_x[w][L], g_buf + row_of(w, L), L);
+            gather_rows_wave(g_x[w]);
+            LANES for (int o = 0; o < 4; ++o)
+                for (int q = 0; q < 2; ++q) g_key[r][o][256 * q + 64 * w + L] = g_x[w][L][2 * o + q];
+        }
+    }
+}
+// inverse pass 1 and the pending cosines of one lane
+void finish(double2 (&x)[8], int L, std::vector<double> &out) {
+    double2 p[8];
+    const double *u = uniform();
+    const Twiddle8 w = packed(kInv1, 64, L, p);
+    x[0] = cmul(x[0], p[7]);
+    dft8_twiddled<true>(x, w);
+    for (int m = 0; m < 8; ++m) {
+        if (m) { x[m] = cturn(x[m], -u[m]); x[m] = make_double2(u[16 + m] * x[m].x, u[16 + m] * x[m].y); }
+        out[L + 64 * m] = x[m].x;
+        out[L + 64 * m + kHalf] = x[m].y;
+    }
+}
+double2 row_times_key(const double2 (&d)[4], int o, int slot) {
+    double2 y = make_double2(0.0, 0.0);
+    for (int r = 0; r < 4; ++r) {
+        const double2 b = g_key[r][o][slot];
+        y = make_double2(fma(-d[r].y, b.y, fma(d[r].x, b.x, y.x)), fma(d[r].y, b.x, fma(d[r].x, b.y, y.y)));
+    }
+    return y;
+}
+
+// four waves per gate: wave r transforms polynomial r in pass 1 and holds rows 2 w, 2 w + 1 of all afterwards
+void step_four_waves(const Poly (&digit)[4], std::vector<double> (&out)[4]) {
+    fold(digit, 1.0);
+    const Twiddle8 w1 = pass1();
+    for (int w = 0; w < 4; ++w) LANES {
+        dft8_twiddled<false>(g_x[w][L], w1);
+        REGISTERS g_buf[w * kPolyStride + k * kRowStride + L] = g_x[w][L][k];
+    }
+    for (int w = 0; w < 4; ++w) {
+        auto mine = [&](int L) { return g_buf + row_of(w, L); };
+        auto k0 = [&](int L) { return 2 * w + (L >> 3 & 1); };
+        double2 (&x)[64][8] = g_x[w];
+        LANES REGISTERS x[L][k] = mine(L)[(L & 7) + 8 * k];
+        LANES dft8_shifted<false>(x[L], shift(kFwd2Shift, 8, k0(L)));
+        LANES REGISTERS mine(L)[k * kGrpStride + (L & 7)] = x[L][k];
+        LANES REGISTERS x[L][k] = mine(L)[(L & 7) * kGrpStride + k];
+        LANES dft8_shifted<false>(x[L], shift(kFwd3, 64, 8 * k0(L) + (L & 7)));
+        gather_rows_wave(x);
+        LANES {
+            double2 y[8];
+            for (int o = 0; o < 4; ++o)
+                for (int q = 0; q < 2; ++q) {
+                    const double2 d[4] = {x[L][q], x[L][2 + q], x[L][4 + q], x[L][6 + q]};
+                    y[2 * o + q] = row_times_key(d, o, 256 * q + 64 * w + L);
+                }
+            REGISTERS x[L][k] = y[k];
+        }
+        scatter_rows_wave(x);
+        LANES radix8<true>(x[L]);
+        LANES REGISTERS mine(L)[(L & 7) * kGrpStride + k] = x[L][k];
+        LANES REGISTERS x[L][k] = mine(L)[k * kGrpStride + (L & 7)];
+        LANES dft8_shifted<true>(x[L], shift(kInv2Shift, 8, L & 7));
+        LANES REGISTERS mine(L)[(L & 7) + 8 * k] = x[L][k];
+    }
+    for (int o = 0; o < 4; ++o) LANES {
+        REGISTERS g_x[o][L][k] = g_buf[o * kPolyStride + k * kRowStride + L];
+        finish(g_x[o][L], L, out[o]);
+    }
+}
+
+// one wave per gate: each polynomial through the wave's one buffer, lane = 8 k0 + (j0 or k1)
+void step_one_wave(const Poly (&digit)[4], std::vector<double> (&out)[4]) {
+    fold(digit, 1.0);
+    const Twiddle8 w1 = pass1();
+    double2 p[8];
+    auto mine = [&](int L) { return g_buf + (L >> 3) * kRowStride; };
+    for (int r = 0; r < 4; ++r) {
+        double2 (&x)[64][8] = g_x[r];
+        LANES { dft8_twiddled<false>(x[L], w1); REGISTERS g_buf[k * kRowStride + L] = x[L][k]; }
+        LANES REGISTERS x[L][k] = mine(L)[(L & 7) + 8 * k];
+        LANES dft8_twiddled<false>(x[L], packed(kFwd2, 8, L >> 3, p));
+        LANES REGISTERS mine(L)[k * kGrpStride + (L & 7)] = x[L][k];
+        LANES REGISTERS x[L][k] = mine(L)[(L & 7) * kGrpStride + k];
+        LANES dft8_shifted<false>(x[L], shift(kFwd3, 64, L));
+    }
+    LANES REGISTERS {
+        const double2 d[4] = {g_x[0][L][k], g_x[1][L][k], g_x[2][L][k], g_x[3][L][k]};
+        for (int o = 0; o < 4; ++o) g_x[o][L][k] = row_times_key(d, o, wave_slot_lane(L) + wave_slot_register(k));
+    }
+    for (int o = 0; o < 4; ++o) {
+        double2 (&x)[64][8] = g_x[o];
+        LANES radix8<true>(x[L]);
+        LANES REGISTERS mine(L)[(L & 7) * kGrpStride + k] = x[L][k];
+        LANES REGISTERS x[L][k] = mine(L)[k * kGrpStride + (L & 7)];
+        LANES dft8_twiddled<true>(x[L], packed(kInv2, 8, L & 7, p));
+        LANES REGISTERS mine(L)[(L & 7) + 8 * k] = x[L][k];
+        LANES { REGISTERS x[L][k] = g_buf[k * kRowStride + L]; finish(x[L], L, out[o]); }
+    }
+}
+
+// both kernels' steps against exact integers; returns the number of wrong coefficients
+long steps(const Poly (&digit)[4], const Poly (&limb)[4][4], double &worst) {
+    store_key(limb);
+    std::vector<double> out[2][4];
+    for (auto &kernel : out) for (auto &o : kernel) o.assign(kN, 0.0);
+    step_four_waves(digit, out[0]);
+    step_one_wave(digit, out[1]);
+    long wrong = 0;
+    for (int o = 0; o < 4; ++o) {
+        Poly want(kN, 0);
+        for (int r = 0; r < 4; ++r)
+            for (int i = 0; i < kN; ++i)
+                for (int j = 0; j < kN; ++j) {
+                    const int64_t v = digit[r][i] * limb[r][o][j];
+                    if (i + j < kN) want[i + j] += v;
+                    else want[i + j - kN] -= v;
+                }
+        for (auto &kernel : out)
+            for (int j = 0; j < kN; ++j) {
+                wrong += (int64_t)nearbyint(kernel[o][j]) != want[j];
+                worst = fmax(worst, fabs(kernel[o][j] - (double)want[j]));
+            }
+    }
+    return wrong;
+}
+
 uint64_t g_state = 0x9E3779B97F4A7C15ull;
 uint32_t next_u32() {          // xorshift64*
     g_state ^= g_state >> 12; g_state ^= g_state << 25; g_state ^= g_state >> 27;
@@ -195,6 +352,23 @@ int main() {
     product("alternating extremes", digit, limb);
     fill([](int r, int j) { return j == 301 * (r + 1) % kN ? 511 : 0; }, random_limb);
     product("monomial digits", digit, limb);
+    {
+        Poly rows[4][4];
+        double worst = 0.0;
+        long wrong = 0;
+        for (int rep = 0; rep < 4; ++rep) {
+            fill(random_digit, random_limb);
+            for (int r = 0; r < 4; ++r)
+                for (int o = 0; o < 4; ++o) {
+                    rows[r][o].assign(kN, 0);
+                    for (int j = 0; j < kN; ++j) rows[r][o][j] = rep == 3 ? (next_u32() & 1 ? 32767 : -32768) : random_limb(r, j);
+                }
+            if (rep == 2) fill([](int r, int j) { return j == 301 * (r + 1) % kN ? 511 : 0; }, random_limb);
+            wrong += steps(digit, rows, worst);
+        }
+        printf("whole steps: wrong %ld largest distance %.3g\n", wrong, worst);
+        g_wrong += wrong;
+    }
     printf("dft8 exactness: wrong %ld largest distance fft512 %.3g table %.3g shifted %.3g\n", g_wrong, g_worst[kFft512],
            g_worst[kTable], g_worst[kShifted]);
     return g_wrong != 0;

@@ -1,6 +1,7 @@
 """CPU run of the transforms of csrc/dft8.h (tests/host/dft8_exactness.cpp), in the form of either blind rotation, on
 random operands and on the ends of their ranges: the rounded products equal exact 64-bit integer ones, and no
-value is further from its integer than the bound derived for the transforms of fft512.h."""
+value is further from its integer than the bound derived for the transforms of fft512.h; and of whole steps
+lane by lane, with the key in slot order and each kernel's own exchanges and slot addresses."""
 import os
 import re
 import shutil
@@ -24,5 +25,7 @@ def test_transforms_with_pending_cosines_are_exact_on_the_host(tmp_path):
     assert r.returncode == 0, r.stdout
     m = re.search(r"wrong 0 largest distance fft512 (\S+) table (\S+) shifted (\S+)", r.stdout)
     assert m, r.stdout
+    steps = re.search(r"whole steps: wrong 0 largest distance (\S+)", r.stdout)
+    assert steps and float(steps.group(1)) < 2 ** -10.5, r.stdout
     # the worst case is bounded by about 2^-10.5 (10 u log2(512) times the operands' norms); a wrong rounding needs 0.5
     assert max(float(v) for v in m.groups()) < 2 ** -10.5, r.stdout
