@@ -5,8 +5,8 @@ configuration 3): host lowering of the layer to its gate circuit, depth-sorted b
 gate's blind rotation and key switch on the GPU, with keys and input ciphertexts already resident
 in HBM.  The headline value is bootstrapped gates per second over the timed steps; ms_per_step is
 the layer latency (mean; median and minimum over the steps are reported beside it).  The line also
-carries the roofline of the dominant kernel (blind rotation, measured with HIP events on the stream
-it runs on, against the published FP64 vector peak and against an FMA loop timed on this device),
+carries the roofline of the dominant work (the blind rotation of a batch, one to three kernel launches,
+measured with HIP events on the stream it runs on, against the published FP64 vector peak and against an FMA loop timed on this device),
 the key switch's rates, and the CPU oracle timed on a bounded sample of the same gate stream.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu]
@@ -266,15 +266,16 @@ def main():
             got = (got.reshape(-1, ob).astype(np.int64) << np.arange(ob)).sum(axis=1)
     mismatches = int((got != expect).sum())
 
-    # ---- roofline of the dominant kernel: algorithmic flops of the gates of one launch over the
-    # average launch duration, from HIP events recorded around every launch on the call's stream ----
-    br_launches = max(1, prof["blind_rotate_launches"])
-    br_avg_ms = prof["blind_rotate_ms"] / br_launches
-    gates_per_launch = prof["gates"] / br_launches          # blind rotations per launch
+    # ---- roofline of the dominant work: algorithmic flops of the gates of one batch over the average
+    # duration of its blind rotation, from HIP events recorded around every batch on the call's stream.  A batch is
+    # one to three launches: its whole rounds on the wave kernel, its remainder on the four-wave kernels. ----
+    br_batches = max(1, prof["blind_rotate_launches"])
+    br_avg_ms = prof["blind_rotate_ms"] / br_batches
+    gates_per_batch = prof["gates"] / br_batches            # blind rotations per batch
     flops_per_gate = FLOPS_PER_STEP * P.n
-    achieved = flops_per_gate * gates_per_launch / (br_avg_ms * 1e-3) / 1e12 if br_avg_ms > 0 else 0.0
+    achieved = flops_per_gate * gates_per_batch / (br_avg_ms * 1e-3) / 1e12 if br_avg_ms > 0 else 0.0
     measured_peak = T.tfhe_measure_fp64_peak(ck)
-    # HBM bytes per launch of that kernel, from the committed rocprofv3 counter summary (if one
+    # HBM bytes per batch, from the committed rocprofv3 counter summary (if one
     # exists for this workload); the counters cannot be read from inside the process
     traffic, hbm = None, None
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic.json")
@@ -282,8 +283,8 @@ def main():
         entry = json.load(open(tpath)).get(args.workload, {})
         traffic = entry.get("blind_rotate_bytes_per_launch")
         if traffic and entry.get("gates_per_launch") and br_avg_ms > 0:
-            # the counters were read on another run: scale to this run's launch size
-            scaled = traffic * gates_per_launch / entry["gates_per_launch"]
+            # the counters were read on another run: scale to this run's batch size
+            scaled = traffic * gates_per_batch / entry["gates_per_launch"]
             gbps = scaled / (br_avg_ms * 1e-3) / 1e9
             hbm = {"achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                    "frac": round(gbps / HBM_PEAK_GBPS, 4), "bytes_per_gate": round(traffic / entry["gates_per_launch"]),
@@ -291,20 +292,21 @@ def main():
                    "source": entry.get("source")}
     roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP64_VECTOR_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / FP64_VECTOR_PEAK_TFLOPS, 4),
-                "traffic": traffic, "kernel": "blind_rotate_wave_kernel",
-                "avg_launch_ms": round(br_avg_ms, 4), "gates_per_launch": round(gates_per_launch, 1),
+                "traffic": traffic, "kernel": "blind rotation of a batch (blind_rotate_wave_kernel for whole rounds of 8 gates "
+                "per CU and remainders above 5, blind_rotate_kernel and blind_rotate_latency_kernel for smaller ones)",
+                "avg_batch_ms": round(br_avg_ms, 4), "gates_per_batch": round(gates_per_batch, 1),
                 "flops_per_gate": flops_per_gate,
                 "peak_measured": round(measured_peak, 2),
                 "frac_of_measured": round(achieved / measured_peak, 4) if measured_peak > 0 else None,
                 "hbm": hbm,
                 "kernel_ms": {"blind_rotate": round(prof["blind_rotate_ms"], 2),
                               "key_switch": round(prof["key_switch_ms"], 2)}}
-    ks_launches = max(1, prof["key_switch_launches"])
-    ks_avg_ms = prof["key_switch_ms"] / ks_launches
+    ks_batches = max(1, prof["key_switch_launches"])
+    ks_avg_ms = prof["key_switch_ms"] / ks_batches
     key_switch = None
     if ks_avg_ms > 0:
-        per_s = prof["gates"] / ks_launches / (ks_avg_ms * 1e-3)
-        key_switch = {"kernel": "key_switch_mfma_kernel", "avg_launch_ms": round(ks_avg_ms, 4),
+        per_s = prof["gates"] / ks_batches / (ks_avg_ms * 1e-3)
+        key_switch = {"kernel": "zero_outputs_kernel + key_switch_mfma_kernel", "avg_batch_ms": round(ks_avg_ms, 4),
                       "algorithmic_ops_per_gate": KS_ALGORITHMIC_OPS,
                       "algorithmic_Tops": round(per_s * KS_ALGORITHMIC_OPS / 1e12, 3),
                       "dense_equivalent_Pops": round(per_s * KS_DENSE_OPS / 1e15, 3),

@@ -268,10 +268,12 @@ int bnn_conv_encrypted(tfhe_cloud_key *ck, const uint32_t *x, int C, int H, int 
 
 /* ---- measurement helpers ---------------------------------------------------------- */
 
-/* Kernel-time accounting of server-side calls on a cloud key: when enabled, every blind
- * rotation and key-switch launch is bracketed by HIP events on the call's stream.
+/* Kernel-time accounting of server-side calls on a cloud key: when enabled, the blind rotation
+ * and the key switch of every batch (a level of a circuit or a batched call, in chunks of 262,144
+ * items) are bracketed by HIP events on the call's stream.  A batch's blind rotation is one to three
+ * kernel launches, its key switch two; blind_rotate_launches and key_switch_launches count batches.
  * tfhe_profile_read synchronises the stream's events and returns accumulated milliseconds
- * and launch counts since the last reset.  Recording never waits for the device. */
+ * and counts since the last reset.  Recording never waits for the device. */
 typedef struct {
     double blind_rotate_ms, key_switch_ms;
     uint64_t blind_rotate_launches, key_switch_launches, gates;
@@ -296,8 +298,8 @@ int tfhe_plan_wire_pool(const tfhe_gate_rec *gates, size_t ngates, size_t nwires
 /* Shape of the circuit that the last bnn_*_encrypted call on this cloud key ran: gate records,
  * wires of the lowered circuit (inputs, the two constants, one per gate), slots of the wire pool
  * it was evaluated in (a slot is reused once the last depth reading its wire has run; this is
- * the device memory the call needed, 4 (n+1) bytes per slot), and circuit depths (= kernel
- * pairs when no depth is wider than a launch).  For a layer evaluated in groups of units, gates
+ * the device memory the call needed, 4 (n+1) bytes per slot), and circuit depths (= batches
+ * when no level is wider than 262,144 gates).  For a layer evaluated in groups of units, gates
  * and wires are totals, pool_wires and depths the largest of any group. */
 typedef struct {
     uint64_t gates, circuit_wires, pool_wires, depths;
