@@ -281,13 +281,13 @@ def main():
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic.json")
     if os.path.exists(tpath):
         entry = json.load(open(tpath)).get(args.workload, {})
-        traffic = entry.get("blind_rotate_bytes_per_launch")
-        if traffic and entry.get("gates_per_launch") and br_avg_ms > 0:
+        traffic = entry.get("blind_rotate_bytes_per_batch")
+        if traffic and entry.get("gates_per_batch") and br_avg_ms > 0:
             # the counters were read on another run: scale to this run's batch size
-            scaled = traffic * gates_per_batch / entry["gates_per_launch"]
+            scaled = traffic * gates_per_batch / entry["gates_per_batch"]
             gbps = scaled / (br_avg_ms * 1e-3) / 1e9
             hbm = {"achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
-                   "frac": round(gbps / HBM_PEAK_GBPS, 4), "bytes_per_gate": round(traffic / entry["gates_per_launch"]),
+                   "frac": round(gbps / HBM_PEAK_GBPS, 4), "bytes_per_gate": round(traffic / entry["gates_per_batch"]),
                    "algorithmic_bytes_per_gate": 2 * 4 * words + 4 * (P.N + 1),
                    "source": entry.get("source")}
     roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP64_VECTOR_PEAK_TFLOPS,

@@ -13,6 +13,7 @@
 //   and psi^(-64 m) on the outputs, whose cosine the caller folds into its rounding.
 // The spectra are those of fft512.h (same frequencies, same scale), whose steps transform the key.
 //
+// (The fused-multiply-add form of Linzer and Feig, IEEE Trans. Signal Processing 41, 1993, carried through three passes.)
 // A twiddle c (1 + i t) costs two fused multiply-adds for the turn by (1 + i t); its cosine is not applied
 // to the number but left pending and absorbed, as a ratio of cosines, by the multiply-adds that take
 // the place of the transform's additions.  Fourteen instructions twiddle seven inputs instead of
@@ -21,7 +22,8 @@
 // cost accuracy however small a cosine is: x (1 + i t) with |t| up to 2^65 and a factor c with c t = 1 is
 // as accurate relative to its size as x times the rounded twiddle.  Largest distance of a product from its integer,
 // against the transforms of fft512.h: random operands 7e-7 against 6e-7, extreme magnitudes with random signs
-// 1.9e-6 against 2.4e-6, every operand at one end of its range 4.6e-5 against 3.1e-5 (a wrong rounding needs 0.5).
+// 1.9e-6 against 2.4e-6, every operand at one end of its range 4.6e-5 against 3.1e-5 (a wrong rounding needs 0.5); on the
+// device, over 12,288 gates each, random keys 1.2e-6 either way, keys at one end of the limbs' range 3.6e-5 against 3.1e-5.
 #pragma once
 #include <hip/hip_runtime.h>
 

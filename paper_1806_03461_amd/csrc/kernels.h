@@ -39,7 +39,7 @@ struct KeySwitchArgs {
 //   wave kernel       eight gates per CU at a time: 7.5 ms a round, 5.2 ms with at most four per CU in it,
 //                     6.3 ms with five
 //   four-wave kernel  1.6, 2.4 and 3.2 ms for one, two and three gates per CU; more begin a second round: four per CU
-//                     take 4.7 ms as two launches of two (1,024 gates 4.8 ms a call, 5.3 on the wave kernel,
+//                     take 4.7 ms as two launches of two (1,024 gates 4.7 ms a call, 5.4 on the wave kernel,
 //                     5.2 as three and one), five 6.1 ms (5.9 as three and two: the same), six 7.1 as twice three
 inline double rest_ms(size_t per_cu) {      // a launch of less than a round
     const double ms[9] = {0.0, 1.6, 2.4, 3.2, 4.7, 6.1, 6.6, 7.1, 7.5};

@@ -201,7 +201,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         const_cast<double2 *>(a.bk_fft), 0, (int)((size_t)a.n * 16 * kHalf * sizeof(double2)), 0x00020000);
     const uint32_t voff = (uint32_t)tid * (uint32_t)sizeof(double2);
     // value of row r, output 2 (part & 1) + o2 at slot 256 (part >> 1) + tid; the two slots of a thread share the scalar
-    // offset, so that the compiler forms it once for both
+    // offset, so that the compiler forms it once for both (against one each: 64 gates 1.59 -> 1.54 ms, 301 gates and more equal)
     auto key = [&](int row, int part, int r, int o2) {
         return load_key(key_rsrc, voff + (part >> 1 ? 4096u : 0u),
                         (uint32_t)row * 16u * kHalf * (uint32_t)sizeof(double2) +
@@ -223,7 +223,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     // barrier or follow one directly -- rotation and forward pass 1, inverse pass 1 and the accumulation -- issue
     // first, forward passes 2 and 3 next, and the other workgroups' gather, products and scatter, which wait
     // on swaps and key loads anyway, last.  Measured against one high level for all of the former: 301 gates
-    // 2.36 -> 2.26 ms, 768 gates 3.41 -> 3.30 ms; raising the gather instead costs up to 30 %.
+    // 2.23 -> 2.21 ms, 512 gates 2.29 -> 2.27, 768 gates 3.42 -> 3.34; raising the gather instead costs up to 30 %.
     auto priority = [](int level) {
         if (AHEAD) return;               // a lone workgroup per CU has nobody to overtake
         if (level == 2) __builtin_amdgcn_s_setprio(2);
@@ -494,21 +494,21 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 // need no exchange between lanes and no barrier stands between a wave and its data: against the four-wave
 // kernel the 256 lane swaps of a gate's step and three barriers are gone, both digits of a component come
 // from one rotated read and one subtraction, and both limbs of an output are added before one LDS
-// accumulation.  With the twiddles of dft8.h a step is 2,500 vector instructions per gate (3,430 issue
-// slots in the four-wave kernel).  A polynomial passes through one 9 KB buffer that belongs to the wave; LDS
+// accumulation.  A step is 2,504 vector instructions per gate (3,166 issue slots in the four-wave
+// kernel, lane swaps counted as the two they take).  A polynomial passes through one 9 KB buffer that belongs to the wave; LDS
 // operations of a wave execute in order, so the stores of one polynomial may follow the loads of the one
 // before it at once.
 //
-// What bounds it: at 2,048 gates or more, about 1,830 ns per gate-step and CU -- vector instructions 68 % of
-// the time, LDS and the key stream through L1 (128 KB per gate-step at 64 B a clock) about half each -- while
-// the clock has dropped to 2.0 GHz, i.e. the chip is at its power limit.  12,288 gates 52.3 -> 44.0 ms.
+// What bounds it: at 2,048 gates or more, about 1,830 ns per gate-step and CU -- vector instructions 67 % of
+// the time, LDS 48 %, the key stream through L1 (128 KB per gate-step at 64 B a clock) 55 % -- while
+// the clock has dropped to 1.96 GHz, i.e. the chip is at its power limit.  12,288 gates 52.3 -> 44.0 ms.
 // What it took, one by one on 12,288 gates: without the twiddles of dft8.h + 2.6 ms; without the barrier
 // before the products + 6 ms (below); without the priorities + 3 ms (below); without interleaving LDS
 // instructions with arithmetic + 2 ms.  Key rows brought to LDS by loads to LDS and read by all four waves
 // instead of four L1 reads: equal (the LDS pipe then carries what L1 carried).
 //
 // Barrier before the products: the four waves of a workgroup then read the key row together and three
-// quarters of their reads hit L1 (265 instead of 1,024 lines per gate-step from L2); without it the waves of
+// quarters of their reads hit L1 (256 instead of 1,024 lines per gate-step from L2); without it the waves of
 // an XCD spread over more rows than its L2 holds.
 // Priorities: the inverse transforms and the first half of the forward ones issue ahead of the second half and
 // the products.  Each half holds half of a step's arithmetic, so the two waves of a SIMD fall into opposite
@@ -953,7 +953,7 @@ __global__ void zero_outputs_kernel(KeySwitchArgs a) {
 // of key tiles and by the latency of getting them started, many by the tiles' way from L2 (64 MB per 32 TILES
 // gates), which two workgroups on a CU keep busier than one with more gates.  Measured against 256 gates x 64 words a
 // workgroup, one wave per SIMD, with up to 32 partial sums of every word added by atomics:
-// 8 gates 26.5 -> 13.3 us, 64 gates 36 -> 17, 256 gates 56 -> 33, 512 gates 82 -> 65, 1,536 gates 237 -> 121,
+// the kernel alone, 8 gates 26.5 -> 13.3 us, 64 gates 36 -> 17, 256 gates 56 -> 33, 512 gates 82 -> 65, 1,536 gates 237 -> 121,
 // 4,096 gates 403 -> 291, 16,384 gates 1,457 -> 1,353.
 // ------------------------------------------------------------------------------------------
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -1170,10 +1170,10 @@ static int latency_batch_limit() {
     return limit;
 }
 
-// Upper bound on the workgroups of a throughput launch, 0 = none (one workgroup per gate, the
+// Upper bound on the workgroups of a launch of blind_rotate_kernel, 0 = none (one workgroup per gate, the
 // default).  With a bound -- three per CU is what stays resident -- each workgroup takes every
 // grid-th gate and all of them walk the key rows together from the first gate to the last.
-// Measured on 12,288 gates: workgroups that start together stay in the same phase of the step,
+// Measured on 12,288 gates, when this kernel took them: workgroups that start together stay in the same phase of the step,
 // so their transform, product and key-load phases coincide instead of overlapping, and the
 // launch takes 68 ms against 56 ms with one workgroup per gate, whose start times spread out.
 static int resident_groups() {

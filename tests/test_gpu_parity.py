@@ -453,4 +453,4 @@ def test_extreme_key_limbs_stay_exact(gpu, orc, pattern):
     finally:
         T.tfhe_rounding_margin_enable(served, False)
     assert np.array_equal(got, oracle_batch(keys, "XOR", cta, ctb))
-    assert 0 < worst < 1e-3, worst          # measured: 2.3e-5 at the extreme patterns, 1e-6 for random keys
+    assert 0 < worst < 1e-3, worst          # measured: 1e-5 at the extreme patterns, 9e-7 for random keys
