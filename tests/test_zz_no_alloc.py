@@ -47,3 +47,35 @@ def test_noalloc_entry_point_equals_gate_batch_on_successive_calls():
         T.tfhe_gate_batch_noalloc(ck, "AND", big, big, big, T.NOALLOC_MAX_GATES + 1)
     assert e.value.code == -3 and "at most" in str(e.value)
     T.tfhe_gate_batch_noalloc(ck, "AND", 0, 0, 0, 0)          # count 0: no-op
+
+
+@pytest.mark.parametrize("count", [5, 300, 900, 2500])
+def test_noalloc_entry_point_under_graph_capture(count):
+    """A captured call -- on the latency kernel, the four-wave kernel, two launches of it, a round of the wave
+    kernel with a remainder -- replayed on new inputs with eager calls between: every replay gives the bytes of
+    the eager call."""
+    import torch
+    import paper_1806_03461_amd as T
+    sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
+    T.tfhe_cloud_key_upload(ck)
+    rng = np.random.default_rng(count)
+    a, b = (torch.empty((count, 501), dtype=torch.int32, device="cuda") for _ in range(2))
+    out, want = torch.zeros_like(a), torch.zeros_like(a)
+
+    def fill(seed):
+        for k, t in enumerate((a, b)):
+            t.copy_(T.to_device(T.tfhe_encrypt(sk, seed + k, rng.integers(0, 2, count).astype(np.uint8))))
+
+    fill(500)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        T.tfhe_gate_batch_noalloc(ck, "XNOR", a, b, out, count)
+    for replay in range(4):
+        fill(510 + 2 * replay)
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        T.tfhe_gate_batch(ck, "XNOR", a, b, want, count)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), replay
