@@ -96,7 +96,7 @@ struct tfhe_cloud_key {
     size_t cus = 256;               // compute units of that device
     uint32_t *d_ksk = nullptr;
     void *d_ksk_tiles = nullptr;    // the same key as int8 operand tiles (t = 8, basebit = 2, n < 512 only)
-    double2 *d_bk_fft = nullptr;    // [n][2l][4][N/2]: output o = 2*component + limb
+    double2 *d_bk_fft = nullptr;    // [n][2l][4][N/2]: output o = 2*component + limb; behind it [n][2l][3][N/2] (sums3.h)
     double2 *d_tables = nullptr;    // twiddle tables
     tfhe::DeviceBuffer ws_gates, ws_ext, ws_wires, ws_outs;
     tfhe::StagingBuffer stage_gates, stage_outs;

@@ -541,7 +541,7 @@ static int tfhe_cloud_key_upload_impl(tfhe_cloud_key *ck) {
     const size_t bk_bytes = ck->bk_raw.size() * sizeof(uint32_t);
     if (int rc = raw.buf.reserve(bk_bytes)) return rc;
     TFHE_HIP(hipMemcpy(raw.buf.ptr, ck->bk_raw.data(), bk_bytes, hipMemcpyHostToDevice));
-    const size_t fft_words = (size_t)P.n * 16 * 512;
+    const size_t fft_words = bk_spectrum_words((size_t)P.n);
     TFHE_HIP(hipMalloc((void **)&ck->d_bk_fft, fft_words * sizeof(double2)));
     if (int rc = launch_bk_to_spectrum((const uint32_t *)raw.buf.ptr, ck->d_bk_fft, ck->d_tables, P.n, nullptr))
         return rc;

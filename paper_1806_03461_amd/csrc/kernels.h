@@ -13,7 +13,7 @@ struct BlindRotateArgs {
     uint32_t *ext;               // device [count][1025]: extracted samples
     size_t count;
     size_t first;                // set by the launcher: a launch takes items first .. count - 1
-    const double2 *bk_fft;       // device [n][4][4][512]
+    const double2 *bk_fft;       // device [n][4][4][512], and behind it [n][4][3][512] (sums3.h)
     const double2 *tables;       // device: exp(i pi j / 1024), j < 2048, and the constants of dft8.h
     int n, bgbit;
     double *margin;              // device, optional: largest rounding distance seen
@@ -36,13 +36,12 @@ struct KeySwitchArgs {
 // How long a blind rotation of `items` gates takes on a device with `cus` compute units, in milliseconds, as
 // measured on 256 of them (n = 500; other step counts scale all of it alike): what the launcher's choice of
 // kernels and the scheduler of narrow circuits go by.
-//   wave kernel       eight gates per CU at a time: 7.5 ms a round, 5.2 ms with at most four per CU in it,
-//                     6.3 ms with five
-//   four-wave kernel  1.6, 2.4 and 3.2 ms for one, two and three gates per CU; more begin a second round: four per CU
-//                     take 4.7 ms as two launches of two (1,024 gates 4.7 ms a call, 5.4 on the wave kernel,
-//                     5.2 as three and one), five 6.1 ms (5.9 as three and two: the same), six 7.1 as twice three
+//   wave kernel       eight gates per CU at a time: 6.4 ms a round, 4.5 ms with at most four per CU in it,
+//                     5.8 ms with five or six, 6.0 ms with seven
+//   four-wave kernel  1.6, 2.3 and 3.3 ms for one, two and three gates per CU; more begin a second round: four per CU
+//                     take 4.5 ms as two launches of two, five 5.5 ms
 inline double rest_ms(size_t per_cu) {      // a launch of less than a round
-    const double ms[9] = {0.0, 1.6, 2.4, 3.2, 4.7, 6.1, 6.6, 7.1, 7.5};
+    const double ms[9] = {0.0, 1.6, 2.3, 3.3, 4.5, 5.5, 5.8, 6.0, 6.4};
     return ms[per_cu];
 }
 // of a batch's last, partial round: whether the four-wave kernels serve it faster than the wave kernel
@@ -50,8 +49,11 @@ inline bool four_waves_faster(size_t per_cu) { return per_cu <= 5; }
 constexpr size_t kRoundPerCu = 8;
 inline double rotation_ms(size_t items, size_t cus) {
     const size_t round = kRoundPerCu * cus, rest = items % round;
-    return 7.5 * (double)(items / round) + rest_ms((rest + cus - 1) / cus);
+    return 6.4 * (double)(items / round) + rest_ms((rest + cus - 1) / cus);
 }
+
+// complex words of the key's spectra, both forms
+inline size_t bk_spectrum_words(size_t n) { return n * 4 * (4 + 3) * 512; }
 
 size_t blind_rotate_lds_bytes();
 int launch_bk_to_spectrum(const uint32_t *bk_raw, double2 *bk_fft, const double2 *tables, int n,

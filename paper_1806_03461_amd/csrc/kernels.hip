@@ -5,13 +5,13 @@
 //
 // Exactness.  Each blind-rotation step needs, for both TRLWE components c,
 //     sum_{r<4} digit_r(X) * BK_i[r][c](X)   mod (X^1024 + 1, 2^32),
-// digit_r with coefficients in [-512, 512).  Every 32-bit key coefficient is split into two
-// signed 16-bit limbs, key = lo + 2^16 hi (mod 2^32); the two integer products
-// sum_r digit_r * lo_r and sum_r digit_r * hi_r have coefficients below 2^36 in magnitude and
-// are computed with double-precision FFTs whose rounding error stays orders of magnitude below
-// 1/2, so rounding the inverse transform to the nearest integer gives them exactly; the result
-// is lo-sum + 2^16 * hi-sum (mod 2^32).  MI355X issues FP64 FMAs at full vector rate, which
-// makes this cheaper than any 32-bit-integer number-theoretic transform on its VALU.
+// digit_r with coefficients in [-512, 512).  The products are integer ones, computed with double-precision FFTs whose
+// rounding error stays far below 1/2, so rounding the inverse transforms gives them exactly.  The key's 32 bits a
+// coefficient are too many for one such product.  The four-wave kernels split every coefficient into two signed 16-bit
+// limbs, key = lo + 2^16 hi (mod 2^32): four products for the two components, coefficients below 2^36, and the result is
+// lo-sum + 2^16 * hi-sum (mod 2^32).  The wave kernel gets both components from three products (sums3.h).  MI355X
+// issues FP64 FMAs at full vector rate, which makes this cheaper than any 32-bit-integer number-theoretic transform on
+// its VALU.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -23,6 +23,7 @@
 #include "dft8.h"
 #include "fft512.h"
 #include "kernels.h"
+#include "sums3.h"
 
 namespace tfhe {
 
@@ -42,35 +43,41 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // ------------------------------------------------------------------------------------------
-// Bootstrapping key -> transform domain.  One workgroup per sample row (i, r): its four waves
-// transform the four polynomials o = 2*component + limb with the very steps the blind rotation
-// applies to its four digit polynomials, so the spectra land in the slot order the products use.
-// bk_raw [n][4][2][1024] uint32  ->  bk_fft [n][4][o][512] complex.
+// Bootstrapping key -> transform domain, in both forms: with the key's limbs for the four-wave kernels, with the factors of
+// sums3.h for the wave kernel.  Two workgroups per sample row (i, r), one for each form: the four waves of the first
+// transform the four polynomials o = 2*component + limb with the very steps the blind rotation applies to its four digit
+// polynomials, so the spectra land in the slot order the products use; of the second's waves, three the three factors.
+// bk_raw [n][4][2][1024] uint32  ->  bk_fft [n][4][o][512] complex, and behind all of it [n][4][3][512].
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void bk_to_spectrum_kernel(const uint32_t *__restrict__ bk_raw,
                                                              double2 *__restrict__ bk_fft,
                                                              const double2 *__restrict__ tables) {
     __shared__ double2 buf[kBufWords];
     const int L = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const size_t row = blockIdx.x;                 // i * 4 + r
-    const int c = wv >> 1, limb = wv & 1;          // pass 1: wave o = 2 c + limb
-    const uint32_t *src = bk_raw + (row * 2 + (size_t)c) * kN;
+    const size_t row = blockIdx.x >> 1;            // i * 4 + r
+    const bool sums = blockIdx.x & 1;
+    const int c = wv >> 1, limb = wv & 1;          // pass 1: wave o = 2 c + limb, or o of sums3.h
+    const uint32_t *src = bk_raw + row * 2 * kN;
     Lane ln;
     lane_init(ln, tables, L);
     double2 x[8];
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
         const int j = L + 64 * m;
-        int32_t v[2];
+        double v[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const uint32_t w = src[j + h * kHalf];
-            const int32_t lo = (int16_t)(w & 0xFFFFu);
-            const int32_t hi = (int16_t)(((w - (uint32_t)lo) >> 16) & 0xFFFFu);
-            v[h] = limb ? hi : lo;
+            if (sums) {
+                v[h] = wv < kSums ? sum_factor(src[j + h * kHalf], src[kN + j + h * kHalf], wv) : 0.0;
+            } else {
+                const uint32_t w = src[c * kN + j + h * kHalf];
+                const int32_t lo = (int16_t)(w & 0xFFFFu);
+                const int32_t hi = (int16_t)(((w - (uint32_t)lo) >> 16) & 0xFFFFu);
+                v[h] = (double)(limb ? hi : lo);
+            }
         }
         // the 1/512 of the inverse transform is folded into the key (exact: a power of two)
-        x[m] = make_double2((double)v[0] * (1.0 / 512.0), (double)v[1] * (1.0 / 512.0));
+        x[m] = make_double2(v[0] * (1.0 / 512.0), v[1] * (1.0 / 512.0));
     }
     fwd_pass1_store(x, ln, buf + wv * kPolyStride, L);
     __syncthreads();
@@ -81,11 +88,13 @@ __global__ __launch_bounds__(256) void bk_to_spectrum_kernel(const uint32_t *__r
     wave_sync();
     fwd_pass3(x, mine, L);
     gather_rows(x);
+    const int outputs = sums ? kSums : 4;
+    double2 *out = bk_fft + (sums ? (size_t)(gridDim.x >> 1) * 4 * kHalf : 0) + row * (size_t)outputs * kHalf;
 #pragma unroll
     for (int o = 0; o < 4; ++o)
 #pragma unroll
         for (int q = 0; q < 2; ++q)
-            bk_fft[(row * 4 + (size_t)o) * kHalf + 256 * q + threadIdx.x] = x[2 * o + q];
+            if (o < outputs) out[(size_t)o * kHalf + 256 * q + threadIdx.x] = x[2 * o + q];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -492,23 +501,23 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 //
 // A lane holds all four digit spectra of its eight frequencies (x[4][8], 128 registers), so the products
 // need no exchange between lanes and no barrier stands between a wave and its data: against the four-wave
-// kernel the 256 lane swaps of a gate's step and three barriers are gone, both digits of a component come
-// from one rotated read and one subtraction, and both limbs of an output are added before one LDS
-// accumulation.  A step is 2,504 vector instructions per gate (3,166 issue slots in the four-wave
-// kernel, lane swaps counted as the two they take).  A polynomial passes through one 9 KB buffer that belongs to the wave; LDS
+// kernel the 256 lane swaps of a gate's step and three barriers are gone, and both digits of a component come
+// from one rotated read and one subtraction.  The two components of the result come from three sums (sums3.h): seven transforms a
+// step and 96 KB of key instead of eight and 128 KB.  A polynomial passes through one 9 KB buffer that belongs to the wave; LDS
 // operations of a wave execute in order, so the stores of one polynomial may follow the loads of the one
 // before it at once.
 //
-// What bounds it: at 2,048 gates or more, about 1,830 ns per gate-step and CU -- vector instructions 67 % of
-// the time, LDS 48 %, the key stream through L1 (128 KB per gate-step at 64 B a clock) 55 % -- while
-// the clock has dropped to 1.96 GHz, i.e. the chip is at its power limit.  12,288 gates 52.3 -> 44.0 ms.
-// What it took, one by one on 12,288 gates: without the twiddles of dft8.h + 2.6 ms; without the barrier
+// What bounds it: vector issue, LDS and the key stream through L1 side by side.  An exchange of a polynomial (8 KB) costs LDS 18 clocks
+// per 16 bytes a lane, 13 of them the store -- the vector units hand LDS about 77 bytes a clock per CU, whatever the width
+// of the store -- so fourteen exchanges are about 2,000 clocks a gate-step beside some 2,250 of vector issue.
+// 65,536 gates: four-wave kernel 284 ms, this kernel with four sums (2,504 vector instructions a gate-step) 236 ms, with three 206 ms.
+// What it took, one by one on 12,288 gates with four sums: without the twiddles of dft8.h + 2.6 ms; without the barrier
 // before the products + 6 ms (below); without the priorities + 3 ms (below); without interleaving LDS
 // instructions with arithmetic + 2 ms.  Key rows brought to LDS by loads to LDS and read by all four waves
 // instead of four L1 reads: equal (the LDS pipe then carries what L1 carried).
 //
 // Barrier before the products: the four waves of a workgroup then read the key row together and three
-// quarters of their reads hit L1 (256 instead of 1,024 lines per gate-step from L2); without it the waves of
+// quarters of their reads hit L1; without it the waves of
 // an XCD spread over more rows than its L2 holds.
 // Priorities: the inverse transforms and the first half of the forward ones issue ahead of the second half and
 // the products.  Each half holds half of a step's arithmetic, so the two waves of a SIMD fall into opposite
@@ -516,7 +525,7 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 // at another place, is 1 to 7 % slower.
 // ------------------------------------------------------------------------------------------
 constexpr int kWaveGates = 4;      // waves (= gates) of a workgroup
-constexpr int kKeyRing = 4;        // key batches (one output at one frequency: four 16-byte loads) in registers
+constexpr int kKeyRing = 4;        // key batches (one sum at one frequency: four 16-byte loads) in registers
 
 struct WaveLds {
     double2 buf[kWaveGates][8 * kRowStride];
@@ -553,7 +562,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
     f3.h1 = a.tables[kFwd3 + 128 + L];
     f3.h1w = a.tables[kFwd3 + 192 + L];
     const __amdgpu_buffer_rsrc_t key_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<double2 *>(a.bk_fft), 0, (int)((size_t)a.n * 16 * kHalf * sizeof(double2)), 0x00020000);
+        const_cast<double2 *>(a.bk_fft + (size_t)a.n * 16 * kHalf), 0, (int)((size_t)a.n * 4 * kSums * kHalf * sizeof(double2)), 0x00020000);
     const uint32_t voff = (uint32_t)wave_slot_lane(L) * (uint32_t)sizeof(double2);
     double worst = 0.0;
 
@@ -682,13 +691,13 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             for (int k = 0; k < 8; ++k) v[k] = mine[(L & 7) * kGrpStride + k];
             wave_sync();
         };
-        const uint32_t row = (uint32_t)i * 16u * kHalf * (uint32_t)sizeof(double2);
+        const uint32_t row = (uint32_t)i * 4u * kSums * kHalf * (uint32_t)sizeof(double2);
         double2 ring[kKeyRing][4];
-        auto load_batch = [&](int b) {                               // output b % 4 at frequency k2 = b / 4
-            const int k2 = b >> 2, o = b & 3;
+        auto load_batch = [&](int b) {                               // sum b % 3 at frequency k2 = b / 3
+            const int k2 = b / kSums, o = b % kSums;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                ring[b % kKeyRing][r] = load_key(key_rsrc, voff, row + (uint32_t)(((r * 4 + o) * kHalf + wave_slot_register(k2)) * sizeof(double2)));
+                ring[b % kKeyRing][r] = load_key(key_rsrc, voff, row + (uint32_t)(((r * kSums + o) * kHalf + wave_slot_register(k2)) * sizeof(double2)));
         };
 
         // ---- forward: four polynomials, the LDS exchanges of one beside the arithmetic of another ----
@@ -740,15 +749,15 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             REGION_END();
         }
 
-        // ---- products with the key row: at every frequency the four digit spectra give way to the four outputs ----
+        // ---- products with the key row: at every frequency the four digit spectra give way to the three sums ----
         __builtin_amdgcn_s_barrier();                // no data passes: the four waves share their key reads
 #pragma unroll
         for (int k2 = 0; k2 < 8; ++k2) {
-            double2 y[4];
+            double2 y[kSums];
 #pragma unroll
-            for (int o = 0; o < 4; ++o) {
-                const int b = 4 * k2 + o;
-                if (b + kKeyRing - 1 < 32) load_batch(b + kKeyRing - 1);
+            for (int o = 0; o < kSums; ++o) {
+                const int b = kSums * k2 + o;
+                if (b + kKeyRing - 1 < 8 * kSums) load_batch(b + kKeyRing - 1);
                 REGION_END();
                 const double2 (&k)[4] = ring[b % kKeyRing];
                 const double2 d0 = x[0][k2];
@@ -767,7 +776,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
                 REGION_END();
             }
 #pragma unroll
-            for (int o = 0; o < 4; ++o) x[o][k2] = y[o];
+            for (int o = 0; o < kSums; ++o) x[o][k2] = y[o];
         }
 
         // ---- back: inverse transforms, exact rounding, accumulate ----
@@ -783,8 +792,8 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             const_double *u = uniform_constants(a.tables);
 #pragma unroll
             for (int m = 1; m < 8; ++m) { tan_m[m] = u[m]; cos_m[m] = u[16 + m]; }
-            uint32_t low[8][2];
-            // pass 1, rounding, and with the second limb the accumulation of a component
+            uint32_t low[8][2];            // the low sum, then what it leaves for component 1 (sums3.h)
+            // pass 1 and rounding of sum o, and the accumulation of component o - 1
             auto finish = [&](int o) {
                 double2 (&v)[8] = x[o];
                 v[0] = cmul(v[0], w10);
@@ -795,17 +804,21 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
                     const double part[2] = {v[m].x, v[m].y};
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        // 1.5 * 2^52 - value leaves round-to-nearest(-value) mod 2^32 in the low word; the value's
-                        // pending cosine rides in the multiply-add, so it is rounded once
-                        const double shifted = m ? fma(-cos_m[m], part[h], 6755399441055744.0) : 6755399441055744.0 - part[h];
-                        const uint32_t r = (uint32_t)__double2loint(shifted);
-                        if (MARGIN) worst = fmax(worst, fabs((m ? cos_m[m] * part[h] : part[h]) + (shifted - 6755399441055744.0)));
-                        if (!(o & 1)) {
-                            low[m][h] = r;
+                        // the value's pending cosine rides in the multiply-add, so it is rounded once
+                        if (o == 0) {
+                            const double shifted = m ? fma(cos_m[m], part[h], kIntegerShift) : kIntegerShift + part[h];
+                            low[m][h] = (uint32_t)__double2loint(shifted);
+                            if (MARGIN) worst = fmax(worst, fabs((m ? cos_m[m] * part[h] : part[h]) - (shifted - kIntegerShift)));
                         } else {
-                            const uint32_t t = low[m][h] + (r << 16);
-                            atomicAdd(&acc[o >> 1][L + 64 * m + h * kHalf], t);
-                            if (m == 0 && h == 0) atomicSub(&acc[o >> 1][kN + L], t);      // the mirror holds -c - 2
+                            const double shifted = m ? fma(-cos_m[m], part[h], kHalfShift) : kHalfShift - part[h];
+                            // the complemented accumulator takes -P: ~(ACC + P) = ~ACC - P
+                            const uint32_t t = minus_product(low[m][h], (uint32_t)__double2loint(shifted));
+                            if (MARGIN) {
+                                const double rest = (m ? cos_m[m] * part[h] : part[h]) - (double)((0u - t) & kSumMask) * (1.0 / (1 << kSumBits));
+                                worst = fmax(worst, fabs(rest - rint(rest)));
+                            }
+                            atomicAdd(&acc[o - 1][L + 64 * m + h * kHalf], t);
+                            if (m == 0 && h == 0) atomicSub(&acc[o - 1][kN + L], t);      // the mirror holds -c - 2
                         }
                     }
                 }
@@ -824,27 +837,17 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             REGION_END();
             dft8_twiddled<true>(x[1], w2);
             REGION_END();
-            store_row(x[1]); load_columns(x[1]);
+            store_row(x[1]); load_columns(x[1]); store_along(x[2]); load_across(x[2]);
             finish(0);
-            TRANSPOSE_BESIDE(6)
-            REGION_END();
-            store_along(x[2]); load_across(x[2]);
-            radix8<true>(x[3]);
-            TRANSPOSE_BESIDE(4)
+            TRANSPOSE_BESIDE(3) TRANSPOSE_BESIDE(3)
             REGION_END();
             dft8_twiddled<true>(x[2], w2);
             REGION_END();
-            store_row(x[2]); load_columns(x[2]); store_along(x[3]); load_across(x[3]);
+            store_row(x[2]); load_columns(x[2]);
             finish(1);
-            TRANSPOSE_BESIDE(3) TRANSPOSE_BESIDE(3)
-            REGION_END();
-            dft8_twiddled<true>(x[3], w2);
-            REGION_END();
-            store_row(x[3]); load_columns(x[3]);
-            finish(2);
             TRANSPOSE_BESIDE(6)
             REGION_END();
-            finish(3);
+            finish(2);
             wave_sync();
         }
     }
@@ -1241,7 +1244,7 @@ uint32_t *static_scratch_ptr() {
 
 int launch_bk_to_spectrum(const uint32_t *bk_raw, double2 *bk_fft, const double2 *tables, int n,
                           hipStream_t stream) {
-    hipLaunchKernelGGL(bk_to_spectrum_kernel, dim3((unsigned)n * 4), dim3(256), 0, stream, bk_raw, bk_fft, tables);
+    hipLaunchKernelGGL(bk_to_spectrum_kernel, dim3((unsigned)n * 8), dim3(256), 0, stream, bk_raw, bk_fft, tables);
     TFHE_HIP(hipGetLastError());
     return TFHE_OK;
 }
