@@ -41,7 +41,7 @@ struct KeySwitchArgs {
 //   four-wave kernel  1.6, 2.3 and 3.3 ms for one, two and three gates per CU; more begin a second round: four per CU
 //                     take 4.5 ms as two launches of two, five 5.5 ms
 inline double rest_ms(size_t per_cu) {      // a launch of less than a round
-    const double ms[9] = {0.0, 1.6, 2.3, 3.3, 4.5, 5.5, 5.8, 6.0, 6.4};
+    const double ms[9] = {0.0, 1.55, 2.26, 3.32, 4.53, 5.49, 5.81, 5.98, 6.42};
     return ms[per_cu];
 }
 // of a batch's last, partial round: whether the four-wave kernels serve it faster than the wave kernel
@@ -49,7 +49,7 @@ inline bool four_waves_faster(size_t per_cu) { return per_cu <= 5; }
 constexpr size_t kRoundPerCu = 8;
 inline double rotation_ms(size_t items, size_t cus) {
     const size_t round = kRoundPerCu * cus, rest = items % round;
-    return 6.4 * (double)(items / round) + rest_ms((rest + cus - 1) / cus);
+    return 6.42 * (double)(items / round) + rest_ms((rest + cus - 1) / cus);
 }
 
 // complex words of the key's spectra, both forms
