@@ -36,16 +36,19 @@ struct KeySwitchArgs {
 // How long a blind rotation of `items` gates takes on a device with `cus` compute units, in milliseconds, as
 // measured on 256 of them (n = 500; other step counts scale all of it alike): what the launcher's choice of
 // kernels and the scheduler of narrow circuits go by.
-//   wave kernel       eight gates per CU at a time: 6.4 ms a round, 4.5 ms with at most four per CU in it,
+//   wave kernel       eight gates per CU at a time: 6.4 ms a round, 4.1 ms with at most four per CU in it,
 //                     5.8 ms with five or six, 6.0 ms with seven
-//   four-wave kernel  1.6, 2.3 and 3.3 ms for one, two and three gates per CU; more begin a second round: four per CU
-//                     take 4.5 ms as two launches of two, five 5.5 ms
+//   four-wave kernel  1.55, 2.3 and 3.3 ms for one, two and three gates per CU, 5.5 ms for five
 inline double rest_ms(size_t per_cu) {      // a launch of less than a round
-    const double ms[9] = {0.0, 1.55, 2.26, 3.32, 4.53, 5.49, 5.81, 5.98, 6.42};
+    const double ms[9] = {0.0, 1.55, 2.26, 3.32, 4.13, 5.49, 5.81, 5.98, 6.42};
     return ms[per_cu];
 }
-// of a batch's last, partial round: whether the four-wave kernels serve it faster than the wave kernel
-inline bool four_waves_faster(size_t per_cu) { return per_cu <= 5; }
+// the kernel that serves a batch's last, partial round fastest: the wave kernel together with the whole rounds or in a launch of its
+// own, or the four-wave kernels
+enum class RestKernel { kFourWaves, kWave, kWithRounds };
+inline RestKernel rest_kernel(size_t per_cu) {
+    return per_cu >= 6 ? RestKernel::kWithRounds : per_cu == 4 ? RestKernel::kWave : RestKernel::kFourWaves;
+}
 constexpr size_t kRoundPerCu = 8;
 inline double rotation_ms(size_t items, size_t cus) {
     const size_t round = kRoundPerCu * cus, rest = items % round;

@@ -544,7 +544,7 @@ static_assert(2 * sizeof(WaveLds) <= 160 * 1024, "two workgroups share a CU's LD
 #define EIGHT(X, V) X(V) X(V) X(V) X(V) X(V) X(V) X(V) X(V)
 #define TRANSPOSE_BESIDE(V) EIGHT(ONE_STORE, V) EIGHT(ONE_LOAD, V)
 
-template <bool MARGIN>
+template <bool MARGIN, bool SHARE>
 __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu(2, 2))) void blind_rotate_wave_kernel(BlindRotateArgs a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     WaveLds &my = *reinterpret_cast<WaveLds *>(lds_raw);
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         }
 
         // ---- products with the key row: at every frequency the four digit spectra give way to the three sums ----
-        __builtin_amdgcn_s_barrier();                // no data passes: the four waves share their key reads
+        if (SHARE) __builtin_amdgcn_s_barrier();     // no data passes: the four waves read the key row together
 #pragma unroll
         for (int k2 = 0; k2 < 8; ++k2) {
             double2 y[kSums];
@@ -1249,18 +1249,19 @@ int launch_bk_to_spectrum(const uint32_t *bk_raw, double2 *bk_fft, const double2
     return TFHE_OK;
 }
 
-// the six blind-rotation kernels and the widest matrix-core key switch, with their
+// the seven blind-rotation kernels and the widest matrix-core key switch, with their
 // dynamic LDS sizes and per-device "attribute set" masks
 namespace {
-constexpr int kBigLdsKernels = 7;
+constexpr int kBigLdsKernels = 8;
 struct BigLdsKernel { const void *fn; size_t lds; std::atomic<uint64_t> done; };
 BigLdsKernel big_lds_kernels[kBigLdsKernels] = {
     {reinterpret_cast<const void *>(&blind_rotate_kernel<false>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_kernel<true>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<false>), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<true>), sizeof(GateLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false>), sizeof(WaveLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<true>), sizeof(WaveLds), {0}},
+    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false, true>), sizeof(WaveLds), {0}},
+    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<true, true>), sizeof(WaveLds), {0}},
+    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false, false>), sizeof(WaveLds), {0}},
     {reinterpret_cast<const void *>(&key_switch_mfma_kernel<4>), sizeof(KsLds<4>), {0}},
 };
 int allow(int which) { return allow_dynamic_lds(big_lds_kernels[which].fn, big_lds_kernels[which].lds, big_lds_kernels[which].done); }
@@ -1298,40 +1299,46 @@ static int launch_four_waves(const BlindRotateArgs &a, hipStream_t stream) {
     return TFHE_OK;
 }
 
-// Whole rounds go to the wave kernel, and what remains follows on the four-wave kernels where those are the
-// faster ones, up to five gates per CU (times in kernels.h).
 static_assert(kRoundPerCu == 2 * kWaveGates, "two workgroups of the wave kernel per CU");
 
+// Items first .. count - 1 with the wave kernel.  With more than one workgroup per CU the waves of a workgroup meet before the
+// products, so that their key reads hit L1 (8,192 gates 26.0 -> 25.2 ms); a lone workgroup leaves L1 and L2 idle enough
+// and loses by waiting (1,024 gates 4.15 ms without, 4.54 with).
+static int launch_wave(const BlindRotateArgs &a, size_t cus, hipStream_t stream) {
+    const size_t items = a.count - a.first;
+    const int which = a.margin ? 5 : items > kWaveGates * cus ? 4 : 6;
+    if (int rc = allow(which)) return rc;
+    const dim3 grid((unsigned)((items + kWaveGates - 1) / kWaveGates)), block(64 * kWaveGates);
+    if (which == 5) hipLaunchKernelGGL((blind_rotate_wave_kernel<true, true>), grid, block, sizeof(WaveLds), stream, a);
+    else if (which == 4) hipLaunchKernelGGL((blind_rotate_wave_kernel<false, true>), grid, block, sizeof(WaveLds), stream, a);
+    else hipLaunchKernelGGL((blind_rotate_wave_kernel<false, false>), grid, block, sizeof(WaveLds), stream, a);
+    TFHE_HIP(hipGetLastError());
+    return TFHE_OK;
+}
+
+// Whole rounds go to the wave kernel, and what remains follows on the kernel that serves it fastest (times in kernels.h): six
+// or seven gates per CU in the same launch, four in one of their own (behind the rounds of the same launch their workgroups would
+// go to whichever CU ended first, two to some), other numbers on the four-wave kernels.
 int launch_blind_rotate(const BlindRotateArgs &args, hipStream_t stream) {
     if (args.count == 0) return TFHE_OK;
     BlindRotateArgs a = args;
     a.first = 0;
     const size_t cus = device_cus() > 0 ? (size_t)device_cus() : 256;
-    size_t whole = a.count - a.count % (kRoundPerCu * cus);
-    if (!four_waves_faster((a.count - whole + cus - 1) / cus)) whole = a.count;
-    if (wave_gates_from() >= 0) whole = a.count >= (size_t)wave_gates_from() ? a.count : 0;
-    if (whole) {
-        a.count = whole;
-        if (int rc = allow(4 + (a.margin ? 1 : 0))) return rc;
-        const dim3 grid((unsigned)((whole + kWaveGates - 1) / kWaveGates));
-        if (a.margin) hipLaunchKernelGGL(blind_rotate_wave_kernel<true>, grid, dim3(64 * kWaveGates), sizeof(WaveLds), stream, a);
-        else hipLaunchKernelGGL(blind_rotate_wave_kernel<false>, grid, dim3(64 * kWaveGates), sizeof(WaveLds), stream, a);
-        TFHE_HIP(hipGetLastError());
+    size_t rest = a.count % (kRoundPerCu * cus);
+    RestKernel kernel = rest_kernel((rest + cus - 1) / cus);
+    if (wave_gates_from() >= 0) {
+        kernel = a.count >= (size_t)wave_gates_from() ? RestKernel::kWithRounds : RestKernel::kFourWaves;
+        rest = a.count;
     }
-    if (whole == args.count) return TFHE_OK;
-    a.first = whole;
+    if (kernel == RestKernel::kWithRounds) rest = 0;
+    if (rest < args.count) {
+        a.count = args.count - rest;
+        if (int rc = launch_wave(a, cus, stream)) return rc;
+    }
+    if (!rest) return TFHE_OK;
+    a.first = args.count - rest;
     a.count = args.count;
-    // Four gates per CU: two launches of two per CU, since the fourth gate of a single one would start when its CU's
-    // first three end and run alone.  Against the wave kernel, a call: 769 gates 5.33 -> 4.80 ms, 1,024 gates
-    // 5.36 -> 4.70 ms; behind a round, where the wave kernel's last workgroups went to whichever CU ended first,
-    // 3,072 gates 15.1 -> 12.8 ms.
-    if (wave_gates_from() < 0 && !resident_groups() && (a.count - a.first + cus - 1) / cus == 4) {
-        a.count = a.first + 2 * cus;
-        if (int rc = launch_four_waves(a, stream)) return rc;
-        a.first = a.count;
-        a.count = args.count;
-    }
-    return launch_four_waves(a, stream);
+    return kernel == RestKernel::kWave ? launch_wave(a, cus, stream) : launch_four_waves(a, stream);
 }
 
 int launch_ksk_to_tiles(const uint32_t *ksk, int stride, int words, void *tiles, hipStream_t stream) {
@@ -1361,7 +1368,7 @@ int launch_key_switch(const KeySwitchArgs &a, hipStream_t stream) {
         } else if (tiles == 2) {
             hipLaunchKernelGGL(key_switch_mfma_kernel<2>, grid, dim3(256), sizeof(KsLds<2>), stream, m);
         } else {
-            if (int rc = allow(6)) return rc;
+            if (int rc = allow(7)) return rc;
             hipLaunchKernelGGL(key_switch_mfma_kernel<4>, grid, dim3(256), sizeof(KsLds<4>), stream, m);
         }
         TFHE_HIP(hipGetLastError());
