@@ -38,9 +38,9 @@ struct KeySwitchArgs {
 // kernels and the scheduler of narrow circuits go by.
 //   wave kernel       eight gates per CU at a time: 6.4 ms a round, 4.1 ms with at most four per CU in it,
 //                     5.8 ms with five or six, 6.0 ms with seven
-//   four-wave kernel  1.55, 2.3 and 3.3 ms for one, two and three gates per CU, 5.5 ms for five
+//   four-wave kernels 1.55, 2.1 and 3.3 ms for one, two and three gates per CU, 5.5 ms for five
 inline double rest_ms(size_t per_cu) {      // a launch of less than a round
-    const double ms[9] = {0.0, 1.55, 2.26, 3.32, 4.13, 5.49, 5.81, 5.98, 6.42};
+    const double ms[9] = {0.0, 1.55, 2.1, 3.32, 4.13, 5.49, 5.81, 5.98, 6.42};
     return ms[per_cu];
 }
 // the kernel that serves a batch's last, partial round fastest: the wave kernel together with the whole rounds or in a launch of its

@@ -168,17 +168,18 @@ __device__ __forceinline__ Twiddle8 pass1_twiddles(const_double *u) {
 
 // A step's key values of one thread come in four parts of 8 (32 registers): part p = 2 q + h holds
 // rows r = 0..3 x outputs o = 2h, 2h+1 at the thread's slot 256 q + tid.
-// AHEAD: the latency variant (launches that leave one workgroup per CU) requests the whole key
-// row of step i + 1 while step i still runs, in eight portions of four loads placed between the
-// phases that follow the products of step i: a portion keeps the CU's one address unit busy for
-// 4 x 16 clocks per wave, and a wave alone on its SIMD cannot issue anything else meanwhile, so
-// portions issued back to back stall all four waves (measured on 64 gates: all 32 loads in one
-// place 2.06 ms, two places 1.82 ms, four 1.71 ms, eight 1.62 ms; no key traffic at all 1.50 ms).
-// At full occupancy other workgroups cover the loads and holding registers for them does not pay:
+// AHEAD: the variants for one or two workgroups per CU request the whole key row of step i + 1 while step i still runs, in
+// eight portions of four loads placed between the phases that follow the products of step i.
+// LONE: one workgroup per CU.  A portion keeps the CU's one address unit busy for 4 x 16 clocks per wave, and a wave alone
+// on its SIMD cannot issue anything else meanwhile, so portions issued back to back stall all four waves (measured on 64
+// gates: all 32 loads in one place 2.06 ms, two places 1.82 ms, four 1.71 ms, eight 1.62 ms; no key traffic at all 1.50 ms).
+// Two workgroups per CU hide that behind each other; there the last two portions go with earlier ones, a step's length
+// ahead of their use, which also saves the registers of the loads in flight across forward passes 2 and 3 (301 gates 1.96 -> 1.94 ms, and no scratch).
+// At three workgroups per CU the others cover the loads and holding registers for them does not pay:
 // with two parts kept in flight (registers freed by moving the pass-2 twiddles to LDS) a launch of
 // 65,536 gates took 390-410 ms instead of 266-278.  The wait for a key row that no workgroup of the
 // XCD has touched yet is what keeps the workgroups of an XCD within the few rows its L2 holds.
-template <bool MARGIN, int AHEAD>
+template <bool MARGIN, int AHEAD, bool LONE>
 __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     extern __shared__ __align__(4096) unsigned char lds_raw[];
     GateLds &my = *reinterpret_cast<GateLds *>(lds_raw);
@@ -186,7 +187,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
 
     // The accumulator's components: with their mirrors in the throughput kernel, 4 KB each from a multiple of
     // 4 KB on, without mirrors, in the latency kernel (see the rotation).
-    auto acc = [&](int c) -> uint32_t * { return AHEAD ? reinterpret_cast<uint32_t *>(lds_raw) + c * kN : my.acc[c]; };
+    auto acc = [&](int c) -> uint32_t * { return LONE ? reinterpret_cast<uint32_t *>(lds_raw) + c * kN : my.acc[c]; };
 
     const int tid = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave, in a scalar register
@@ -234,7 +235,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     // on swaps and key loads anyway, last.  Measured against one high level for all of the former: 301 gates
     // 2.23 -> 2.21 ms, 512 gates 2.29 -> 2.27, 768 gates 3.42 -> 3.34; raising the gather instead costs up to 30 %.
     auto priority = [](int level) {
-        if (AHEAD) return;               // a lone workgroup per CU has nobody to overtake
+        if (LONE) return;                // a lone workgroup per CU has nobody to overtake
         if (level == 2) __builtin_amdgcn_s_setprio(2);
         else if (level == 1) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
@@ -277,7 +278,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
             const uint32_t c = ~(j < kN - bb ? first : 0u - first);
             acc(0)[j] = ~0u;
             acc(1)[j] = c;
-            if (!AHEAD && j < kMirror) { my.acc[0][kN + j] = 0u - ~0u - 2u; my.acc[1][kN + j] = 0u - c - 2u; }
+            if (!LONE && j < kMirror) { my.acc[0][kN + j] = 0u - ~0u - 2u; my.acc[1][kN + j] = 0u - c - 2u; }
         }
     }
     __syncthreads();
@@ -323,7 +324,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         // and five scalar ones) and needs no mirror: bit 12 of a lane's own sum is its sign, the bits below are its
         // offset, and (c ^ flip) + flip is +-ACC - 1 for either flip.
         uint32_t from[8][2], flip[8][2], bias[8][2];
-        if (AHEAD) {
+        if (LONE) {
             uint32_t low12 = 4095u;
             asm("" : "+v"(low12));                   // in a vector register: one v_and_or_b32 takes no second constant
 #pragma unroll
@@ -353,27 +354,27 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         for (int m = 0; m < 8; ++m)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                rot[m][h] = *(lds_word *)(uintptr_t)(AHEAD ? from[m][h] : lane4 + from[m][h]);
+                rot[m][h] = *(lds_word *)(uintptr_t)(LONE ? from[m][h] : lane4 + from[m][h]);
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
             int32_t dig[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int j = L + 64 * m + h * kHalf;
-                const uint32_t turned = (rot[m][h] ^ flip[m][h]) + (AHEAD ? flip[m][h] : 0u);
+                const uint32_t turned = (rot[m][h] ^ flip[m][h]) + (LONE ? flip[m][h] : 0u);
                 const uint32_t d = turned + acc(comp)[j] + bias[m][h];
                 dig[h] = __builtin_amdgcn_sbfe((int32_t)d, dfield, (uint32_t)a.bgbit);    // signed field
             }
             x[m] = make_double2((double)dig[0], (double)dig[1]);
         }
         }
-        if (i > 0) load_ahead(i, 6);
+        if (LONE && i > 0) load_ahead(i, 6);
         {
             const_double *u = uniform_constants(a.tables);
             dft8_twiddled<false>(x, pass1_twiddles(u), [&](int k, double2 v) { poly[k * kRowStride + L] = v; }, pause);
         }
         __syncthreads();
-        if (i > 0) load_ahead(i, 7);
+        if (LONE && i > 0) load_ahead(i, 7);
 
         // ---- this wave's frequencies of all four polynomials ----
         priority(1);
@@ -437,6 +438,7 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         __syncthreads();
         abar_next = my.bar[i + 1];           // bar[n] exists (it holds bbar)
         load_ahead(next, 3);
+        if (!LONE) load_ahead(next, 6);
 
         // ---- inverse pass 1 of output polynomial o = wave, exact rounding, accumulate ----
         priority(2);
@@ -460,11 +462,12 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
                 if (sel) r <<= 16;
                 if (m == 3 && h == 1) load_ahead(next, 4);
                 atomicAdd(&acc(comp)[L + 64 * m + h * kHalf], r);
-                if (!AHEAD && m == 0 && h == 0) atomicSub(&my.acc[comp][kN + L], r);      // the mirror holds -c - 2
+                if (!LONE && m == 0 && h == 0) atomicSub(&my.acc[comp][kN + L], r);      // the mirror holds -c - 2
             }
         }
         __syncthreads();
         load_ahead(next, 5);
+        if (!LONE) load_ahead(next, 7);
     }
 
     // ---- epilogue: the constant coefficient as an LWE sample under the ring key ----
@@ -485,14 +488,22 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
 
 template <bool MARGIN>
 __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu(3, 3))) void blind_rotate_kernel(BlindRotateArgs a) {
-    blind_rotate_body<MARGIN, 0>(a);
+    blind_rotate_body<MARGIN, 0, false>(a);
+}
+
+// The same step for two gates per CU, where 256 registers a wave hold the key row of step i + 1 while step i runs.  With the
+// row loaded where it is used, the way from L2 costs a fifth of such a launch (512 gates 2.25 ms; 1.83 if every load hit L1, 2.25
+// if every one hit L2), and a third workgroup that would cover it is not there: 301 gates 2.20 -> 1.94 ms, 400 gates 2.30 -> 1.96, 512 gates
+// 2.25 -> 2.10 to 2.18.  Half of the row ahead: 2.29, 2.29, 2.33.  The priorities matter more here: without them 301 gates 2.42.
+__global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu(2, 2))) void blind_rotate_pair_kernel(BlindRotateArgs a) {
+    blind_rotate_body<false, 4, false>(a);
 }
 
 // The same step for batches of at most one gate per CU, where a gate's latency is all that
 // counts: the whole key row of step i + 1 is requested while step i still runs.
 template <bool MARGIN>
 __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu(1, 1))) void blind_rotate_latency_kernel(BlindRotateArgs a) {
-    blind_rotate_body<MARGIN, 4>(a);
+    blind_rotate_body<MARGIN, 4, true>(a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1173,6 +1184,15 @@ static int latency_batch_limit() {
     return limit;
 }
 
+// Largest batch that goes to the variant for two gates per compute unit.
+static int pair_batch_limit() {
+    static const int limit = [] {
+        if (const char *e = getenv("TFHE_PAIR_BATCH")) return atoi(e);
+        return 2 * latency_batch_limit();
+    }();
+    return limit;
+}
+
 // Upper bound on the workgroups of a launch of blind_rotate_kernel, 0 = none (one workgroup per gate, the
 // default).  With a bound -- three per CU is what stays resident -- each workgroup takes every
 // grid-th gate and all of them walk the key rows together from the first gate to the last.
@@ -1249,10 +1269,10 @@ int launch_bk_to_spectrum(const uint32_t *bk_raw, double2 *bk_fft, const double2
     return TFHE_OK;
 }
 
-// the seven blind-rotation kernels and the widest matrix-core key switch, with their
+// the eight blind-rotation kernels and the widest matrix-core key switch, with their
 // dynamic LDS sizes and per-device "attribute set" masks
 namespace {
-constexpr int kBigLdsKernels = 8;
+constexpr int kBigLdsKernels = 9;
 struct BigLdsKernel { const void *fn; size_t lds; std::atomic<uint64_t> done; };
 BigLdsKernel big_lds_kernels[kBigLdsKernels] = {
     {reinterpret_cast<const void *>(&blind_rotate_kernel<false>), sizeof(GateLds), {0}},
@@ -1262,6 +1282,7 @@ BigLdsKernel big_lds_kernels[kBigLdsKernels] = {
     {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false, true>), sizeof(WaveLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<true, true>), sizeof(WaveLds), {0}},
     {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false, false>), sizeof(WaveLds), {0}},
+    {reinterpret_cast<const void *>(&blind_rotate_pair_kernel), sizeof(GateLds), {0}},
     {reinterpret_cast<const void *>(&key_switch_mfma_kernel<4>), sizeof(KsLds<4>), {0}},
 };
 int allow(int which) { return allow_dynamic_lds(big_lds_kernels[which].fn, big_lds_kernels[which].lds, big_lds_kernels[which].done); }
@@ -1271,7 +1292,7 @@ int allow(int which) { return allow_dynamic_lds(big_lds_kernels[which].fn, big_l
 // device properties, the address of the static scratch), done once per device at key upload so
 // that later calls only launch.
 int prepare_kernels() {
-    (void)latency_batch_limit();
+    (void)pair_batch_limit();
     (void)resident_groups();
     (void)wave_gates_from();
     for (int k = 0; k < kBigLdsKernels; ++k)
@@ -1283,17 +1304,20 @@ int prepare_kernels() {
 static int launch_four_waves(const BlindRotateArgs &a, hipStream_t stream) {
     const size_t lds = sizeof(GateLds), items = a.count - a.first;
     const bool latency = items <= (size_t)latency_batch_limit();
-    if (int rc = allow((latency ? 2 : 0) + (a.margin ? 1 : 0))) return rc;
+    const bool pair = !latency && !a.margin && items <= (size_t)pair_batch_limit();
+    if (int rc = allow(pair ? 7 : (latency ? 2 : 0) + (a.margin ? 1 : 0))) return rc;
+    const dim3 block(kThreadsPerGate);
     if (latency) {
-        // at most one gate per CU: the variant that requests each key row a step ahead
         const dim3 grid((unsigned)items);
-        if (a.margin) hipLaunchKernelGGL(blind_rotate_latency_kernel<true>, grid, dim3(kThreadsPerGate), lds, stream, a);
-        else hipLaunchKernelGGL(blind_rotate_latency_kernel<false>, grid, dim3(kThreadsPerGate), lds, stream, a);
+        if (a.margin) hipLaunchKernelGGL(blind_rotate_latency_kernel<true>, grid, block, lds, stream, a);
+        else hipLaunchKernelGGL(blind_rotate_latency_kernel<false>, grid, block, lds, stream, a);
+    } else if (pair) {
+        hipLaunchKernelGGL(blind_rotate_pair_kernel, dim3((unsigned)items), block, lds, stream, a);
     } else {
         const size_t bound = (size_t)resident_groups();
         const dim3 grid((unsigned)(bound ? std::min(items, bound) : items));
-        if (a.margin) hipLaunchKernelGGL(blind_rotate_kernel<true>, grid, dim3(kThreadsPerGate), lds, stream, a);
-        else hipLaunchKernelGGL(blind_rotate_kernel<false>, grid, dim3(kThreadsPerGate), lds, stream, a);
+        if (a.margin) hipLaunchKernelGGL(blind_rotate_kernel<true>, grid, block, lds, stream, a);
+        else hipLaunchKernelGGL(blind_rotate_kernel<false>, grid, block, lds, stream, a);
     }
     TFHE_HIP(hipGetLastError());
     return TFHE_OK;
@@ -1368,7 +1392,7 @@ int launch_key_switch(const KeySwitchArgs &a, hipStream_t stream) {
         } else if (tiles == 2) {
             hipLaunchKernelGGL(key_switch_mfma_kernel<2>, grid, dim3(256), sizeof(KsLds<2>), stream, m);
         } else {
-            if (int rc = allow(7)) return rc;
+            if (int rc = allow(8)) return rc;
             hipLaunchKernelGGL(key_switch_mfma_kernel<4>, grid, dim3(256), sizeof(KsLds<4>), stream, m);
         }
         TFHE_HIP(hipGetLastError());
