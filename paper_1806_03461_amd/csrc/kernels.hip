@@ -561,8 +561,10 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
     WaveLds &my = *reinterpret_cast<WaveLds *>(lds_raw);
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int L = threadIdx.x & 63;
-    const size_t slot = a.first + (size_t)blockIdx.x * kWaveGates + wv;
-    const size_t gi = slot < a.count ? slot : a.count - 1;      // a wave without a gate repeats the last one and writes nothing
+    // the items are spread evenly over the workgroups, at most one a wave
+    const size_t items = a.count - a.first, begin = a.first + items * blockIdx.x / gridDim.x;
+    const size_t end = a.first + items * (blockIdx.x + 1) / gridDim.x;
+    const size_t gi = begin + wv;
     uint32_t (&acc)[2][kN + kMirror] = my.acc[wv];
     double2 *const buf = my.buf[wv];
     double2 *const mine = buf + (L >> 3) * kRowStride;          // passes 2, 3: lane = 8 k0 + (j0 or k1)
@@ -576,6 +578,8 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         const_cast<double2 *>(a.bk_fft + (size_t)a.n * 16 * kHalf), 0, (int)((size_t)a.n * 4 * kSums * kHalf * sizeof(double2)), 0x00020000);
     const uint32_t voff = (uint32_t)wave_slot_lane(L) * (uint32_t)sizeof(double2);
     double worst = 0.0;
+    __syncthreads();
+    if (gi >= end) return;            // a wave without a gate: the barriers below wait for the others only
 
     int op = a.uniform_op;
     size_t i0 = gi, i1 = gi;
@@ -610,7 +614,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             if (j < kMirror) { acc[0][kN + j] = 0u - ~0u - 2u; acc[1][kN + j] = 0u - c - 2u; }
         }
     }
-    __syncthreads();
+    wave_sync();
 
     const uint32_t dround = 1u << (31 - 2 * a.bgbit), dhalf = 1u << (31 - a.bgbit);
     const uint32_t field0 = (uint32_t)(32 - a.bgbit), field1 = (uint32_t)(32 - 2 * a.bgbit);
@@ -863,11 +867,9 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         }
     }
 
-    if (slot < a.count) {
-        uint32_t *ext = a.ext + gi * (size_t)(kN + 1);
-        for (int j = L; j < kN; j += 64) ext[j] = j == 0 ? ~acc[0][0] : acc[0][kN - j] + 1u;
-        if (L == 0) ext[kN] = ~acc[1][0];
-    }
+    uint32_t *ext = a.ext + gi * (size_t)(kN + 1);
+    for (int j = L; j < kN; j += 64) ext[j] = j == 0 ? ~acc[0][0] : acc[0][kN - j] + 1u;
+    if (L == 0) ext[kN] = ~acc[1][0];
     if (MARGIN)
         atomicMax(reinterpret_cast<unsigned long long *>(a.margin), (unsigned long long)__double_as_longlong(worst));
 }
@@ -1328,11 +1330,15 @@ static_assert(kRoundPerCu == 2 * kWaveGates, "two workgroups of the wave kernel 
 // Items first .. count - 1 with the wave kernel.  With more than one workgroup per CU the waves of a workgroup meet before the
 // products, so that their key reads hit L1 (8,192 gates 26.0 -> 25.2 ms); a lone workgroup leaves L1 and L2 idle enough
 // and loses by waiting (1,024 gates 4.15 ms without, 4.54 with).
+// Five or six gates per CU are spread over two workgroups on every CU instead of filling half of the CUs with two whole ones:
+// 1,025 gates 5.65 -> 5.3 ms, 1,536 gates 5.82 -> 5.44.  Seven are not: the CUs that end early leave the others their power
+// (1,554 gates 6.0 ms as they are, 6.2 spread).
 static int launch_wave(const BlindRotateArgs &a, size_t cus, hipStream_t stream) {
     const size_t items = a.count - a.first;
     const int which = a.margin ? 5 : items > kWaveGates * cus ? 4 : 6;
     if (int rc = allow(which)) return rc;
-    const dim3 grid((unsigned)((items + kWaveGates - 1) / kWaveGates)), block(64 * kWaveGates);
+    const size_t least = (items + kWaveGates - 1) / kWaveGates;
+    const dim3 grid((unsigned)(items > kWaveGates * cus && items <= 6 * cus ? 2 * cus : least)), block(64 * kWaveGates);
     if (which == 5) hipLaunchKernelGGL((blind_rotate_wave_kernel<true, true>), grid, block, sizeof(WaveLds), stream, a);
     else if (which == 4) hipLaunchKernelGGL((blind_rotate_wave_kernel<false, true>), grid, block, sizeof(WaveLds), stream, a);
     else hipLaunchKernelGGL((blind_rotate_wave_kernel<false, false>), grid, block, sizeof(WaveLds), stream, a);
@@ -1340,16 +1346,16 @@ static int launch_wave(const BlindRotateArgs &a, size_t cus, hipStream_t stream)
     return TFHE_OK;
 }
 
-// Whole rounds go to the wave kernel, and what remains follows on the kernel that serves it fastest (times in kernels.h): six
-// or seven gates per CU in the same launch, four in one of their own (behind the rounds of the same launch their workgroups would
-// go to whichever CU ended first, two to some), other numbers on the four-wave kernels.
+// Whole rounds go to the wave kernel, and what remains follows on the kernel that serves it fastest (times in kernels.h): seven
+// gates per CU in the same launch, four to six in one of their own (behind the rounds of the same launch their workgroups would
+// go to whichever CU ended first), fewer on the four-wave kernels.
 int launch_blind_rotate(const BlindRotateArgs &args, hipStream_t stream) {
     if (args.count == 0) return TFHE_OK;
     BlindRotateArgs a = args;
     a.first = 0;
     const size_t cus = device_cus() > 0 ? (size_t)device_cus() : 256;
     size_t rest = a.count % (kRoundPerCu * cus);
-    RestKernel kernel = rest_kernel((rest + cus - 1) / cus);
+    RestKernel kernel = rest_kernel((rest + cus - 1) / cus, rest < a.count);
     if (wave_gates_from() >= 0) {
         kernel = a.count >= (size_t)wave_gates_from() ? RestKernel::kWithRounds : RestKernel::kFourWaves;
         rest = a.count;
