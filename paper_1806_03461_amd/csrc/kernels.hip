@@ -147,7 +147,7 @@ __device__ __forceinline__ double2 load_key(__amdgpu_buffer_rsrc_t rsrc, uint32_
     return out;
 }
 
-// The constants that are the same in every lane come through the scalar cache once a step (the pointer is
+// The constants that are the same in every lane come through the scalar cache, in most kernels once a step (the pointer is
 // made opaque, or the compiler keeps all of them in scalar registers over the loop and spills).
 typedef __attribute__((address_space(4))) const double const_double;
 __device__ __forceinline__ const_double *uniform_constants(const double2 *tables) {
@@ -207,6 +207,14 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     for (int q = 0; q < 3; ++q) i1[q] = a.tables[kInv1 + (5 + q) * 64 + L];
     for (int e = tid; e < 5 * 64; e += kThreadsPerGate) my.inv1[e] = a.tables[kInv1 + e];
     auto pause = [] { __builtin_amdgcn_sched_barrier(0); };
+    // The constants that are the same in every lane.  With one or two workgroups per CU nobody covers the waits for them, which
+    // also wait for every LDS read in flight: forward pass 1 keeps its own over the loop, and a lone workgroup, whose rotation
+    // needs no scalar registers, the cosines of the rounding too (8 gates 1.555 -> 1.53 ms a call; 301 gates 2.02 -> 1.975, 512 gates
+    // 2.32 -> 2.21; there with the cosines 2.02 and 2.26).
+    const_double *const kept = uniform_constants(a.tables);
+    const Twiddle8 kept_w1 = pass1_twiddles(kept);
+    double kept_cos[8];
+    for (int m = 1; m < 8; ++m) kept_cos[m] = kept[16 + m];
     const __amdgpu_buffer_rsrc_t key_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<double2 *>(a.bk_fft), 0, (int)((size_t)a.n * 16 * kHalf * sizeof(double2)), 0x00020000);
     const uint32_t voff = (uint32_t)tid * (uint32_t)sizeof(double2);
@@ -370,8 +378,8 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         }
         if (LONE && i > 0) load_ahead(i, 6);
         {
-            const_double *u = uniform_constants(a.tables);
-            dft8_twiddled<false>(x, pass1_twiddles(u), [&](int k, double2 v) { poly[k * kRowStride + L] = v; }, pause);
+            const Twiddle8 w1 = AHEAD ? kept_w1 : pass1_twiddles(uniform_constants(a.tables));
+            dft8_twiddled<false>(x, w1, [&](int k, double2 v) { poly[k * kRowStride + L] = v; }, pause);
         }
         __syncthreads();
         if (LONE && i > 0) load_ahead(i, 7);
@@ -446,19 +454,22 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         for (int k = 0; k < 8; ++k) x[k] = poly[k * kRowStride + L];
         x[0] = cmul(x[0], p[7]);
         dft8_twiddled<true>(x, unpack_twiddles(p));
-        const_double *u = uniform_constants(a.tables);
+        const_double *u = AHEAD ? kept : uniform_constants(a.tables);
+        double tan_m[8], cos_m[8];
+#pragma unroll
+        for (int m = 1; m < 8; ++m) { tan_m[m] = AHEAD ? kept_w1.t[m] : u[m]; cos_m[m] = LONE ? kept_cos[m] : u[16 + m]; }
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
-            if (m) x[m] = cturn(x[m], -u[m]);
+            if (m) x[m] = cturn(x[m], -tan_m[m]);
             const double part[2] = {x[m].x, x[m].y};
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 // 1.5 * 2^52 - value leaves round-to-nearest(-value) = -round(value) mod 2^32 in the low word (ties
                 // go to even either way); the complemented accumulator takes it: ~(ACC + r) = ~ACC - r.
                 // The value's pending cosine rides in the multiply-add, so it is rounded once.
-                const double shifted = m ? fma(-u[16 + m], part[h], 6755399441055744.0) : 6755399441055744.0 - part[h];
+                const double shifted = m ? fma(-cos_m[m], part[h], 6755399441055744.0) : 6755399441055744.0 - part[h];
                 uint32_t r = (uint32_t)__double2loint(shifted);
-                if (MARGIN) worst = fmax(worst, fabs((m ? u[16 + m] * part[h] : part[h]) + (shifted - 6755399441055744.0)));
+                if (MARGIN) worst = fmax(worst, fabs((m ? cos_m[m] * part[h] : part[h]) + (shifted - 6755399441055744.0)));
                 if (sel) r <<= 16;
                 if (m == 3 && h == 1) load_ahead(next, 4);
                 atomicAdd(&acc(comp)[L + 64 * m + h * kHalf], r);
