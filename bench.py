@@ -34,9 +34,10 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 # Algorithmic double-precision work of one bootstrapped gate on this path (n = 500 steps):
-# per step 8 complex 512-point FFTs at the conventional 5 N log2 N flops, 8 x 512 complex
-# twist / untwist multiplications (6 flops), 16 x 512 complex multiply-accumulates (8 flops).
-FLOPS_PER_STEP = 8 * 5 * 512 * 9 + 8 * 512 * 6 + 16 * 512 * 8
+# per step 7 complex 512-point FFTs at the conventional 5 N log2 N flops, 7 x 512 complex
+# twist / untwist multiplications (6 flops), 12 x 512 complex multiply-accumulates (8 flops).
+# That is the wave kernel's step; the few gates on the four-wave kernels, with 8 and 16, count the same.
+FLOPS_PER_STEP = 7 * 5 * 512 * 9 + 7 * 512 * 6 + 12 * 512 * 8
 FP64_VECTOR_PEAK_TFLOPS = 78.6
 HBM_PEAK_GBPS = 8000.0
 INT8_MATRIX_PEAK_POPS = 5.0
@@ -268,7 +269,7 @@ def main():
 
     # ---- roofline of the dominant work: algorithmic flops of the gates of one batch over the average
     # duration of its blind rotation, from HIP events recorded around every batch on the call's stream.  A batch is
-    # one to three launches: its whole rounds on the wave kernel, its remainder on the four-wave kernels. ----
+    # one or two launches: its whole rounds on the wave kernel, its remainder on the kernel that serves it fastest. ----
     br_batches = max(1, prof["blind_rotate_launches"])
     br_avg_ms = prof["blind_rotate_ms"] / br_batches
     gates_per_batch = prof["gates"] / br_batches            # blind rotations per batch
@@ -293,7 +294,7 @@ def main():
     roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP64_VECTOR_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / FP64_VECTOR_PEAK_TFLOPS, 4),
                 "traffic": traffic, "kernel": "blind rotation of a batch (blind_rotate_wave_kernel for whole rounds of 8 gates "
-                "per CU and remainders above 5, blind_rotate_kernel and blind_rotate_latency_kernel for smaller ones)",
+                "per CU and remainders of 4 or more, blind_rotate_latency_kernel, blind_rotate_pair_kernel, blind_rotate_kernel for 1, 2, 3)",
                 "avg_batch_ms": round(br_avg_ms, 4), "gates_per_batch": round(gates_per_batch, 1),
                 "flops_per_gate": flops_per_gate,
                 "peak_measured": round(measured_peak, 2),
