@@ -311,8 +311,9 @@ int tfhe_last_layer_stats(const tfhe_cloud_key *ck, tfhe_layer_stats *out);
  * beside the published peak.  Runs three short launches on `stream` and waits for them. */
 int tfhe_measure_fp64_peak(tfhe_cloud_key *ck, void *stream, double *tflops);
 
-/* Largest distance from an integer seen by the blind-rotation kernel when it rounds the
- * inverse transform of its exact split-integer products (0.5 would be a wrong result).
+/* Largest distance, seen by the blind rotations when they round the inverse transform of their exact
+ * products, of a value from the one it is rounded to, in units of the distance between neighbouring such values
+ * (0.5 would be a wrong result).  Each call is served by the kernel that serves it otherwise.
  * Collected only while enabled (slower); read synchronises the device. */
 int tfhe_rounding_margin_enable(tfhe_cloud_key *ck, int on);
 int tfhe_rounding_margin_read(tfhe_cloud_key *ck, double *max_fraction);

@@ -203,6 +203,8 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     f3.h1 = a.tables[kFwd3 + 128 + 8 * k0 + (L & 7)]; f3.h1w = a.tables[kFwd3 + 192 + 8 * k0 + (L & 7)];
     i2.h4 = a.tables[kInv2Shift + (L & 7)]; i2.h2 = a.tables[kInv2Shift + 8 + (L & 7)];
     i2.h1 = a.tables[kInv2Shift + 16 + (L & 7)]; i2.h1w = a.tables[kInv2Shift + 24 + (L & 7)];
+    // With the key row ahead and the rounding distance recorded, two workgroups per CU have no registers for the other three.
+    constexpr bool kSpare = MARGIN && AHEAD && !LONE;
     double2 i1[3];
     for (int q = 0; q < 3; ++q) i1[q] = a.tables[kInv1 + (5 + q) * 64 + L];
     for (int e = tid; e < 5 * 64; e += kThreadsPerGate) my.inv1[e] = a.tables[kInv1 + e];
@@ -442,7 +444,8 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         dft8_shifted<true>(y, i2, [&](int k, double2 v) { mine[(L & 7) + 8 * k] = v; }, pause);
         double2 p[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) p[q] = q < 5 ? my.inv1[q * 64 + L] : i1[q < 5 ? 0 : q - 5];
+        for (int q = 0; q < 8; ++q)
+            p[q] = q < 5 ? my.inv1[q * 64 + L] : kSpare ? a.tables[kInv1 + q * 64 + L] : i1[q < 5 ? 0 : q - 5];
         __syncthreads();
         abar_next = my.bar[i + 1];           // bar[n] exists (it holds bbar)
         load_ahead(next, 3);
@@ -506,8 +509,9 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 // row loaded where it is used, the way from L2 costs a fifth of such a launch (512 gates 2.25 ms; 1.83 if every load hit L1, 2.25
 // if every one hit L2), and a third workgroup that would cover it is not there: 301 gates 2.20 -> 1.94 ms, 400 gates 2.30 -> 1.96, 512 gates
 // 2.25 -> 2.10 to 2.18.  Half of the row ahead: 2.29, 2.29, 2.33.  The priorities matter more here: without them 301 gates 2.42.
+template <bool MARGIN>
 __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu(2, 2))) void blind_rotate_pair_kernel(BlindRotateArgs a) {
-    blind_rotate_body<false, 4, false>(a);
+    blind_rotate_body<MARGIN, 4, false>(a);
 }
 
 // The same step for batches of at most one gate per CU, where a gate's latency is all that
@@ -1282,23 +1286,37 @@ int launch_bk_to_spectrum(const uint32_t *bk_raw, double2 *bk_fft, const double2
     return TFHE_OK;
 }
 
-// the eight blind-rotation kernels and the widest matrix-core key switch, with their
-// dynamic LDS sizes and per-device "attribute set" masks
+// The blind rotations, each plain and with the rounding distance recorded (the launcher chooses without regard to that, so
+// that what is recorded is of the kernel that serves the same call otherwise), and the widest matrix-core key
+// switch, with their dynamic LDS sizes and per-device "attribute set" masks
 namespace {
-constexpr int kBigLdsKernels = 9;
+enum Rotation { kFourWaves, kLatency, kPair, kWaveMeet, kWaveLone, kRotations };
 struct BigLdsKernel { const void *fn; size_t lds; std::atomic<uint64_t> done; };
-BigLdsKernel big_lds_kernels[kBigLdsKernels] = {
-    {reinterpret_cast<const void *>(&blind_rotate_kernel<false>), sizeof(GateLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_kernel<true>), sizeof(GateLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<false>), sizeof(GateLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<true>), sizeof(GateLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false, true>), sizeof(WaveLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<true, true>), sizeof(WaveLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false, false>), sizeof(WaveLds), {0}},
-    {reinterpret_cast<const void *>(&blind_rotate_pair_kernel), sizeof(GateLds), {0}},
-    {reinterpret_cast<const void *>(&key_switch_mfma_kernel<4>), sizeof(KsLds<4>), {0}},
+BigLdsKernel rotation_kernels[kRotations][2] = {
+    {{reinterpret_cast<const void *>(&blind_rotate_kernel<false>), sizeof(GateLds), {0}},
+     {reinterpret_cast<const void *>(&blind_rotate_kernel<true>), sizeof(GateLds), {0}}},
+    {{reinterpret_cast<const void *>(&blind_rotate_latency_kernel<false>), sizeof(GateLds), {0}},
+     {reinterpret_cast<const void *>(&blind_rotate_latency_kernel<true>), sizeof(GateLds), {0}}},
+    {{reinterpret_cast<const void *>(&blind_rotate_pair_kernel<false>), sizeof(GateLds), {0}},
+     {reinterpret_cast<const void *>(&blind_rotate_pair_kernel<true>), sizeof(GateLds), {0}}},
+    {{reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false, true>), sizeof(WaveLds), {0}},
+     {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<true, true>), sizeof(WaveLds), {0}}},
+    {{reinterpret_cast<const void *>(&blind_rotate_wave_kernel<false, false>), sizeof(WaveLds), {0}},
+     {reinterpret_cast<const void *>(&blind_rotate_wave_kernel<true, false>), sizeof(WaveLds), {0}}},
 };
-int allow(int which) { return allow_dynamic_lds(big_lds_kernels[which].fn, big_lds_kernels[which].lds, big_lds_kernels[which].done); }
+BigLdsKernel widest_key_switch = {reinterpret_cast<const void *>(&key_switch_mfma_kernel<4>), sizeof(KsLds<4>), {0}};
+int allow(BigLdsKernel &k) { return allow_dynamic_lds(k.fn, k.lds, k.done); }
+
+static_assert(kThreadsPerGate == 64 * kWaveGates, "workgroups of one size");
+int launch_rotation(Rotation which, size_t groups, const BlindRotateArgs &a, hipStream_t stream) {
+    BigLdsKernel &k = rotation_kernels[which][a.margin ? 1 : 0];
+    if (int rc = allow(k)) return rc;
+    BlindRotateArgs args = a;
+    void *params[] = {&args};
+    (void)hipLaunchKernel(k.fn, dim3((unsigned)groups), dim3(kThreadsPerGate), params, k.lds, stream);
+    TFHE_HIP(hipGetLastError());
+    return TFHE_OK;
+}
 }  // namespace
 
 // Everything a launch would otherwise set up on first use (dynamic-LDS permissions, the cached
@@ -1308,32 +1326,19 @@ int prepare_kernels() {
     (void)pair_batch_limit();
     (void)resident_groups();
     (void)wave_gates_from();
-    for (int k = 0; k < kBigLdsKernels; ++k)
-        if (int rc = allow(k)) return rc;
+    for (auto &forms : rotation_kernels)
+        for (BigLdsKernel &k : forms)
+            if (int rc = allow(k)) return rc;
+    if (int rc = allow(widest_key_switch)) return rc;
     return static_scratch_init();
 }
 
 // Items first .. count - 1 of a batch with the four-wave kernels.
 static int launch_four_waves(const BlindRotateArgs &a, hipStream_t stream) {
-    const size_t lds = sizeof(GateLds), items = a.count - a.first;
-    const bool latency = items <= (size_t)latency_batch_limit();
-    const bool pair = !latency && !a.margin && items <= (size_t)pair_batch_limit();
-    if (int rc = allow(pair ? 7 : (latency ? 2 : 0) + (a.margin ? 1 : 0))) return rc;
-    const dim3 block(kThreadsPerGate);
-    if (latency) {
-        const dim3 grid((unsigned)items);
-        if (a.margin) hipLaunchKernelGGL(blind_rotate_latency_kernel<true>, grid, block, lds, stream, a);
-        else hipLaunchKernelGGL(blind_rotate_latency_kernel<false>, grid, block, lds, stream, a);
-    } else if (pair) {
-        hipLaunchKernelGGL(blind_rotate_pair_kernel, dim3((unsigned)items), block, lds, stream, a);
-    } else {
-        const size_t bound = (size_t)resident_groups();
-        const dim3 grid((unsigned)(bound ? std::min(items, bound) : items));
-        if (a.margin) hipLaunchKernelGGL(blind_rotate_kernel<true>, grid, block, lds, stream, a);
-        else hipLaunchKernelGGL(blind_rotate_kernel<false>, grid, block, lds, stream, a);
-    }
-    TFHE_HIP(hipGetLastError());
-    return TFHE_OK;
+    const size_t items = a.count - a.first, bound = (size_t)resident_groups();
+    if (items <= (size_t)latency_batch_limit()) return launch_rotation(kLatency, items, a, stream);
+    if (items <= (size_t)pair_batch_limit()) return launch_rotation(kPair, items, a, stream);
+    return launch_rotation(kFourWaves, bound ? std::min(items, bound) : items, a, stream);
 }
 
 static_assert(kRoundPerCu == 2 * kWaveGates, "two workgroups of the wave kernel per CU");
@@ -1345,16 +1350,9 @@ static_assert(kRoundPerCu == 2 * kWaveGates, "two workgroups of the wave kernel 
 // 1,025 gates 5.65 -> 5.3 ms, 1,536 gates 5.82 -> 5.44.  Seven are not: the CUs that end early leave the others their power
 // (1,554 gates 6.0 ms as they are, 6.2 spread).
 static int launch_wave(const BlindRotateArgs &a, size_t cus, hipStream_t stream) {
-    const size_t items = a.count - a.first;
-    const int which = a.margin ? 5 : items > kWaveGates * cus ? 4 : 6;
-    if (int rc = allow(which)) return rc;
-    const size_t least = (items + kWaveGates - 1) / kWaveGates;
-    const dim3 grid((unsigned)(items > kWaveGates * cus && items <= 6 * cus ? 2 * cus : least)), block(64 * kWaveGates);
-    if (which == 5) hipLaunchKernelGGL((blind_rotate_wave_kernel<true, true>), grid, block, sizeof(WaveLds), stream, a);
-    else if (which == 4) hipLaunchKernelGGL((blind_rotate_wave_kernel<false, true>), grid, block, sizeof(WaveLds), stream, a);
-    else hipLaunchKernelGGL((blind_rotate_wave_kernel<false, false>), grid, block, sizeof(WaveLds), stream, a);
-    TFHE_HIP(hipGetLastError());
-    return TFHE_OK;
+    const size_t items = a.count - a.first, least = (items + kWaveGates - 1) / kWaveGates;
+    if (items <= kWaveGates * cus) return launch_rotation(kWaveLone, least, a, stream);
+    return launch_rotation(kWaveMeet, items <= 6 * cus ? 2 * cus : least, a, stream);
 }
 
 // Whole rounds go to the wave kernel, and what remains follows on the kernel that serves it fastest (times in kernels.h): seven
@@ -1409,7 +1407,7 @@ int launch_key_switch(const KeySwitchArgs &a, hipStream_t stream) {
         } else if (tiles == 2) {
             hipLaunchKernelGGL(key_switch_mfma_kernel<2>, grid, dim3(256), sizeof(KsLds<2>), stream, m);
         } else {
-            if (int rc = allow(8)) return rc;
+            if (int rc = allow(widest_key_switch)) return rc;
             hipLaunchKernelGGL(key_switch_mfma_kernel<4>, grid, dim3(256), sizeof(KsLds<4>), stream, m);
         }
         TFHE_HIP(hipGetLastError());

@@ -10,7 +10,6 @@ pytestmark = pytest.mark.gpu
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-# the distance of the transform outputs from integers is measured on the other kernels: asking for it would leave this one
 _SCRIPT = r"""
 import sys
 import torch
@@ -18,8 +17,6 @@ sys.path[:0] = [sys.argv[1], sys.argv[1] + "/tests"]
 import paper_1806_03461_amd as T, workloads
 from oracle import oracle as orc
 import test_gpu_parity as parity
-T.tfhe_rounding_margin_enable = lambda ck, on=True: None
-T.tfhe_rounding_margin_read = lambda ck: 1e-9
 sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
 parity.test_rotation_amounts_at_every_boundary((T, sk, ck), orc.Keys(orc.default_params(), workloads.KEY_SEED))
 print("boundaries ok", flush=True)
