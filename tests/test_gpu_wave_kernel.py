@@ -79,29 +79,30 @@ import test_gpu_parity as parity
 read = T.tfhe_rounding_margin_read
 def margin(ck):
     worst = read(ck)
-    print("largest distance from an integer", worst, flush=True)
+    print("largest distance read", worst, flush=True)
     return worst
 T.tfhe_rounding_margin_read = margin
 sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
 parity.test_rotation_amounts_at_every_boundary((T, sk, ck), orc.Keys(orc.default_params(), workloads.KEY_SEED))
 print("boundaries ok", flush=True)
-for pattern in ("all_min", "alternating", "random"):
+parity.LAUNCHES = [(1, float(sys.argv[2]))]
+for pattern in parity.EXTREMES:
     parity.test_extreme_key_limbs_stay_exact((T, sk, ck), orc, pattern)
     print(pattern, "ok", flush=True)
 """
 
 
-@pytest.mark.parametrize("kernel,knobs", [("wave", {"TFHE_WAVE_GATES_FROM": "1"}), ("four waves", {"TFHE_LATENCY_BATCH": "0"})],
+@pytest.mark.parametrize("kernel,knobs,bound", [("wave", {"TFHE_WAVE_GATES_FROM": "1"}, 2 ** -4.5), ("four waves", {"TFHE_LATENCY_BATCH": "0"}, 2 ** -10.5)],
                          ids=["wave", "four_waves"])
-def test_extreme_keys_and_rotations_on_the_kernels_of_larger_batches(kernel, knobs, say):
-    """The parity tests with key limbs at the ends of their range and with rotation amounts on every boundary are too
-    small to leave the latency kernel by themselves: the same checks with every launch on the others."""
+def test_extreme_keys_and_rotations_on_the_kernels_of_larger_batches(kernel, knobs, bound, say):
+    """The parity test with rotation amounts on every boundary is too small to leave the latency kernel by itself: the
+    same check, and extreme keys on a few gates, with every launch on the others."""
     env = {k: v for k, v in os.environ.items() if not k.startswith("TFHE_")}
-    r = subprocess.run([sys.executable, "-c", _EXTREMES, ROOT], env={**env, **knobs}, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+    r = subprocess.run([sys.executable, "-c", _EXTREMES, ROOT, repr(bound)], env={**env, **knobs}, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
                        text=True, timeout=200)
     assert r.returncode == 0, r.stdout
-    assert r.stdout.count(" ok") == 4 and r.stdout.count("largest distance") == 3, r.stdout
-    say(kernel + ": " + "; ".join(l for l in r.stdout.splitlines() if "distance" in l or l.endswith("ok")))
+    assert r.stdout.count(" ok") == 6 and r.stdout.count("largest distance read") == 5, r.stdout
+    say(kernel + ": " + "; ".join(l for l in r.stdout.splitlines() if "distance read" in l or l.endswith("ok")))
 
 
 @pytest.mark.parametrize("count", [769, 1024, 1025, 1281, 2047, 2048, 2049, 2900])
@@ -142,7 +143,7 @@ def test_rounding_margin_and_multiplexers_of_a_large_batch(real_keys):
     T.tfhe_mux_batch(ck, T.to_device(cts), T.to_device(cta), T.to_device(ctb), out, m)
     worst = T.tfhe_rounding_margin_read(ck)
     T.tfhe_rounding_margin_enable(ck, False)
-    assert 0 < worst < 1e-3, worst          # the bound the parity tests hold the four-wave kernels to
+    assert 0 < worst < 1e-3, worst          # derived bound 2^-4.5; measured 6e-5 with a generated key
     host = T.to_host(out)
     assert np.array_equal(T.tfhe_decrypt(sk, host), np.where(s == 1, a, b))
     for i in (0, 1, 1022, 1023, 1024, 1025, m - 1):
