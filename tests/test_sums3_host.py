@@ -23,6 +23,11 @@ def test_three_sums_give_the_product_on_the_host(tmp_path):
     assert r.returncode == 0, r.stdout
     # 10 u log2(512) times the operands' norms, with factors of 22 bits (low) and 21 bits (top); a wrong rounding needs 0.5
     seen = re.findall(r"wrong 0 distance low (\S+) top (\S+) (\S+)", r.stdout)
+    random = re.findall(r"random +wrong 0 distance low (\S+) top (\S+) (\S+)", r.stdout)
     assert len(seen) == r.stdout.count("distance") >= 30, r.stdout
     assert max(float(v[0]) for v in seen) < 2 ** -4.5, r.stdout
     assert max(float(x) for v in seen for x in v[1:]) < 2 ** -5.5, r.stdout
+    # the largest that csrc/sums3.h quotes, from random operands and from all of them
+    for runs, low, top in ((random, 3.5e-5, 1.8e-5), (seen, 3.5e-3, 1.8e-3)):
+        assert max(float(v[0]) for v in runs) <= low, r.stdout
+        assert max(float(x) for v in runs for x in v[1:]) <= top, r.stdout
