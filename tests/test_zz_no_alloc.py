@@ -49,11 +49,11 @@ def test_noalloc_entry_point_equals_gate_batch_on_successive_calls():
     T.tfhe_gate_batch_noalloc(ck, "AND", 0, 0, 0, 0)          # count 0: no-op
 
 
-@pytest.mark.parametrize("count", [5, 300, 900, 2500])
+@pytest.mark.parametrize("count", [5, 300, 600, 900, 1100, 2500, 3200])
 def test_noalloc_entry_point_under_graph_capture(count):
-    """A captured call -- on the latency kernel, the four-wave kernel, two launches of it, a round of the wave
-    kernel with a remainder -- replayed on new inputs with eager calls between: every replay gives the bytes of
-    the eager call."""
+    """A captured call -- on the kernels for one, two and three gates per CU, on the wave kernel with one workgroup per CU
+    and spread over two, on a round of it with two and with five gates per CU behind (the kernels for two and three) --
+    replayed on new inputs with eager calls between: every replay gives the bytes of the eager call."""
     import torch
     import paper_1806_03461_amd as T
     sk, ck = T.tfhe_keygen(T.default_params(), workloads.KEY_SEED)
