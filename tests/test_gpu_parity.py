@@ -402,8 +402,8 @@ def test_measured_fp64_ceiling_is_plausible(gpu):
 def test_kernel_choices_do_not_change_results(gpu):
     """The same calls give the same bytes whichever kernels serve them: the default process (launches
     this small: latency variant of the blind rotation, matrix-core key switch with split mask words);
-    every launch sent to the throughput kernel, with one workgroup per gate and with at most 5
-    workgroups (each then walks several gates, the last ones fewer than the first); every launch on
+    every launch on the kernel for two gates per CU; every launch sent to the throughput kernel, with one
+    workgroup per gate and with at most 5 workgroups (each then walks several gates, the last ones fewer than the first); every launch on
     the kernel that keeps one gate per wavefront; the gather key
     switch at the benchmark parameters, with a gate's mask words split over workgroups and not; layer
     calls that evaluate their units in groups of at most 300 estimated gates (two or three units)."""
@@ -411,11 +411,12 @@ def test_kernel_choices_do_not_change_results(gpu):
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     digests = []
     for knobs in ({}, {"TFHE_LATENCY_BATCH": "0", "TFHE_RESIDENT_GROUPS": "5"}, {"TFHE_LATENCY_BATCH": "0"},
-                  {"TFHE_WAVE_GATES_FROM": "1"}, {"TFHE_KS_MATRIX_FROM": "0"}, {"TFHE_KS_MATRIX_FROM": "0", "TFHE_KS_SPLITS": "1"},
+                  {"TFHE_LATENCY_BATCH": "0", "TFHE_PAIR_BATCH": "1000000"}, {"TFHE_WAVE_GATES_FROM": "1"},
+                  {"TFHE_KS_MATRIX_FROM": "0"}, {"TFHE_KS_MATRIX_FROM": "0", "TFHE_KS_SPLITS": "1"},
                   {"TFHE_LAYER_GROUP_GATES": "300"}):
         env = dict(os.environ)
-        for k in ("TFHE_LATENCY_BATCH", "TFHE_RESIDENT_GROUPS", "TFHE_CHUNK_GATES", "TFHE_KS_MATRIX_FROM", "TFHE_KS_SPLITS",
-                  "TFHE_LAYER_GROUP_GATES", "TFHE_WAVE_GATES_FROM"):
+        for k in ("TFHE_LATENCY_BATCH", "TFHE_PAIR_BATCH", "TFHE_RESIDENT_GROUPS", "TFHE_CHUNK_GATES", "TFHE_KS_MATRIX_FROM",
+                  "TFHE_KS_SPLITS", "TFHE_LAYER_GROUP_GATES", "TFHE_WAVE_GATES_FROM"):
             env.pop(k, None)
         env.update(knobs)
         r = subprocess.run([sys.executable, "-c", _CHUNK_SCRIPT, root], env=env, stdout=subprocess.PIPE,
