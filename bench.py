@@ -5,7 +5,7 @@ configuration 3): host lowering of the layer to its gate circuit, depth-sorted b
 gate's blind rotation and key switch on the GPU, with keys and input ciphertexts already resident
 in HBM.  The headline value is bootstrapped gates per second over the timed steps; ms_per_step is
 the layer latency (mean; median and minimum over the steps are reported beside it).  The line also
-carries the roofline of the dominant work (the blind rotation of a batch, one to three kernel launches,
+carries the roofline of the dominant work (the blind rotation of a batch, one or two kernel launches,
 measured with HIP events on the stream it runs on, against the published FP64 vector peak and against an FMA loop timed on this device),
 the key switch's rates, and the CPU oracle timed on a bounded sample of the same gate stream.
 
@@ -97,7 +97,7 @@ def main():
                          "(a known-traffic kernel to scale rocprofv3's FETCH_SIZE / WRITE_SIZE by)")
     args = ap.parse_args()
     if args.gpus != 1:
-        sys.exit("bench.py: this build runs on one GPU only; --gpus must be 1 "
+        sys.exit("bench.py: runs on one GPU only; --gpus must be 1 "
                  "(units of a layer would be partitioned across GPUs with one all-gather of the "
                  "output ciphertexts per layer; that is not built)")
 
@@ -294,7 +294,8 @@ def main():
     roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP64_VECTOR_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / FP64_VECTOR_PEAK_TFLOPS, 4),
                 "traffic": traffic, "kernel": "blind rotation of a batch (blind_rotate_wave_kernel for whole rounds of 8 gates "
-                "per CU and remainders of 4 or more, blind_rotate_latency_kernel, blind_rotate_pair_kernel, blind_rotate_kernel for 1, 2, 3)",
+                "per CU and remainders of 4 or more, blind_rotate_latency_kernel, blind_rotate_pair_kernel, blind_rotate_kernel for 1, 2, 3 "
+                "and 5 behind whole rounds)",
                 "avg_batch_ms": round(br_avg_ms, 4), "gates_per_batch": round(gates_per_batch, 1),
                 "flops_per_gate": flops_per_gate,
                 "peak_measured": round(measured_peak, 2),
