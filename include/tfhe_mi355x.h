@@ -30,8 +30,8 @@
  *     A cloud key carries device workspaces that its calls share: issue the
  *     server-side calls on one cloud key from one thread at a time and on one
  *     stream (the stream orders successive calls; calls on different streams would
- *     race on the workspaces).  An uploaded cloud key holds about 180 MB of device
- *     memory for the keys, up to 1.07 GB for the samples between the two kernels
+ *     race on the workspaces).  An uploaded cloud key holds about 235 MB of device
+ *     memory for the keys (the bootstrapping key in two forms; 340 MB at n = 1024), up to 1.07 GB for the samples between the two kernels
  *     (4,100 B per gate of the widest launch) and, for the layer calls, a wire pool of
  *     one ciphertext (4 (n+1) bytes) per wire that is alive at the same time (about a
  *     third of the layer's gates; tfhe_last_layer_stats reports it).  A layer of more

@@ -533,9 +533,11 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 // operations of a wave execute in order, so the stores of one polynomial may follow the loads of the one
 // before it at once.
 //
-// What bounds it: vector issue, LDS and the key stream through L1 side by side.  An exchange of a polynomial (8 KB) costs LDS 18 clocks
-// per 16 bytes a lane, 13 of them the store -- the vector units hand LDS about 77 bytes a clock per CU, whatever the width
-// of the store -- so fourteen exchanges are about 2,000 clocks a gate-step beside some 2,250 of vector issue.
+// What bounds it: vector issue, LDS and the key stream through L1 side by side.  Of the 3,460 clocks that a CU spends on a gate-step in
+// whole rounds, vector issue fills 65 %, LDS 47 % and L1 44 %.  Alone, an exchange of a polynomial (8 KB) costs LDS 18 clocks
+// per 16 bytes a lane, 14 of them the store -- the vector units hand LDS about 75 bytes a clock per CU, whatever the width
+// of the store -- so fourteen exchanges are about 2,000 clocks a gate-step beside 2,240 of vector issue.  The key rows' way into L2 does
+// not bound it: a variant whose rows always hit L2 takes the same time (65,536 gates 216.8 against 217.0 ms).
 // 65,536 gates: four-wave kernel 284 ms, this kernel with four sums (2,504 vector instructions a gate-step) 236 ms, with three 206 ms.
 // What it took, one by one on 12,288 gates with four sums: without the twiddles of dft8.h + 2.6 ms; without the barrier
 // before the products + 6 ms (below); without the priorities + 3 ms (below); without interleaving LDS

@@ -57,7 +57,7 @@ def test_popcount_tree_random_with_signed_weights(m):
 
 def test_adder_gate_counts_match_paper_statement():
     """A half adder is 2 gates; a full-adder cell is 5 gates (the paper's '5k gates per k-bit
-    RC adder'); this build's k-bit adder starts with a half adder at bit 0, hence 5k - 3."""
+    RC adder'); the k-bit adder here starts with a half adder at bit 0, hence 5k - 3."""
     pc = paper_counts()
     cir = cc.Circuit(2)
     cc.add_numbers(cir, ([(0, 0)], 1), ([(1, 0)], 1))
