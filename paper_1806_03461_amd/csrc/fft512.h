@@ -162,8 +162,7 @@ FFT_HD void fwd_pass3(double2 (&x)[8], const double2 *row, int L) {
 }
 
 // Slots of a spectrum for a wave that holds one whole polynomial, lane 8 k0 + k1, register k2: slot 256 q + 64 w + lane'
-// is frequency k0 = 2 w + (lane' >> 3 & 1), k1 = lane' & 7, k2 = 2 (lane' >> 4) + q, so the lane reads at its own
-// part plus the register's: four runs of 16 consecutive slots per load.
+// is frequency k0 = 2 w + (lane' >> 3 & 1), k1 = lane' & 7, k2 = 2 (lane' >> 4) + q, the lane's own part plus the register's.
 FFT_HD constexpr int wave_slot_lane(int L) { return (L >> 4) * 64 + (L & 15); }
 FFT_HD constexpr int wave_slot_register(int k2) { return 256 * (k2 & 1) + 16 * (k2 >> 1); }
 

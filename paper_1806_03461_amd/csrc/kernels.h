@@ -13,7 +13,7 @@ struct BlindRotateArgs {
     uint32_t *ext;               // device [count][1025]: extracted samples
     size_t count;
     size_t first;                // set by the launcher: a launch takes items first .. count - 1
-    const double2 *bk_fft;       // device [n][4][4][512], and behind it [n][4][3][512] (sums3.h)
+    const double2 *bk_fft;       // device [n][4][4][512], and behind it [n][8][3][4][64] (sums3.h)
     const double2 *tables;       // device: exp(i pi j / 1024), j < 2048, and the constants of dft8.h
     int n, bgbit;
     double *margin;              // device, optional: largest rounding distance seen

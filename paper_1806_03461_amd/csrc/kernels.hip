@@ -47,7 +47,7 @@ __device__ __forceinline__ void wave_sync() {
 // sums3.h for the wave kernel.  Two workgroups per sample row (i, r), one for each form: the four waves of the first
 // transform the four polynomials o = 2*component + limb with the very steps the blind rotation applies to its four digit
 // polynomials, so the spectra land in the slot order the products use; of the second's waves, three the three factors.
-// bk_raw [n][4][2][1024] uint32  ->  bk_fft [n][4][o][512] complex, and behind all of it [n][4][3][512].
+// bk_raw [n][4][2][1024] uint32  ->  bk_fft [n][4 rows][o][512] complex, and behind all of it [n][k2 8][3 sums][4 rows][64 lanes].
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void bk_to_spectrum_kernel(const uint32_t *__restrict__ bk_raw,
                                                              double2 *__restrict__ bk_fft,
@@ -88,13 +88,23 @@ __global__ __launch_bounds__(256) void bk_to_spectrum_kernel(const uint32_t *__r
     wave_sync();
     fwd_pass3(x, mine, L);
     gather_rows(x);
-    const int outputs = sums ? kSums : 4;
-    double2 *out = bk_fft + (sums ? (size_t)(gridDim.x >> 1) * 4 * kHalf : 0) + row * (size_t)outputs * kHalf;
+    if (sums) {
+        // the wave kernel's order: what a wave reads at one frequency k2 of one sum is 4 KB in a row
+        double2 *out = bk_fft + (size_t)(gridDim.x >> 1) * 4 * kHalf + (row >> 2) * (size_t)(4 * kSums * kHalf) + (row & 3) * 64;
+#pragma unroll
+        for (int o = 0; o < kSums; ++o)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int k2 = 2 * (L >> 4) + q, lane = 16 * wv + (L & 15);      // wave_slot_lane and wave_slot_register, backwards
+                out[(k2 * kSums + o) * 256 + lane] = x[2 * o + q];
+            }
+        return;
+    }
+    double2 *out = bk_fft + row * (size_t)(4 * kHalf);
 #pragma unroll
     for (int o = 0; o < 4; ++o)
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
-            if (o < outputs) out[(size_t)o * kHalf + 256 * q + threadIdx.x] = x[2 * o + q];
+        for (int q = 0; q < 2; ++q) out[(size_t)o * kHalf + 256 * q + threadIdx.x] = x[2 * o + q];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -553,7 +563,6 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 // at another place, is 1 to 7 % slower.
 // ------------------------------------------------------------------------------------------
 constexpr int kWaveGates = 4;      // waves (= gates) of a workgroup
-constexpr int kKeyRing = 4;        // key batches (one sum at one frequency: four 16-byte loads) in registers
 
 struct WaveLds {
     double2 buf[kWaveGates][8 * kRowStride];
@@ -564,16 +573,22 @@ struct WaveLds {
 static_assert(kFwd2 < kInv2 && kInv2 < kInv1 && kInv1 < kFwd3, "the table's order");
 static_assert(2 * sizeof(WaveLds) <= 160 * 1024, "two workgroups share a CU's LDS");
 
-// Scheduling patterns of the instructions between two region ends: eight stores to LDS, then eight
-// loads, each followed by V vector instructions of other work, instead of sixteen LDS instructions in a row.
+// Scheduling patterns of the instructions between two region ends.  EXCHANGE: eight stores to LDS, then eight loads, each followed by nine
+// vector instructions of other work as long as there is any.  A store of 16 bytes a lane holds its wave's issue for 28 clocks if another
+// LDS instruction follows and for 10 behind enough arithmetic; loads may stand together (nine against three: 1,024 gates 3.99 against
+// 4.40 ms, 16,384 gates 51.9 against 53.3).  KEYS: a key load, then four multiply-adds, instead of four loads in a row.
 #define REGION_END() __builtin_amdgcn_sched_barrier(0)
-#define ONE_STORE(V) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0); __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
-#define ONE_LOAD(V) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
-#define EIGHT(X, V) X(V) X(V) X(V) X(V) X(V) X(V) X(V) X(V)
-#define TRANSPOSE_BESIDE(V) EIGHT(ONE_STORE, V) EIGHT(ONE_LOAD, V)
+#define ONE_OF(KIND, V) __builtin_amdgcn_sched_group_barrier(KIND, 1, 0); __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+#define FOUR_OF(KIND, V) ONE_OF(KIND, V) ONE_OF(KIND, V) ONE_OF(KIND, V) ONE_OF(KIND, V)
+#define EXCHANGE_BESIDE() FOUR_OF(0x200, 9) FOUR_OF(0x200, 9) FOUR_OF(0x100, 9) FOUR_OF(0x100, 9)
+#define KEYS_BESIDE() FOUR_OF(0x020, 4)
 
 template <bool MARGIN, bool SHARE>
-__global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu(2, 2))) void blind_rotate_wave_kernel(BlindRotateArgs a) {
+__global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu(SHARE ? 2 : 1, SHARE ? 2 : 1)))
+void blind_rotate_wave_kernel(BlindRotateArgs a) {
+    // Key batches (one sum at one frequency: four 16-byte loads) in registers.  A lone wave covers the way from L2 with one more
+    // (1,024 gates 3.98 -> 3.90 ms); with two on a SIMD five or six are no faster than four.
+    constexpr int kKeyRing = SHARE ? 4 : 5;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     WaveLds &my = *reinterpret_cast<WaveLds *>(lds_raw);
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -593,7 +608,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
     f3.h1w = a.tables[kFwd3 + 192 + L];
     const __amdgpu_buffer_rsrc_t key_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<double2 *>(a.bk_fft + (size_t)a.n * 16 * kHalf), 0, (int)((size_t)a.n * 4 * kSums * kHalf * sizeof(double2)), 0x00020000);
-    const uint32_t voff = (uint32_t)wave_slot_lane(L) * (uint32_t)sizeof(double2);
+    const uint32_t voff = (uint32_t)L * (uint32_t)sizeof(double2);
     double worst = 0.0;
     __syncthreads();
     if (gi >= end) return;            // a wave without a gate: the barriers below wait for the others only
@@ -636,29 +651,33 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
     const uint32_t dround = 1u << (31 - 2 * a.bgbit), dhalf = 1u << (31 - a.bgbit);
     const uint32_t field0 = (uint32_t)(32 - a.bgbit), field1 = (uint32_t)(32 - 2 * a.bgbit);
     int bars = 0;                               // the rotation amounts of 64 steps, one per lane
-    for (int i = 0; i < a.n; ++i) {
+    uint32_t back4 = 0;                         // bytes that the step's rotation reads back
+    auto set_step = [&](int i) {
         if ((i & 63) == 0) bars = rotation(i + L < a.n ? i + L : a.n);
-        const int abar = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(bars, i & 63));
-        const uint32_t back4 = (uint32_t)(0 - abar) << 2;
+        back4 = (uint32_t)(0 - __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(bars, i & 63))) << 2;
+    };
+    // rotated and plain reads of a component (see blind_rotate_body for the mirror and the sign)
+    typedef __attribute__((address_space(3))) const uint32_t lds_word;
+    uint32_t rot[8][2], own[8][2];
+    auto read_component = [&](int comp) {
+        const uint32_t acc_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_word *)acc[comp]);
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t s = back4 + (uint32_t)(64 * m + h * kHalf) * 4u + 4096u;
+                const uint32_t from = __builtin_amdgcn_readfirstlane(acc_at + (s & 4095u));
+                rot[m][h] = *(lds_word *)(uintptr_t)(((uint32_t)L << 2) + from);
+                own[m][h] = acc[comp][L + 64 * m + h * kHalf];
+            }
+        wave_sync();
+    };
+    set_step(0);
+    read_component(0);
+    for (int i = 0; i < a.n; ++i) {
         double2 x[4][8];
 
         // ---- the pieces of a step ----
-        // rotated and plain reads of a component (see blind_rotate_body for the mirror and the sign)
-        typedef __attribute__((address_space(3))) const uint32_t lds_word;
-        uint32_t rot[8][2], own[8][2];
-        auto read_component = [&](int comp) {
-            const uint32_t acc_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_word *)acc[comp]);
-#pragma unroll
-            for (int m = 0; m < 8; ++m)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t s = back4 + (uint32_t)(64 * m + h * kHalf) * 4u + 4096u;
-                    const uint32_t from = __builtin_amdgcn_readfirstlane(acc_at + (s & 4095u));
-                    rot[m][h] = *(lds_word *)(uintptr_t)(((uint32_t)L << 2) + from);
-                    own[m][h] = acc[comp][L + 64 * m + h * kHalf];
-                }
-            wave_sync();
-        };
         // both digits of the difference, folded: x[2 comp] and x[2 comp + 1]
         auto digits = [&](int comp) {
 #pragma unroll
@@ -725,17 +744,17 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         };
         const uint32_t row = (uint32_t)i * 4u * kSums * kHalf * (uint32_t)sizeof(double2);
         double2 ring[kKeyRing][4];
-        auto load_batch = [&](int b) {                               // sum b % 3 at frequency k2 = b / 3
-            const int k2 = b / kSums, o = b % kSums;
+        // Sum b % 3 at frequency k2 = b / 3: four rows of 1 KB behind each other, which one scalar offset and the immediate offsets of
+        // the loads reach.
+        auto load_batch = [&](int b) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                ring[b % kKeyRing][r] = load_key(key_rsrc, voff, row + (uint32_t)(((r * kSums + o) * kHalf + wave_slot_register(k2)) * sizeof(double2)));
+            for (int r = 0; r < 4; ++r) ring[b % kKeyRing][r] = load_key(key_rsrc, voff + 1024u * (uint32_t)r, row + 4096u * (uint32_t)b);
         };
 
-        // ---- forward: four polynomials, the LDS exchanges of one beside the arithmetic of another ----
+        // ---- forward: four polynomials.  An exchange stands beside the arithmetic of another polynomial, and one more piece of arithmetic
+        // comes between it and its own polynomial's next pass, so that its latency is covered too: at most one exchange a region ----
         {
             double2 p[8];
-            read_component(0);
             load_twiddles(my.constants, 8, L >> 3, p);
             const Twiddle8 w2 = unpack_twiddles(p);
             const Twiddle8 w1 = pass1_twiddles(uniform_constants(a.tables));
@@ -745,40 +764,49 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             REGION_END();
             store_columns(x[0]); load_row(x[0]);
             dft8_twiddled<false>(x[1], w1);
-            TRANSPOSE_BESIDE(6)
+            EXCHANGE_BESIDE()
             REGION_END();
             read_component(1);
+            store_columns(x[1]); load_row(x[1]);
+            REGION_END();
             dft8_twiddled<false>(x[0], w2);
             REGION_END();
-            store_across(x[0]); load_along(x[0]); store_columns(x[1]); load_row(x[1]);
+            if (SHARE) __builtin_amdgcn_s_setprio(0);
+            store_across(x[0]); load_along(x[0]);
             digits(1);
             dft8_twiddled<false>(x[2], w1);
-            TRANSPOSE_BESIDE(7) TRANSPOSE_BESIDE(7)
+            EXCHANGE_BESIDE()
             REGION_END();
+            store_columns(x[2]); load_row(x[2]);
             dft8_twiddled<false>(x[1], w2);
+            EXCHANGE_BESIDE()
             REGION_END();
-            store_across(x[1]); load_along(x[1]); store_columns(x[2]); load_row(x[2]);
-            dft8_shifted<false>(x[0], f3);
+            store_across(x[1]); load_along(x[1]);
             dft8_twiddled<false>(x[3], w1);
-            TRANSPOSE_BESIDE(5) TRANSPOSE_BESIDE(5)
+            EXCHANGE_BESIDE()
             REGION_END();
-            __builtin_amdgcn_s_setprio(0);
+            store_columns(x[3]); load_row(x[3]);
             dft8_twiddled<false>(x[2], w2);
+            EXCHANGE_BESIDE()
             REGION_END();
-            store_across(x[2]); load_along(x[2]); store_columns(x[3]); load_row(x[3]);
-            dft8_shifted<false>(x[1], f3);
-            TRANSPOSE_BESIDE(2) TRANSPOSE_BESIDE(1)
+            store_across(x[2]); load_along(x[2]);
+            dft8_shifted<false>(x[0], f3);
+            EXCHANGE_BESIDE()
             REGION_END();
-            load_batch(0); load_batch(1);
             dft8_twiddled<false>(x[3], w2);
             REGION_END();
+            load_batch(0);
             store_across(x[3]); load_along(x[3]);
+            dft8_shifted<false>(x[1], f3);
+            EXCHANGE_BESIDE()
+            REGION_END();
+            load_batch(1);
             dft8_shifted<false>(x[2], f3);
-            TRANSPOSE_BESIDE(3)
             REGION_END();
             load_batch(2);
             dft8_shifted<false>(x[3], f3);
             REGION_END();
+            if (!SHARE) load_batch(3);
         }
 
         // ---- products with the key row: at every frequency the four digit spectra give way to the three sums ----
@@ -790,7 +818,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             for (int o = 0; o < kSums; ++o) {
                 const int b = kSums * k2 + o;
                 if (b + kKeyRing - 1 < 8 * kSums) load_batch(b + kKeyRing - 1);
-                REGION_END();
+                if (!SHARE) REGION_END();
                 const double2 (&k)[4] = ring[b % kKeyRing];
                 const double2 d0 = x[0][k2];
                 double yr = d0.x * k[0].x, yi = d0.x * k[0].y;
@@ -805,6 +833,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
                     yi = fma(d.y, k[r].x, yi);
                 }
                 y[o] = make_double2(yr, yi);
+                if (SHARE) { KEYS_BESIDE() }
                 REGION_END();
             }
 #pragma unroll
@@ -812,7 +841,7 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         }
 
         // ---- back: inverse transforms, exact rounding, accumulate ----
-        __builtin_amdgcn_s_setprio(2);
+        if (SHARE) __builtin_amdgcn_s_setprio(2);
         {
             double2 p[8];
             load_twiddles(my.constants + (kInv2 - kFwd2), 8, L & 7, p);
@@ -859,28 +888,38 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             REGION_END();
             store_along(x[0]); load_across(x[0]);
             radix8<true>(x[1]);
-            TRANSPOSE_BESIDE(4)
+            EXCHANGE_BESIDE()
             REGION_END();
-            dft8_twiddled<true>(x[0], w2);
-            REGION_END();
-            store_row(x[0]); load_columns(x[0]); store_along(x[1]); load_across(x[1]);
+            store_along(x[1]); load_across(x[1]);
             radix8<true>(x[2]);
-            TRANSPOSE_BESIDE(2) TRANSPOSE_BESIDE(2)
+            EXCHANGE_BESIDE()
             REGION_END();
+            store_along(x[2]); load_across(x[2]);
+            dft8_twiddled<true>(x[0], w2);
+            EXCHANGE_BESIDE()
+            REGION_END();
+            store_row(x[0]); load_columns(x[0]);
             dft8_twiddled<true>(x[1], w2);
+            EXCHANGE_BESIDE()
             REGION_END();
-            store_row(x[1]); load_columns(x[1]); store_along(x[2]); load_across(x[2]);
-            finish(0);
-            TRANSPOSE_BESIDE(3) TRANSPOSE_BESIDE(3)
-            REGION_END();
+            store_row(x[1]); load_columns(x[1]);
             dft8_twiddled<true>(x[2], w2);
+            EXCHANGE_BESIDE()
             REGION_END();
             store_row(x[2]); load_columns(x[2]);
-            finish(1);
-            TRANSPOSE_BESIDE(6)
+            finish(0);
+            EXCHANGE_BESIDE()
             REGION_END();
+            finish(1);
+            wave_sync();
+            REGION_END();
+            // component 0 is complete: the next step's reads of it go before the rounding of component 1 (after the last step they
+            // are not used)
+            set_step(i + 1 < a.n ? i + 1 : i);
+            read_component(0);
             finish(2);
             wave_sync();
+            REGION_END();
         }
     }
 
