@@ -656,18 +656,25 @@ void blind_rotate_wave_kernel(BlindRotateArgs a) {
         if ((i & 63) == 0) bars = rotation(i + L < a.n ? i + L : a.n);
         back4 = (uint32_t)(0 - __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(bars, i & 63))) << 2;
     };
-    // rotated and plain reads of a component (see blind_rotate_body for the mirror and the sign)
+    // Rotated and plain reads of a component (see blind_rotate_body for the mirror and the sign).  A lone wave pays for every scalar
+    // instruction: it keeps the sixteen addresses of component 0 for component 1 (1,024 gates 3.88 -> 3.82 ms).  With two waves on a
+    // SIMD that is slower (16,384 gates 50.9 -> 51.6 ms).
     typedef __attribute__((address_space(3))) const uint32_t lds_word;
-    uint32_t rot[8][2], own[8][2];
+    const uint32_t lane_at = (uint32_t)(uintptr_t)(lds_word *)acc[0] + ((uint32_t)L << 2);
+    uint32_t rot[8][2], own[8][2], at[8][2];
     auto read_component = [&](int comp) {
         const uint32_t acc_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_word *)acc[comp]);
 #pragma unroll
         for (int m = 0; m < 8; ++m)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const uint32_t s = back4 + (uint32_t)(64 * m + h * kHalf) * 4u + 4096u;
-                const uint32_t from = __builtin_amdgcn_readfirstlane(acc_at + (s & 4095u));
-                rot[m][h] = *(lds_word *)(uintptr_t)(((uint32_t)L << 2) + from);
+                const uint32_t back = (back4 + (uint32_t)(64 * m + h * kHalf) * 4u) & 4095u;
+                if (SHARE) {
+                    rot[m][h] = *(lds_word *)(uintptr_t)(((uint32_t)L << 2) + __builtin_amdgcn_readfirstlane(acc_at + back));
+                } else {
+                    if (comp == 0) at[m][h] = lane_at + __builtin_amdgcn_readfirstlane(back);
+                    rot[m][h] = ((lds_word *)(uintptr_t)at[m][h])[comp * (kN + kMirror)];
+                }
                 own[m][h] = acc[comp][L + 64 * m + h * kHalf];
             }
         wave_sync();
