@@ -181,8 +181,11 @@ __device__ __forceinline__ Twiddle8 pass1_twiddles(const_double *u) {
 // AHEAD: the variants for one or two workgroups per CU request the whole key row of step i + 1 while step i still runs, in
 // eight portions of four loads placed between the phases that follow the products of step i.
 // LONE: one workgroup per CU.  A portion keeps the CU's one address unit busy for 4 x 16 clocks per wave, and a wave alone
-// on its SIMD cannot issue anything else meanwhile, so portions issued back to back stall all four waves (measured on 64
-// gates: all 32 loads in one place 2.06 ms, two places 1.82 ms, four 1.71 ms, eight 1.62 ms; no key traffic at all 1.50 ms).
+// on its SIMD cannot issue anything else meanwhile, so all 32 loads in one place stall all four waves.  Where the portions stand was
+// searched for, with the places the scheduler may not move instructions across: the four waves run in step, and a load that waits
+// for the address unit delays everything behind it.  About 250 arrangements were timed: one portion after each of eight phases 1.530 ms
+// for 8 gates and 1.588 for 256; this one -- two after the products, two and one in the waits for the inverse exchanges, one and two
+// behind the step's last and first barriers -- 1.482 and 1.524; most others 1.50 to 1.64.
 // Two workgroups per CU hide that behind each other; there the last two portions go with earlier ones, a step's length
 // ahead of their use, which also saves the registers of the loads in flight across forward passes 2 and 3 (301 gates 1.96 -> 1.94 ms, and no scratch).
 // At three workgroups per CU the others cover the loads and holding registers for them does not pay:
@@ -219,6 +222,8 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
     for (int q = 0; q < 3; ++q) i1[q] = a.tables[kInv1 + (5 + q) * 64 + L];
     for (int e = tid; e < 5 * 64; e += kThreadsPerGate) my.inv1[e] = a.tables[kInv1 + e];
     auto pause = [] { __builtin_amdgcn_sched_barrier(0); };
+    auto pause_if_shared = [] { if (!LONE) __builtin_amdgcn_sched_barrier(0); };
+    auto lone_pause = [] { if (LONE) __builtin_amdgcn_sched_barrier(0); };
     // The constants that are the same in every lane.  With one or two workgroups per CU nobody covers the waits for them, which
     // also wait for every LDS read in flight: forward pass 1 keeps its own over the loop, and a lone workgroup, whose rotation
     // needs no scalar registers, the cosines of the rounding too (8 gates 1.555 -> 1.53 ms a call; 301 gates 2.02 -> 1.975, 512 gates
@@ -314,7 +319,8 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
                 ahead[e >> 1][r][o2] = key(row, e >> 1, r, o2);
     };
 #pragma unroll
-    for (int e = 0; e < 8; ++e) load_ahead(0, e);
+    for (int e = 0; e < 8; ++e)
+        if (!LONE || (e & 3) != 3) load_ahead(0, e);      // a lone workgroup requests portions 3 and 7 in the step itself
 
     int abar_next = my.bar[0];
     for (int i = 0; i < a.n; ++i) {
@@ -381,27 +387,29 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int j = L + 64 * m + h * kHalf;
-                const uint32_t turned = (rot[m][h] ^ flip[m][h]) + (LONE ? flip[m][h] : 0u);
-                const uint32_t d = turned + acc(comp)[j] + bias[m][h];
+                uint32_t d = (rot[m][h] ^ flip[m][h]) + acc(comp)[j];
+                if (LONE) asm("" : "+v"(d));             // v_xad_u32, and one v_add3_u32 for the other two
+                d += LONE ? flip[m][h] + bias[m][h] : bias[m][h];
                 dig[h] = __builtin_amdgcn_sbfe((int32_t)d, dfield, (uint32_t)a.bgbit);    // signed field
             }
             x[m] = make_double2((double)dig[0], (double)dig[1]);
         }
         }
-        if (LONE && i > 0) load_ahead(i, 6);
+        lone_pause();
         {
             const Twiddle8 w1 = AHEAD ? kept_w1 : pass1_twiddles(uniform_constants(a.tables));
             dft8_twiddled<false>(x, w1, [&](int k, double2 v) { poly[k * kRowStride + L] = v; }, pause);
         }
         __syncthreads();
-        if (LONE && i > 0) load_ahead(i, 7);
+        if (LONE) { load_ahead(i, 3); load_ahead(i, 7); }
+        lone_pause();
 
         // ---- this wave's frequencies of all four polynomials ----
         priority(1);
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[j] = mine[(L & 7) + 8 * j];
         wave_sync();
-        dft8_shifted<false>(x, f2, [&](int k, double2 v) { mine[k * kGrpStride + (L & 7)] = v; }, pause);
+        dft8_shifted<false>(x, f2, [&](int k, double2 v) { mine[k * kGrpStride + (L & 7)] = v; }, pause_if_shared);
         wave_sync();
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[j] = mine[(L & 7) * kGrpStride + j];
@@ -441,25 +449,28 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
         }
         const int next = i + 1 < a.n ? i + 1 : i;     // the last step requests its own row again
         load_ahead(next, 0);
+        if (LONE) load_ahead(next, 2);
 
         // ---- back: scatter the four output spectra to their lanes, inverse passes 3 and 2 ----
         scatter_rows(y);
         radix8<true>(y, [&](int k, double2 v) { mine[(L & 7) * kGrpStride + k] = v; }, pause);
         wave_sync();
         load_ahead(next, 1);
+        if (LONE) load_ahead(next, 6);
 #pragma unroll
         for (int k = 0; k < 8; ++k) y[k] = mine[k * kGrpStride + (L & 7)];
         wave_sync();
-        load_ahead(next, 2);
+        if (!LONE) load_ahead(next, 2);
         dft8_shifted<true>(y, i2, [&](int k, double2 v) { mine[(L & 7) + 8 * k] = v; }, pause);
+        if (LONE) load_ahead(next, 4);
         double2 p[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q)
             p[q] = q < 5 ? my.inv1[q * 64 + L] : kSpare ? a.tables[kInv1 + q * 64 + L] : i1[q < 5 ? 0 : q - 5];
         __syncthreads();
         abar_next = my.bar[i + 1];           // bar[n] exists (it holds bbar)
-        load_ahead(next, 3);
-        if (!LONE) load_ahead(next, 6);
+        lone_pause();
+        if (!LONE) { load_ahead(next, 3); load_ahead(next, 6); }
 
         // ---- inverse pass 1 of output polynomial o = wave, exact rounding, accumulate ----
         priority(2);
@@ -484,12 +495,13 @@ __device__ __forceinline__ void blind_rotate_body(const BlindRotateArgs &a) {
                 uint32_t r = (uint32_t)__double2loint(shifted);
                 if (MARGIN) worst = fmax(worst, fabs((m ? cos_m[m] * part[h] : part[h]) + (shifted - 6755399441055744.0)));
                 if (sel) r <<= 16;
-                if (m == 3 && h == 1) load_ahead(next, 4);
+                if (!LONE && m == 3 && h == 1) load_ahead(next, 4);
                 atomicAdd(&acc(comp)[L + 64 * m + h * kHalf], r);
                 if (!LONE && m == 0 && h == 0) atomicSub(&my.acc[comp][kN + L], r);      // the mirror holds -c - 2
             }
         }
         __syncthreads();
+        lone_pause();
         load_ahead(next, 5);
         if (!LONE) load_ahead(next, 7);
     }
