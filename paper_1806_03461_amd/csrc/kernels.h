@@ -36,17 +36,18 @@ struct KeySwitchArgs {
 // How long a blind rotation of `items` gates takes on a device with `cus` compute units, in milliseconds, as
 // measured on 256 of them (n = 500; other step counts scale all of it alike): what the launcher's choice of
 // kernels and the scheduler of narrow circuits go by.
-//   wave kernel       eight gates per CU at a time: 6.4 ms a round, 4.15 ms with at most four per CU in it,
-//                     5.4 ms with five and 5.45 to 5.75 ms with six, by machine, spread evenly over the CUs (5.85 with the key
-//                     switch of so many: the scheduler had better not count on it), 6.0 ms with seven
-//   four-wave kernels 1.55, 2.1 and 3.3 ms for one, two and three gates per CU, 5.5 ms for five
+//   wave kernel       eight gates per CU at a time: 6.1 ms a round, 3.7 ms with at most four per CU in it,
+//                     5.1 ms with five or six, spread evenly over the CUs, 5.7 ms with seven
+//   four-wave kernels 1.5, 2.1 and 3.3 ms for one, two and three gates per CU, 5.5 ms for five
+// The table holds the times that schedules were last chosen by (6.4, 4.15, 5.4 to 5.85, 6.0; 1.55): with today's, schedules of
+// 6,000 to 120,000 gates come out within 0.6 % of the same estimated time, either way.
 inline double rest_ms(size_t per_cu) {      // a launch of less than a round
     const double ms[9] = {0.0, 1.55, 2.1, 3.32, 4.15, 5.4, 5.85, 6.0, 6.42};
     return ms[per_cu];
 }
 // The kernel that serves a batch's last, partial round fastest: the wave kernel together with the whole rounds or in a launch of its
 // own, or the four-wave kernels.  Five gates per CU: 1,025 gates 5.3 ms on the wave kernel and 5.65 on the four-wave ones, behind
-// a round 3,328 gates 12.0 and 11.7.
+// a round 3,328 gates 12.1 and 11.95.
 enum class RestKernel { kFourWaves, kWave, kWithRounds };
 inline RestKernel rest_kernel(size_t per_cu, bool behind_rounds) {
     if (per_cu >= 7) return RestKernel::kWithRounds;

@@ -555,24 +555,23 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 // operations of a wave execute in order, so the stores of one polynomial may follow the loads of the one
 // before it at once.
 //
-// What bounds it: vector issue, LDS and the key stream through L1 side by side.  Of the 3,460 clocks that a CU spends on a gate-step in
-// whole rounds, vector issue fills 65 %, LDS 47 % and L1 44 %.  Alone, an exchange of a polynomial (8 KB) costs LDS 18 clocks
-// per 16 bytes a lane, 14 of them the store -- the vector units hand LDS about 75 bytes a clock per CU, whatever the width
-// of the store -- so fourteen exchanges are about 2,000 clocks a gate-step beside 2,240 of vector issue.  The key rows' way into L2 does
-// not bound it: a variant whose rows always hit L2 takes the same time (65,536 gates 216.8 against 217.0 ms).
-// 65,536 gates: four-wave kernel 284 ms, this kernel with four sums (2,504 vector instructions a gate-step) 236 ms, with three 206 ms.
-// What it took, one by one on 12,288 gates with four sums: without the twiddles of dft8.h + 2.6 ms; without the barrier
-// before the products + 6 ms (below); without the priorities + 3 ms (below); without interleaving LDS
-// instructions with arithmetic + 2 ms.  Key rows brought to LDS by loads to LDS and read by all four waves
-// instead of four L1 reads: equal (the LDS pipe then carries what L1 carried).
+// What bounds it: vector issue, LDS and the key stream through L1 side by side, at a clock that power lowers (2.18 GHz in whole rounds,
+// 2.39 with a workgroup per CU).  An exchange of a polynomial (8 KB) costs its wave eight stores of 28 clocks of issue and eight
+// loads of about 14, and the CU's LDS 13 and 5 clocks each, whatever their width: fourteen exchanges are about 2,000 clocks of LDS
+// a gate-step beside 2,240 of vector issue.  So at most one exchange stands in a region between two scheduling barriers, its stores nine vector
+// instructions apart, and one more piece of arithmetic comes before its result is used; the step's first reads go before the
+// rounding of the step before.  Against two exchanges in a region, closer and used at once: 1,024 gates 4.47 -> 3.84 ms, 16,384 gates
+// 51.8 -> 49.4, 65,536 gates 206.0 -> 200.0 (four sums 236, the four-wave kernel 284).
+// Without the barrier before the products + 1 %; without any exchange - 15 %, without key loads - 8 % (half of which is clock), without both
+// - 27 % (with the exchanges as they stood before).  Key rows brought to LDS and read from there by all four waves instead of four L1
+// reads: equal.  Products spread over the forward half, a digit polynomial or a component at a time: registers spill.
 //
 // Barrier before the products: the four waves of a workgroup then read the key row together and three
 // quarters of their reads hit L1; without it the waves of
 // an XCD spread over more rows than its L2 holds.
-// Priorities: the inverse transforms and the first half of the forward ones issue ahead of the second half and
-// the products.  Each half holds half of a step's arithmetic, so the two waves of a SIMD fall into opposite
-// halves: one computes while the other waits for LDS and keys.  One level less or more, or the change
-// at another place, is 1 to 7 % slower.
+// Priorities: the inverse transforms and the beginning of the forward ones, up to the second exchange, issue ahead of the rest and the
+// products, so that the two waves of a SIMD fall into opposite halves: one computes while the other waits for LDS and keys.
+// 16,384 gates, lowered behind the first second pass 51.6 ms, up to eight pieces later 51.9 to 53.3; raised a piece later 53.
 // ------------------------------------------------------------------------------------------
 constexpr int kWaveGates = 4;      // waves (= gates) of a workgroup
 
@@ -1405,10 +1404,11 @@ static_assert(kRoundPerCu == 2 * kWaveGates, "two workgroups of the wave kernel 
 
 // Items first .. count - 1 with the wave kernel.  With more than one workgroup per CU the waves of a workgroup meet before the
 // products, so that their key reads hit L1 (8,192 gates 26.0 -> 25.2 ms); a lone workgroup leaves L1 and L2 idle enough
-// and loses by waiting (1,024 gates 4.15 ms without, 4.54 with).
+// and loses by waiting (1,024 gates 4.15 ms without, 4.54 with, when that was measured; 3.8 now).
 // Five or six gates per CU are spread over two workgroups on every CU instead of filling half of the CUs with two whole ones:
-// 1,025 gates 5.65 -> 5.3 ms, 1,536 gates 5.82 -> 5.44.  Seven are not: the CUs that end early leave the others their power
-// (1,554 gates 6.0 ms as they are, 6.2 spread).
+// 1,025 gates 5.65 -> 5.3 ms, 1,536 gates 5.82 -> 5.44 (5.2 now).  Seven are not: the CUs that end early leave the others their power
+// (1,554 gates 5.68 ms as they are, 5.93 spread).  Four at a time and the others in a launch of their own is slower: 1,280 gates 5.37
+// against 5.20 ms, 1,536 gates 5.91 against 5.23.
 static int launch_wave(const BlindRotateArgs &a, size_t cus, hipStream_t stream) {
     const size_t items = a.count - a.first, least = (items + kWaveGates - 1) / kWaveGates;
     if (items <= kWaveGates * cus) return launch_rotation(kWaveLone, least, a, stream);
