@@ -572,6 +572,9 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 // Priorities: the inverse transforms and the beginning of the forward ones, up to the second exchange, issue ahead of the rest and the
 // products, so that the two waves of a SIMD fall into opposite halves: one computes while the other waits for LDS and keys.
 // 16,384 gates, lowered behind the first second pass 51.6 ms, up to eight pieces later 51.9 to 53.3; raised a piece later 53.
+// Two waves per SIMD in the lone form too, with the same priorities: alone it has one, but launches for two keys on two streams then
+// share the CUs.  800, 900 and 1,024 gates for each of two keys: 6.36, 6.61 and 6.74 ms; 6.78, 7.06 and 7.21 without priorities; 7.74,
+// 7.55 and 7.59 compiled for one wave, one launch after the other.  One of them alone 3.75, 3.75 and 3.82 in either form.
 // ------------------------------------------------------------------------------------------
 constexpr int kWaveGates = 4;      // waves (= gates) of a workgroup
 
@@ -595,8 +598,7 @@ static_assert(2 * sizeof(WaveLds) <= 160 * 1024, "two workgroups share a CU's LD
 #define KEYS_BESIDE() FOUR_OF(0x020, 4)
 
 template <bool MARGIN, bool SHARE>
-__global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu(SHARE ? 2 : 1, SHARE ? 2 : 1)))
-void blind_rotate_wave_kernel(BlindRotateArgs a) {
+__global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu(2, 2))) void blind_rotate_wave_kernel(BlindRotateArgs a) {
     // Key batches (one sum at one frequency: four 16-byte loads) in registers.  A lone wave covers the way from L2 with one more
     // (1,024 gates 3.98 -> 3.90 ms); with two on a SIMD five or six are no faster than four.
     constexpr int kKeyRing = SHARE ? 4 : 5;
@@ -663,8 +665,18 @@ void blind_rotate_wave_kernel(BlindRotateArgs a) {
     const uint32_t field0 = (uint32_t)(32 - a.bgbit), field1 = (uint32_t)(32 - 2 * a.bgbit);
     int bars = 0;                               // the rotation amounts of 64 steps, one per lane
     uint32_t back4 = 0;                         // bytes that the step's rotation reads back
+    // The lane's number, counted again where it is needed once in 64 steps or at the end: kept, it and the addresses formed from it take
+    // registers that the lone form does not have.
+    auto lane_again = [] {
+        uint32_t all = ~0u;
+        asm volatile("" : "+s"(all));
+        return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+    };
     auto set_step = [&](int i) {
-        if ((i & 63) == 0) bars = rotation(i + L < a.n ? i + L : a.n);
+        if ((i & 63) == 0) {
+            const int j = i + lane_again();
+            bars = rotation(j < a.n ? j : a.n);
+        }
         back4 = (uint32_t)(0 - __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(bars, i & 63))) << 2;
     };
     // Rotated and plain reads of a component (see blind_rotate_body for the mirror and the sign).  A lone wave pays for every scalar
@@ -716,9 +728,10 @@ void blind_rotate_wave_kernel(BlindRotateArgs a) {
         };
         // lane-dependent constants are read again where they are needed: kept in registers they would
         // leave none for the key loads in flight
+        typedef __attribute__((address_space(3))) const double2 lds_words;
         auto load_twiddles = [&](const double2 *table, int width, int lane, double2 (&p)[8]) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) p[q] = table[q * width + lane];
+            for (int q = 0; q < 8; ++q) p[q] = *(const double2 *)((lds_words *)(table + lane) + q * width);
         };
         auto store_columns = [&](const double2 (&v)[8]) {            // element k of lane L at row k, column L
 #pragma unroll
@@ -789,7 +802,7 @@ void blind_rotate_wave_kernel(BlindRotateArgs a) {
             REGION_END();
             dft8_twiddled<false>(x[0], w2);
             REGION_END();
-            if (SHARE) __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_s_setprio(0);
             store_across(x[0]); load_along(x[0]);
             digits(1);
             dft8_twiddled<false>(x[2], w1);
@@ -859,7 +872,7 @@ void blind_rotate_wave_kernel(BlindRotateArgs a) {
         }
 
         // ---- back: inverse transforms, exact rounding, accumulate ----
-        if (SHARE) __builtin_amdgcn_s_setprio(2);
+        __builtin_amdgcn_s_setprio(2);
         {
             double2 p[8];
             load_twiddles(my.constants + (kInv2 - kFwd2), 8, L & 7, p);
@@ -942,8 +955,9 @@ void blind_rotate_wave_kernel(BlindRotateArgs a) {
     }
 
     uint32_t *ext = a.ext + gi * (size_t)(kN + 1);
-    for (int j = L; j < kN; j += 64) ext[j] = j == 0 ? ~acc[0][0] : acc[0][kN - j] + 1u;
-    if (L == 0) ext[kN] = ~acc[1][0];
+    const int lane = lane_again();
+    for (int j = lane; j < kN; j += 64) ext[j] = j == 0 ? ~acc[0][0] : acc[0][kN - j] + 1u;
+    if (lane == 0) ext[kN] = ~acc[1][0];
     if (MARGIN)
         atomicMax(reinterpret_cast<unsigned long long *>(a.margin), (unsigned long long)__double_as_longlong(worst));
 }
@@ -1409,6 +1423,7 @@ static_assert(kRoundPerCu == 2 * kWaveGates, "two workgroups of the wave kernel 
 // 1,025 gates 5.65 -> 5.3 ms, 1,536 gates 5.82 -> 5.44 (5.2 now).  Seven are not: the CUs that end early leave the others their power
 // (1,554 gates 5.68 ms as they are, 5.93 spread).  Four at a time and the others in a launch of their own is slower: 1,280 gates 5.37
 // against 5.20 ms, 1,536 gates 5.91 against 5.23.
+// Two lone launches for two keys, on two streams, do share the CUs (see the kernel).
 static int launch_wave(const BlindRotateArgs &a, size_t cus, hipStream_t stream) {
     const size_t items = a.count - a.first, least = (items + kWaveGates - 1) / kWaveGates;
     if (items <= kWaveGates * cus) return launch_rotation(kWaveLone, least, a, stream);

@@ -1,7 +1,9 @@
-"""What the compiler reports for the device kernels, with the build's own flags: no kernel needs scratch memory, and every
-blind rotation exists with and without the recording of its rounding distance.  Scratch is memory that the runtime sets up for a
+"""What the compiler reports for the device kernels, with the build's own flags: no kernel needs scratch memory, every
+blind rotation exists with and without the recording of its rounding distance, and as many of its waves as it is written for fit on
+a SIMD.  Scratch is memory that the runtime sets up for a
 queue when the first kernel that needs it is dispatched, and tfhe_gate_batch_noalloc promises that no allocation of any
-kind happens inside; a blind rotation without the recording form is one that tfhe_rounding_margin_enable cannot look at."""
+kind happens inside; a blind rotation without the recording form is one that tfhe_rounding_margin_enable cannot look at; and
+launches for two keys on two streams share the CUs only as far as their registers allow."""
 import os
 import re
 import shutil
@@ -12,17 +14,33 @@ import pytest
 from paper_1806_03461_amd import build
 
 
-def test_no_kernel_uses_scratch_memory():
+@pytest.fixture(scope="module")
+def report():
     if not shutil.which("hipcc"):
         pytest.skip("no hipcc")
     r = subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", "-Rpass-analysis=kernel-resource-usage", "-o", os.devnull,
                         os.path.join(build.CSRC, "kernels.hip")], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=600)
     assert r.returncode == 0, r.stdout
-    names = re.findall(r"Function Name: (\S+)", r.stdout)
-    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stdout)]
-    assert len(names) == len(scratch) and any("blind_rotate_wave_kernel" in n for n in names), r.stdout
+    return r.stdout
+
+
+def test_no_kernel_uses_scratch_memory(report):
+    names = re.findall(r"Function Name: (\S+)", report)
+    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", report)]
+    assert len(names) == len(scratch) and any("blind_rotate_wave_kernel" in n for n in names), report
     assert [(n, s) for n, s in zip(names, scratch) if s] == []
     # _ZN..blind_rotate_x_kernelILb<MARGIN>E..., the recording form first among its template arguments
     rotations = [re.search(r"(blind_rotate\w*?_kernel)(?:ILb([01])E(\w*?)EEv)?", n).groups() for n in names if "blind_rotate" in n]
     plain, recording = ({(name, rest) for name, margin, rest in rotations if margin == form} for form in "01")
     assert len(plain) == 5 and len(rotations) == 10 and plain == recording, rotations
+
+
+def test_blind_rotations_leave_room_for_the_waves_they_are_written_for(report):
+    """Three waves a SIMD of the four-wave kernel, two of the pair kernel and of either form of the wave kernel: 900 gates for each of
+    two keys, on two streams, take 6.6 ms together if two workgroups of the lone form share a CU, 7.6 if not."""
+    names = re.findall(r"Function Name: (\S+)", report)
+    occupancy = [int(v) for v in re.findall(r"Occupancy \[waves/SIMD\]: (\d+)", report)]
+    assert len(names) == len(occupancy), report
+    waves = {"blind_rotate_kernel": 3, "blind_rotate_pair_kernel": 2, "blind_rotate_wave_kernel": 2, "blind_rotate_latency_kernel": 1}
+    found = [(re.search(r"(blind_rotate\w*?_kernel)", n).group(1), o) for n, o in zip(names, occupancy) if "blind_rotate" in n]
+    assert len(found) == 10 and [(n, o) for n, o in found if o < waves[n]] == [], found
