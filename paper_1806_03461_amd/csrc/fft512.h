@@ -161,10 +161,10 @@ FFT_HD void fwd_pass3(double2 (&x)[8], const double2 *row, int L) {
     radix8<false>(x);
 }
 
-// Slots of a spectrum for a wave that holds one whole polynomial, lane 8 k0 + k1, register k2: slot 256 q + 64 w + lane'
-// is frequency k0 = 2 w + (lane' >> 3 & 1), k1 = lane' & 7, k2 = 2 (lane' >> 4) + q, the lane's own part plus the register's.
-FFT_HD constexpr int wave_slot_lane(int L) { return (L >> 4) * 64 + (L & 15); }
-FFT_HD constexpr int wave_slot_register(int k2) { return 256 * (k2 & 1) + 16 * (k2 >> 1); }
+// A wave that holds one whole polynomial has frequency k0 + 8 k1 + 64 k2 in register k2 of lane 8 k0 + k1.  What gather (below) leaves
+// in register 2 r + q of lane L of wave w, k0 = 2 w + (L >> 3 & 1), k1 = L & 7, k2 = 2 (L >> 4) + q, is there in this lane and register.
+FFT_HD constexpr int whole_lane(int w, int L) { return 16 * w + (L & 15); }
+FFT_HD constexpr int whole_register(int L, int q) { return 2 * (L >> 4) + q; }
 
 // ---- gather / scatter: registers <-> lane bits 5 and 4 -----------------------------------
 // One exchange step on a pair of 32-bit registers (a, b) of all lanes, lane bit `bit` (5 or 4):

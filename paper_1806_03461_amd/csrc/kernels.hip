@@ -89,15 +89,11 @@ __global__ __launch_bounds__(256) void bk_to_spectrum_kernel(const uint32_t *__r
     fwd_pass3(x, mine, L);
     gather_rows(x);
     if (sums) {
-        // the wave kernel's order: what a wave reads at one frequency k2 of one sum is 4 KB in a row
-        double2 *out = bk_fft + (size_t)(gridDim.x >> 1) * 4 * kHalf + (row >> 2) * (size_t)(4 * kSums * kHalf) + (row & 3) * 64;
+        double2 *out = bk_fft + (size_t)(gridDim.x >> 1) * 4 * kHalf + (row >> 2) * (size_t)kSumKeyWords;
 #pragma unroll
         for (int o = 0; o < kSums; ++o)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int k2 = 2 * (L >> 4) + q, lane = 16 * wv + (L & 15);      // wave_slot_lane and wave_slot_register, backwards
-                out[(k2 * kSums + o) * 256 + lane] = x[2 * o + q];
-            }
+            for (int q = 0; q < 2; ++q) out[sum_key_word(whole_register(L, q), o, (int)(row & 3), whole_lane(wv, L))] = x[2 * o + q];
         return;
     }
     double2 *out = bk_fft + row * (size_t)(4 * kHalf);
@@ -620,8 +616,8 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
     f3.h1 = a.tables[kFwd3 + 128 + L];
     f3.h1w = a.tables[kFwd3 + 192 + L];
     const __amdgpu_buffer_rsrc_t key_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<double2 *>(a.bk_fft + (size_t)a.n * 16 * kHalf), 0, (int)((size_t)a.n * 4 * kSums * kHalf * sizeof(double2)), 0x00020000);
-    const uint32_t voff = (uint32_t)L * (uint32_t)sizeof(double2);
+        const_cast<double2 *>(a.bk_fft + (size_t)a.n * 16 * kHalf), 0, (int)((size_t)a.n * kSumKeyWords * sizeof(double2)), 0x00020000);
+    const uint32_t voff = (uint32_t)sum_key_word(0, 0, 0, L) * (uint32_t)sizeof(double2);
     double worst = 0.0;
     __syncthreads();
     if (gi >= end) return;            // a wave without a gate: the barriers below wait for the others only
@@ -773,13 +769,15 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
             for (int k = 0; k < 8; ++k) v[k] = mine[(L & 7) * kGrpStride + k];
             wave_sync();
         };
-        const uint32_t row = (uint32_t)i * 4u * kSums * kHalf * (uint32_t)sizeof(double2);
+        constexpr uint32_t kWord = sizeof(double2);
+        const uint32_t row = (uint32_t)i * kSumKeyWords * kWord;
         double2 ring[kKeyRing][4];
         // Sum b % 3 at frequency k2 = b / 3: four rows of 1 KB behind each other, which one scalar offset and the immediate offsets of
         // the loads reach.
         auto load_batch = [&](int b) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) ring[b % kKeyRing][r] = load_key(key_rsrc, voff + 1024u * (uint32_t)r, row + 4096u * (uint32_t)b);
+            for (int r = 0; r < 4; ++r)
+                ring[b % kKeyRing][r] = load_key(key_rsrc, voff + kWord * sum_key_word(0, 0, r, 0), row + kWord * sum_key_word(b / kSums, b % kSums, 0, 0));
         };
 
         // ---- forward: four polynomials.  An exchange stands beside the arithmetic of another polynomial, and one more piece of arithmetic

@@ -30,6 +30,11 @@ FFT_HD double sum_factor(uint32_t key0, uint32_t key1, int o) {
     return (double)(int32_t)(o == 1 ? key0 : key1) * (1.0 / (1 << kSumBits));
 }
 
+// The factors' spectra of one step, in the order in which a wave that holds whole polynomials reads them: a sum at a time, at
+// one frequency of every lane, its four rows behind each other.  Complex word of row r of sum o at register k2 of a lane.
+FFT_HD constexpr int sum_key_word(int k2, int o, int r, int lane) { return ((k2 * kSums + o) * 4 + r) * 64 + lane; }
+constexpr int kSumKeyWords = sum_key_word(8, 0, 0, 0);
+
 // Added to a number in a double's middle, these leave it in fixed point in the low word: an integer, or (with 2^-10 as
 // the unit of the last place and 2^(b-1) units of half a P added, which turns rounding down into rounding to nearest) P / 2.
 // |A|, |B| < 2^41: 4,096 terms of at most 512 * 2^31 / 2^b, of which not all 4,096 can be the largest with the same sign

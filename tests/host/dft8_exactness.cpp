@@ -3,14 +3,18 @@
 // The key comes, as on the device, from the steps of csrc/fft512.h.  The products
 // sum_r digit_r * limb_{r,o} mod X^1024 + 1 are compared with exact 64-bit integers, and their largest distance
 // from an integer with that of the same products through the transforms of fft512.h, on random operands and on
-// operands at the ends of their ranges.  A second part runs whole steps lane by lane as the two kernels do: the key in slot
-// order, its slots addressed by each kernel's own rule, and the exchanges through LDS and between lanes.
+// operands at the ends of their ranges.  A second part runs whole steps lane by lane as the kernels do, with the exchanges through
+// LDS and between lanes: four waves per gate with the key's limbs in slot order, one wave per gate with the factors of
+// csrc/sums3.h where the upload stores them for it, up to the two components mod 2^32.
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
 #include <vector>
 
 #include "../../paper_1806_03461_amd/csrc/dft8.h"
+#include "../../paper_1806_03461_amd/csrc/sums3.h"
 #include "fft512_inverse.h"
 
 using namespace fft512;
@@ -161,6 +165,8 @@ void product(const char *name, const Poly (&digit)[4], const Poly (&limb)[4]) {
 typedef double2 Lanes[4][64][8];        // [wave or polynomial][lane][register]
 Lanes g_x;
 double2 g_key[4][4][kHalf];             // [row][output][slot]
+double2 g_sum_key[kSumKeyWords];
+struct KeyRows { uint32_t word[4][2][kN]; };        // [row][component]
 
 Twiddle8 pass1() {
     Twiddle8 w;
@@ -171,8 +177,9 @@ Twiddle8 pass1() {
     w.sig0 = u[12]; w.sig1 = u[13]; w.tau = u[14]; w.tauh = u[15];
     return w;
 }
-void fold(const Poly (&p)[4], double scale) {
-    for (int r = 0; r < 4; ++r)
+template <class P>
+void fold(const P *p, int count, double scale) {
+    for (int r = 0; r < count; ++r)
         for (int L = 0; L < 64; ++L)
             for (int m = 0; m < 8; ++m)
                 g_x[r][L][m] = make_double2((double)p[r][L + 64 * m] * scale, (double)p[r][L + 64 * m + kHalf] * scale);
@@ -180,19 +187,38 @@ void fold(const Poly (&p)[4], double scale) {
 #define LANES for (int L = 0; L < 64; ++L)
 #define REGISTERS for (int k = 0; k < 8; ++k)
 
-// the key as the upload stores it: the steps of fft512.h, four outputs of a row at a time
+// the key as the upload stores it: the steps of fft512.h, four polynomials of a row at a time, gathered
+void transform_row() {
+    for (int w = 0; w < 4; ++w) LANES fwd_pass1_store(g_x[w][L], g_lane[L], g_buf + w * kPolyStride, L);
+    for (int w = 0; w < 4; ++w) {
+        LANES fwd_pass2_load(g_x[w][L], g_buf + row_of(w, L), L);
+        LANES fwd_pass2_store(g_x[w][L], g_lane[L], g_buf + row_of(w, L), L);
+        LANES fwd_pass3(g_x[w][L], g_buf + row_of(w, L), L);
+        gather_rows_wave(g_x[w]);
+    }
+}
 void store_key(const Poly (&limb)[4][4]) {
     for (int r = 0; r < 4; ++r) {
-        fold(limb[r], 1.0 / 512.0);
-        for (int w = 0; w < 4; ++w) LANES fwd_pass1_store(g_x[w][L], g_lane[L], g_buf + w * kPolyStride, L);
-        for (int w = 0; w < 4; ++w) {
-            LANES fwd_pass2_load(g_x[w][L], g_buf + row_of(w, L), L);
-            LANES fwd_pass2_store(g_x[w][L], g_lane[L], g_buf + row_of(w, L), L);
-            LANES fwd_pass3(g_x[w][L], g_buf + row_of(w, L), L);
-            gather_rows_wave(g_x[w]);
+        fold(limb[r], 4, 1.0 / 512.0);
+        transform_row();
+        for (int w = 0; w < 4; ++w)
             LANES for (int o = 0; o < 4; ++o)
                 for (int q = 0; q < 2; ++q) g_key[r][o][256 * q + 64 * w + L] = g_x[w][L][2 * o + q];
+    }
+}
+void store_sum_key(const KeyRows &key) {
+    std::fill(g_sum_key, g_sum_key + kSumKeyWords, make_double2(NAN, NAN));      // a word that is not written shows
+    std::vector<double> factor[4];
+    for (int r = 0; r < 4; ++r) {
+        for (int o = 0; o < 4; ++o) {
+            factor[o].assign(kN, 0.0);
+            for (int j = 0; j < kN && o < kSums; ++j) factor[o][j] = sum_factor(key.word[r][0][j], key.word[r][1][j], o);
         }
+        fold(factor, 4, 1.0 / 512.0);
+        transform_row();
+        for (int w = 0; w < 4; ++w)
+            LANES for (int o = 0; o < kSums; ++o)
+                for (int q = 0; q < 2; ++q) g_sum_key[sum_key_word(whole_register(L, q), o, r, whole_lane(w, L))] = g_x[w][L][2 * o + q];
     }
 }
 // inverse pass 1 and the pending cosines of one lane
@@ -208,10 +234,11 @@ void finish(double2 (&x)[8], int L, std::vector<double> &out) {
         out[L + 64 * m + kHalf] = x[m].y;
     }
 }
-double2 row_times_key(const double2 (&d)[4], int o, int slot) {
+template <class Key>
+double2 row_times_key(const double2 (&d)[4], Key &&key) {
     double2 y = make_double2(0.0, 0.0);
     for (int r = 0; r < 4; ++r) {
-        const double2 b = g_key[r][o][slot];
+        const double2 b = key(r);
         y = make_double2(fma(-d[r].y, b.y, fma(d[r].x, b.x, y.x)), fma(d[r].y, b.x, fma(d[r].x, b.y, y.y)));
     }
     return y;
@@ -219,7 +246,7 @@ double2 row_times_key(const double2 (&d)[4], int o, int slot) {
 
 // four waves per gate: wave r transforms polynomial r in pass 1 and holds rows 2 w, 2 w + 1 of all afterwards
 void step_four_waves(const Poly (&digit)[4], std::vector<double> (&out)[4]) {
-    fold(digit, 1.0);
+    fold(digit, 4, 1.0);
     const Twiddle8 w1 = pass1();
     for (int w = 0; w < 4; ++w) LANES {
         dft8_twiddled<false>(g_x[w][L], w1);
@@ -240,7 +267,7 @@ void step_four_waves(const Poly (&digit)[4], std::vector<double> (&out)[4]) {
             for (int o = 0; o < 4; ++o)
                 for (int q = 0; q < 2; ++q) {
                     const double2 d[4] = {x[L][q], x[L][2 + q], x[L][4 + q], x[L][6 + q]};
-                    y[2 * o + q] = row_times_key(d, o, 256 * q + 64 * w + L);
+                    y[2 * o + q] = row_times_key(d, [&](int r) { return g_key[r][o][256 * q + 64 * w + L]; });
                 }
             REGISTERS x[L][k] = y[k];
         }
@@ -258,8 +285,8 @@ void step_four_waves(const Poly (&digit)[4], std::vector<double> (&out)[4]) {
 }
 
 // one wave per gate: each polynomial through the wave's one buffer, lane = 8 k0 + (j0 or k1)
-void step_one_wave(const Poly (&digit)[4], std::vector<double> (&out)[4]) {
-    fold(digit, 1.0);
+void step_one_wave(const Poly (&digit)[4], std::vector<double> (&out)[kSums]) {
+    fold(digit, 4, 1.0);
     const Twiddle8 w1 = pass1();
     double2 p[8];
     auto mine = [&](int L) { return g_buf + (L >> 3) * kRowStride; };
@@ -274,9 +301,9 @@ void step_one_wave(const Poly (&digit)[4], std::vector<double> (&out)[4]) {
     }
     LANES REGISTERS {
         const double2 d[4] = {g_x[0][L][k], g_x[1][L][k], g_x[2][L][k], g_x[3][L][k]};
-        for (int o = 0; o < 4; ++o) g_x[o][L][k] = row_times_key(d, o, wave_slot_lane(L) + wave_slot_register(k));
+        for (int o = 0; o < kSums; ++o) g_x[o][L][k] = row_times_key(d, [&](int r) { return g_sum_key[sum_key_word(k, o, r, L)]; });
     }
-    for (int o = 0; o < 4; ++o) {
+    for (int o = 0; o < kSums; ++o) {
         double2 (&x)[64][8] = g_x[o];
         LANES radix8<true>(x[L]);
         LANES REGISTERS mine(L)[(L & 7) * kGrpStride + k] = x[L][k];
@@ -287,13 +314,12 @@ void step_one_wave(const Poly (&digit)[4], std::vector<double> (&out)[4]) {
     }
 }
 
-// both kernels' steps against exact integers; returns the number of wrong coefficients
+// the four-wave kernels' step against exact integers; returns the number of wrong coefficients
 long steps(const Poly (&digit)[4], const Poly (&limb)[4][4], double &worst) {
     store_key(limb);
-    std::vector<double> out[2][4];
-    for (auto &kernel : out) for (auto &o : kernel) o.assign(kN, 0.0);
-    step_four_waves(digit, out[0]);
-    step_one_wave(digit, out[1]);
+    std::vector<double> out[4];
+    for (auto &o : out) o.assign(kN, 0.0);
+    step_four_waves(digit, out);
     long wrong = 0;
     for (int o = 0; o < 4; ++o) {
         Poly want(kN, 0);
@@ -304,11 +330,32 @@ long steps(const Poly (&digit)[4], const Poly (&limb)[4][4], double &worst) {
                     if (i + j < kN) want[i + j] += v;
                     else want[i + j - kN] -= v;
                 }
-        for (auto &kernel : out)
-            for (int j = 0; j < kN; ++j) {
-                wrong += (int64_t)nearbyint(kernel[o][j]) != want[j];
-                worst = fmax(worst, fabs(kernel[o][j] - (double)want[j]));
-            }
+        for (int j = 0; j < kN; ++j) {
+            wrong += (int64_t)nearbyint(out[o][j]) != want[j];
+            worst = fmax(worst, fabs(out[o][j] - (double)want[j]));
+        }
+    }
+    return wrong;
+}
+// the wave kernel's step, both components mod 2^32; returns the number of wrong coefficients
+long sum_steps(const Poly (&digit)[4], const KeyRows &key) {
+    store_sum_key(key);
+    std::vector<double> out[kSums];
+    for (auto &o : out) o.assign(kN, 0.0);
+    step_one_wave(digit, out);
+    auto low_word = [](double v) { uint64_t b; std::memcpy(&b, &v, 8); return (uint32_t)b; };
+    long wrong = 0;
+    for (int j = 0; j < kN; ++j) {
+        uint32_t q = low_word(kIntegerShift + out[0][j]);
+        for (int c = 0; c < 2; ++c) {
+            uint32_t want = 0;
+            for (int r = 0; r < 4; ++r)
+                for (int i = 0; i < kN; ++i) {
+                    const uint32_t v = (uint32_t)digit[r][i] * key.word[r][c][(j - i) & (kN - 1)];
+                    want += i <= j ? v : 0u - v;
+                }
+            wrong += minus_product(q, low_word(kHalfShift - out[1 + c][j])) != 0u - want;
+        }
     }
     return wrong;
 }
@@ -365,6 +412,9 @@ int main() {
                 }
             if (rep == 2) fill([](int r, int j) { return j == 301 * (r + 1) % kN ? 511 : 0; }, random_limb);
             wrong += steps(digit, rows, worst);
+            static KeyRows key;
+            for (auto &row : key.word) for (auto &component : row) for (uint32_t &word : component) word = rep == 3 ? 0x80000000u - (next_u32() & 1) : next_u32();
+            wrong += sum_steps(digit, key);
         }
         printf("whole steps: wrong %ld largest distance %.3g\n", wrong, worst);
         g_wrong += wrong;

@@ -1,7 +1,7 @@
 """CPU run of the transforms of csrc/dft8.h (tests/host/dft8_exactness.cpp), in the form of either blind rotation, on
 random operands and on the ends of their ranges: the rounded products equal exact 64-bit integer ones, and no
 value is further from its integer than the bound derived for the transforms of fft512.h; and of whole steps
-lane by lane, with the key in slot order and each kernel's own exchanges and slot addresses."""
+lane by lane, with each kernel's own exchanges and with the key where the upload stores it for that kernel."""
 import os
 import re
 import shutil
