@@ -69,6 +69,64 @@ def test_small_batches_equal_the_four_wave_kernels():
     assert digests[0] == digests[1]
 
 
+_BOTH_FORMS = r"""
+import hashlib, sys
+import numpy as np, torch
+sys.path.insert(0, sys.argv[1])
+import paper_1806_03461_amd as T
+cus = torch.cuda.get_device_properties(0).multi_processor_count
+# rotation amounts are read 64 steps at a time: one step, and one to either side of a whole reading
+for n, bgbit, t, basebit in ((1, 10, 8, 2), (63, 10, 8, 2), (64, 10, 8, 2), (65, 10, 8, 2), (300, 8, 5, 3), (500, 10, 8, 2)):
+    sk, ck = T.tfhe_keygen(T.Params(n, 1024, 1, 2, bgbit, t, basebit, -15, -25), 900 + n)
+    # one workgroup per CU, two on every CU with some of their waves, whole ones
+    for count in (5, 4 * cus + 6, 6 * cus + 5):
+        amounts = (64 * np.arange(n + 1)[None, :] + np.arange(count)[:, None]) % 2048           # every one of 0 .. 2047, where there are as many
+        a = torch.from_numpy((amounts << 21).astype(np.uint32).view(np.int32)).cuda()
+        b, out = torch.zeros_like(a), torch.empty_like(a)
+        T.tfhe_gate_batch(ck, "NAND", a, b, out, count)
+        torch.cuda.synchronize()
+        print("digest", n, bgbit, count, hashlib.sha256(T.to_host(out).tobytes()).hexdigest(), flush=True)
+"""
+
+
+def test_step_counts_and_rotations_on_both_forms_equal_the_four_wave_kernels():
+    """The forms for one and for two workgroups per CU are different code: either with every rotation amount, with step counts
+    around the 64 amounts that are read at a time, and with another gadget base."""
+    found = []
+    for gates_from in ("1", "1000000000"):
+        env = {k: v for k, v in os.environ.items() if not k.startswith("TFHE_")}
+        env["TFHE_WAVE_GATES_FROM"] = gates_from
+        r = subprocess.run([sys.executable, "-c", _BOTH_FORMS, ROOT], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                           text=True, timeout=200)
+        assert r.returncode == 0, r.stdout
+        found.append([l for l in r.stdout.splitlines() if l.startswith("digest")])
+    assert len(found[0]) == 18 and len({l.split()[-1] for l in found[0]}) == 18 and found[0] == found[1], found
+
+
+def test_two_keys_on_two_streams():
+    """900 gates for each of two keys at a time, on two streams: the lone form's workgroups share the CUs.  The same bytes as
+    one key after the other, three times."""
+    import torch
+    import paper_1806_03461_amd as T
+    rng = np.random.default_rng(90)
+    keys = [T.tfhe_keygen(T.default_params(), seed)[1] for seed in (workloads.KEY_SEED, 5)]
+    a, b = (torch.from_numpy(rng.integers(0, 1 << 32, (900, 501), dtype=np.uint64).astype(np.uint32).view(np.int32)).cuda() for _ in range(2))
+    want, got = ([torch.empty_like(a) for _ in keys] for _ in range(2))
+    streams = [torch.cuda.Stream() for _ in keys]
+    for ck, out in zip(keys, want):
+        T.tfhe_gate_batch(ck, "XOR", a, b, out, 900)
+        torch.cuda.synchronize()
+    assert not torch.equal(*want)
+    for _ in range(3):
+        for out in got:
+            out.zero_()
+        torch.cuda.synchronize()
+        for ck, stream, out in zip(keys, streams, got):
+            T.tfhe_gate_batch(ck, "XOR", a, b, out, 900, stream=stream.cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 _EXTREMES = r"""
 import sys
 import torch
