@@ -33,21 +33,22 @@ struct KeySwitchArgs {
     int matrix;                  // use the matrix-core kernel (needs ksk_tiles, t = 8, basebit = 2, n + 1 <= 512)
 };
 
-// How long a blind rotation of `items` gates takes on a device with `cus` compute units, in milliseconds, as
-// measured on 256 of them (n = 500; other step counts scale all of it alike): what the launcher's choice of
-// kernels and the scheduler of narrow circuits go by.
-//   wave kernel       eight gates per CU at a time: 6.1 ms a round, 3.7 ms with at most four per CU in it,
-//                     5.1 ms with five or six, spread evenly over the CUs, 5.7 ms with seven
-//   four-wave kernels 1.5, 2.1 and 3.3 ms for one, two and three gates per CU, 5.5 ms for five
-// The table holds the times that schedules were last chosen by (6.4, 4.15, 5.4 to 5.85, 6.0; 1.55): with today's, schedules of
-// 6,000 to 120,000 gates come out within 0.6 % of the same estimated time, either way.
+// What the scheduler of narrow circuits weighs launches by: the milliseconds that a blind rotation of `items` gates took on a device
+// with `cus` compute units (256 of them, n = 500) before the wave kernel's step was cut as it is.  It takes now, by events around the rotation:
+//   wave kernel       eight gates per CU at a time: 6.0 ms a round, 3.68 with at most four per CU in it, 5.0 to 5.25 with five or six,
+//                     spread evenly over the CUs, 5.58 with seven
+//   four-wave kernels 1.46 to 1.48 ms, 1.90 to 2.08 and 2.99 to 3.26 for one, two and three gates per CU, 5.3 for five
+// The table is not these: filled by them, 213 dense layers of up to 110,000 gates whose schedule changes would by these times take 0.4 % less on
+// average (4 % less to 1.8 % more), ten scores of 256 inputs, measured, 52.9 ms instead of 53.5 and five other circuits the same within
+// 0.2 %, while of the 22,593 gates of 24 sorting networks of 64 inputs none would move.  The launcher's rule does not use it.
 inline double rest_ms(size_t per_cu) {      // a launch of less than a round
     const double ms[9] = {0.0, 1.55, 2.1, 3.32, 4.15, 5.4, 5.85, 6.0, 6.42};
     return ms[per_cu];
 }
 // The kernel that serves a batch's last, partial round fastest: the wave kernel together with the whole rounds or in a launch of its
-// own, or the four-wave kernels.  Five gates per CU: 1,025 gates 5.3 ms on the wave kernel and 5.65 on the four-wave ones, behind
-// a round 3,328 gates 12.1 and 11.95.
+// own, or the four-wave kernels.  Calls on the wave kernel and on the four-wave ones: four gates per CU, 1,024 gates 3.77 and 5.48 ms,
+// 3,072 (behind a round) 10.6 and 11.95; five, 1,025 gates 5.33 and 5.93, 1,280 gates 5.16 and 5.97, behind a round 3,073 gates
+// 12.62 and 12.51, 3,328 gates 11.97 and 11.96.
 enum class RestKernel { kFourWaves, kWave, kWithRounds };
 inline RestKernel rest_kernel(size_t per_cu, bool behind_rounds) {
     if (per_cu >= 7) return RestKernel::kWithRounds;

@@ -1416,11 +1416,11 @@ static_assert(kRoundPerCu == 2 * kWaveGates, "two workgroups of the wave kernel 
 
 // Items first .. count - 1 with the wave kernel.  With more than one workgroup per CU the waves of a workgroup meet before the
 // products, so that their key reads hit L1 (8,192 gates 26.0 -> 25.2 ms); a lone workgroup leaves L1 and L2 idle enough
-// and loses by waiting (1,024 gates 4.15 ms without, 4.54 with, when that was measured; 3.8 now).
+// and loses by waiting (a call of 1,024 gates 3.77 ms on the form without, 4.50 on the form with).
 // Five or six gates per CU are spread over two workgroups on every CU instead of filling half of the CUs with two whole ones:
-// 1,025 gates 5.65 -> 5.3 ms, 1,536 gates 5.82 -> 5.44 (5.2 now).  Seven are not: the CUs that end early leave the others their power
-// (1,554 gates 5.68 ms as they are, 5.93 spread).  Four at a time and the others in a launch of their own is slower: 1,280 gates 5.37
-// against 5.20 ms, 1,536 gates 5.91 against 5.23.
+// calls of 1,280 gates 5.52 -> 5.16 ms, 1,536 gates 5.64 -> 5.16, 3,584 gates 12.5 -> 11.85.  Seven are not: the CUs that end early
+// leave the others their power (1,554 gates 5.66 ms as they are, 5.90 spread; 1,792 gates 5.84 and 6.01).  Four at a time and the others in
+// a launch of their own is slower: 1,280 gates 5.37 against 5.20 ms, 1,536 gates 5.91 against 5.23.
 // Two lone launches for two keys, on two streams, do share the CUs (see the kernel).
 static int launch_wave(const BlindRotateArgs &a, size_t cus, hipStream_t stream) {
     const size_t items = a.count - a.first, least = (items + kWaveGates - 1) / kWaveGates;
