@@ -270,7 +270,7 @@ int bnn_conv_encrypted(tfhe_cloud_key *ck, const uint32_t *x, int C, int H, int 
 
 /* Kernel-time accounting of server-side calls on a cloud key: when enabled, the blind rotation
  * and the key switch of every batch (a level of a circuit or a batched call, in chunks of 262,144
- * items) are bracketed by HIP events on the call's stream.  A batch's blind rotation is one to three
+ * items) are bracketed by HIP events on the call's stream.  A batch's blind rotation is one or two
  * kernel launches, its key switch two; blind_rotate_launches and key_switch_launches count batches.
  * tfhe_profile_read synchronises the stream's events and returns accumulated milliseconds
  * and counts since the last reset.  Recording never waits for the device. */

@@ -174,14 +174,17 @@ __device__ __forceinline__ Twiddle8 pass1_twiddles(const_double *u) {
 
 // A step's key values of one thread come in four parts of 8 (32 registers): part p = 2 q + h holds
 // rows r = 0..3 x outputs o = 2h, 2h+1 at the thread's slot 256 q + tid.
-// AHEAD: the variants for one or two workgroups per CU request the whole key row of step i + 1 while step i still runs, in
-// eight portions of four loads placed between the phases that follow the products of step i.
+// AHEAD: the variants for one or two workgroups per CU request the key row in eight portions of four loads, ahead of the products that
+// use it.  With two workgroups all eight are of the row of step i + 1 and stand between the phases that follow the products of step i.
 // LONE: one workgroup per CU.  A portion keeps the CU's one address unit busy for 4 x 16 clocks per wave, and a wave alone
-// on its SIMD cannot issue anything else meanwhile, so all 32 loads in one place stall all four waves.  Where the portions stand was
-// searched for, with the places the scheduler may not move instructions across: the four waves run in step, and a load that waits
-// for the address unit delays everything behind it.  About 250 arrangements were timed: one portion after each of eight phases 1.530 ms
-// for 8 gates and 1.588 for 256; this one -- two after the products, two and one in the waits for the inverse exchanges, one and two
-// behind the step's last and first barriers -- 1.482 and 1.524; most others 1.50 to 1.64.
+// on its SIMD cannot issue anything else meanwhile, so all 32 loads in one place stall all four waves.  Six portions are of step i + 1: two
+// after the products, two and one in the waits for the inverse exchanges, one behind the step's last barrier; the other two (3 and 7)
+// are of step i itself, behind its first barrier, still an exchange and two passes ahead of their use.  All stand where the wave waits
+// anyway; which of these places, and which of them the scheduler may not move instructions across, was found by timing about 250
+// arrangements: one portion after each of eight phases 1.530 ms for 8 gates and 1.588 for 256, this one 1.482 and 1.524, most
+// others 1.50 to 1.64.  What tells them apart is how four waves in step meet at the address unit and at LDS, which no rule here predicts:
+// another compiler's order of instructions may want another one.  The way from L2 is longer than with single portions (counted 104
+// clocks then, 178 to 189 now that portions stand in pairs) and is covered.
 // Two workgroups per CU hide that behind each other; there the last two portions go with earlier ones, a step's length
 // ahead of their use, which also saves the registers of the loads in flight across forward passes 2 and 3 (301 gates 1.96 -> 1.94 ms, and no scratch).
 // At three workgroups per CU the others cover the loads and holding registers for them does not pay:
@@ -533,7 +536,7 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 }
 
 // The same step for batches of at most one gate per CU, where a gate's latency is all that
-// counts: the whole key row of step i + 1 is requested while step i still runs.
+// counts: six of the eight portions of a key row are requested a step ahead, the other two in the step.
 template <bool MARGIN>
 __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu(1, 1))) void blind_rotate_latency_kernel(BlindRotateArgs a) {
     blind_rotate_body<MARGIN, 4, true>(a);
@@ -553,11 +556,11 @@ __global__ __launch_bounds__(kThreadsPerGate) __attribute__((amdgpu_waves_per_eu
 //
 // What bounds it: vector issue, LDS and the key stream through L1 side by side, at a clock that power lowers (2.18 GHz in whole rounds,
 // 2.39 with a workgroup per CU).  An exchange of a polynomial (8 KB) costs its wave eight stores of 28 clocks of issue and eight
-// loads of about 14, and the CU's LDS 13 and 5 clocks each, whatever their width: fourteen exchanges are about 2,000 clocks of LDS
-// a gate-step beside 2,240 of vector issue.  So at most one exchange stands in a region between two scheduling barriers, its stores nine vector
-// instructions apart, and one more piece of arithmetic comes before its result is used; the step's first reads go before the
-// rounding of the step before.  Against two exchanges in a region, closer and used at once: 1,024 gates 4.47 -> 3.84 ms, 16,384 gates
-// 51.8 -> 49.4, 65,536 gates 206.0 -> 200.0 (four sums 236, the four-wave kernel 284).
+// loads of about 14, and the CU's LDS 13 and 5 clocks each (a 16-byte store as two of 8 bytes costs the same): fourteen exchanges are about
+// 2,000 clocks of LDS a gate-step beside 2,240 of vector issue.  So at most one exchange stands in a region between two scheduling barriers,
+// its stores nine vector instructions apart, and, but for the step's first, one more piece of arithmetic comes before its result is
+// used; the step's first reads go before the rounding of the step before.  Calls, against two exchanges in a region, closer and used
+// at once: 1,024 gates 4.26 -> 3.80 ms, 16,384 gates 52.2 -> 49.8, 65,536 gates 205.5 -> 199.8 (four sums 236, the four-wave kernel 284).
 // Without the barrier before the products + 1 %; without any exchange - 15 %, without key loads - 8 % (half of which is clock), without both
 // - 27 % (with the exchanges as they stood before).  Key rows brought to LDS and read from there by all four waves instead of four L1
 // reads: equal.  Products spread over the forward half, a digit polynomial or a component at a time: registers spill.
@@ -584,9 +587,10 @@ static_assert(kFwd2 < kInv2 && kInv2 < kInv1 && kInv1 < kFwd3, "the table's orde
 static_assert(2 * sizeof(WaveLds) <= 160 * 1024, "two workgroups share a CU's LDS");
 
 // Scheduling patterns of the instructions between two region ends.  EXCHANGE: eight stores to LDS, then eight loads, each followed by nine
-// vector instructions of other work as long as there is any.  A store of 16 bytes a lane holds its wave's issue for 28 clocks if another
-// LDS instruction follows and for 10 behind enough arithmetic; loads may stand together (nine against three: 1,024 gates 3.99 against
-// 4.40 ms, 16,384 gates 51.9 against 53.3).  KEYS: a key load, then four multiply-adds, instead of four loads in a row.
+// vector instructions of other work as long as there is any.  A store of 16 bytes a lane holds its wave's issue for 28 clocks, and for 52
+// where four waves store in step, unless six or more multiply-adds stand behind each (nine against five and three:
+// 1,024 gates 3.80, 3.98 and 4.47 ms, 16,384 gates 49.8, 51.3 and 52.0).  KEYS: a key load, then four multiply-adds,
+// instead of four loads in a row (16,384 gates 50.1 -> 49.8 ms).
 #define REGION_END() __builtin_amdgcn_sched_barrier(0)
 #define ONE_OF(KIND, V) __builtin_amdgcn_sched_group_barrier(KIND, 1, 0); __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
 #define FOUR_OF(KIND, V) ONE_OF(KIND, V) ONE_OF(KIND, V) ONE_OF(KIND, V) ONE_OF(KIND, V)
@@ -596,7 +600,7 @@ static_assert(2 * sizeof(WaveLds) <= 160 * 1024, "two workgroups share a CU's LD
 template <bool MARGIN, bool SHARE>
 __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu(2, 2))) void blind_rotate_wave_kernel(BlindRotateArgs a) {
     // Key batches (one sum at one frequency: four 16-byte loads) in registers.  A lone wave covers the way from L2 with one more
-    // (1,024 gates 3.98 -> 3.90 ms); with two on a SIMD five or six are no faster than four.
+    // (1,024 gates 3.92 -> 3.80 ms); with two on a SIMD five or six are no faster than four.
     constexpr int kKeyRing = SHARE ? 4 : 5;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     WaveLds &my = *reinterpret_cast<WaveLds *>(lds_raw);
@@ -676,8 +680,8 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         back4 = (uint32_t)(0 - __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(bars, i & 63))) << 2;
     };
     // Rotated and plain reads of a component (see blind_rotate_body for the mirror and the sign).  A lone wave pays for every scalar
-    // instruction: it keeps the sixteen addresses of component 0 for component 1 (1,024 gates 3.88 -> 3.82 ms).  With two waves on a
-    // SIMD that is slower (16,384 gates 50.9 -> 51.6 ms).
+    // instruction: it keeps the sixteen addresses of component 0 for component 1 (1,024 gates 3.86 -> 3.80 ms).  With two waves on a
+    // SIMD that is slower (16,384 gates 49.8 -> 50.5 ms).
     typedef __attribute__((address_space(3))) const uint32_t lds_word;
     const uint32_t lane_at = (uint32_t)(uintptr_t)(lds_word *)acc[0] + ((uint32_t)L << 2);
     uint32_t rot[8][2], own[8][2], at[8][2];
@@ -781,7 +785,9 @@ __global__ __launch_bounds__(64 * kWaveGates) __attribute__((amdgpu_waves_per_eu
         };
 
         // ---- forward: four polynomials.  An exchange stands beside the arithmetic of another polynomial, and one more piece of arithmetic
-        // comes between it and its own polynomial's next pass, so that its latency is covered too: at most one exchange a region ----
+        // comes between it and its own polynomial's next pass, so that its latency is covered too: at most one exchange a region.  The
+        // step's beginning has no other arithmetic yet: polynomial 1's first exchange stands beside the reads of component 1 alone, and
+        // is what comes between polynomial 0's first exchange and its next pass ----
         {
             double2 p[8];
             load_twiddles(my.constants, 8, L >> 3, p);
